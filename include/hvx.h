@@ -113,7 +113,9 @@ typedef int32_t hvx_status;
 #define HVX_QUERY_ROWS_PER_ITEM 10 /* rows per work item of the first kernel */
 #define HVX_QUERY_NUM_GENERATED 11 /* kernels of the plan generated for their group (HVX_OPT_CODEGEN) */
 #define HVX_QUERY_PLAN_CUTS 12     /* values at which the plan choice in force cuts fusion */
-#define HVX_QUERY_GEN_TILE 13      /* tile of the first generated tile kernel: width << 16 | height (0: none) */
+#define HVX_QUERY_GEN_TILE 13      /* tile of the first generated kernel with a local operator: width << 16 |
+                                      height (0: none); of a streamed one, the columns of a strip and the
+                                      number its bands' rows are a multiple of */
 
 /* ---- context ------------------------------------------------------------ */
 

@@ -14,9 +14,9 @@ CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(os.path.dirname(HERE), "_build")
 LIB = os.path.join(HERE, "libhvx.so")
 
-SOURCES = ["api.cpp", "verify.cpp", "runtime.cpp", "server.cpp", "expr.cpp", "codegen.cpp", "kernels.hip", "global.hip"]
+SOURCES = ["api.cpp", "verify.cpp", "runtime.cpp", "server.cpp", "expr.cpp", "codegen.cpp", "codegen_stream.cpp", "kernels.hip", "global.hip"]
 # device headers compiled again, with the generated kernels, by hipRTC at run time
-RTC_HEADERS = ["hvx_desc.h", "gen_abi.h", "dev_phase.hpp", "dev_reduce.hpp", "dev_generic.hpp"]
+RTC_HEADERS = ["hvx_desc.h", "gen_abi.h", "dev_phase.hpp", "dev_reduce.hpp", "dev_generic.hpp", "dev_stream.hpp"]
 
 ARCH = os.environ.get("HVX_OFFLOAD_ARCH", "gfx950")
 COMMON = [

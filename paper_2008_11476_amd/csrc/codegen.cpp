@@ -14,13 +14,14 @@
 // pitch and LDS offset is a literal, so a read is one LDS access with a
 // constant offset.  Tiles whose halo lies inside the image take a body
 // without border tests; the others apply each operator's border rule.
-#include "codegen.h"
+#include "codegen_emit.h"
 
 #include <hip/hiprtc.h>
 
+#include <math.h>
+
 #include <algorithm>
 #include <array>
-#include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -42,57 +43,6 @@ extern const int kRtcHeaderCount;
 extern const char* const kRtcHeaderNames[];
 extern const char* const kRtcHeaderTexts[];
 
-namespace {
-
-constexpr int kGenThreads = 256;
-constexpr int kGenLdsBytes = 48 * 1024;
-constexpr int kMaxDevices = 64;
-
-bool is_local(int kind) { return !is_point_op(kind) && !is_global_op(kind); }
-
-struct Text {
-  std::string s;
-  void operator()(const char* fmt, ...) __attribute__((format(printf, 2, 3))) {
-    char buf[1024];
-    va_list ap;
-    va_start(ap, fmt);
-    int n = vsnprintf(buf, sizeof buf, fmt, ap);
-    va_end(ap);
-    if (n >= (int)sizeof buf) {
-      std::vector<char> big(n + 1);
-      va_start(ap, fmt);
-      vsnprintf(big.data(), big.size(), fmt, ap);
-      va_end(ap);
-      s += big.data();
-    } else {
-      s += buf;
-    }
-    s += '\n';
-  }
-};
-
-std::string fmt(const char* f, ...) __attribute__((format(printf, 1, 2)));
-std::string fmt(const char* f, ...) {
-  char buf[512];
-  va_list ap;
-  va_start(ap, f);
-  vsnprintf(buf, sizeof buf, f, ap);
-  va_end(ap);
-  return buf;
-}
-
-std::string float_lit(float f) {
-  uint32_t u;
-  memcpy(&u, &f, 4);
-  return fmt("__builtin_bit_cast(float, 0x%08xu)", u);
-}
-
-// A Convolve mask that is the outer product of a column and a row of
-// integers, m[j][i] = a[j] b[i], as those two factors (b divided by the gcd
-// of its entries; every integer factorisation is a multiple of that one).
-// Summing each window column with the weights a and then the column sums
-// with the weights b gives the same 32-bit wrapped sum as the mask itself,
-// since the two double sums are equal as integers.
 bool conv_rank_one(const GOp& o, int a[5], int b[5]) {
   const int cols = o.p0, rows = o.p1;
   int j0 = -1;
@@ -115,6 +65,18 @@ bool conv_rank_one(const GOp& o, int a[5], int b[5]) {
       if (o.mask[j * cols + i] != a[j] * b[i]) return false;
   }
   return true;
+}
+
+namespace {
+
+constexpr int kGenThreads = 256;
+constexpr int kGenLdsBytes = 48 * 1024;
+constexpr int kMaxDevices = 64;
+
+std::string float_lit(float f) {
+  uint32_t u;
+  memcpy(&u, &f, 4);
+  return fmt("__builtin_bit_cast(float, 0x%08xu)", u);
 }
 
 // column-first costs (4 + 2 rx) column sums of the non-zero weights of a
@@ -251,10 +213,12 @@ bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, std::string
   return true;
 }
 
-void emit_prelude(Text& t, const GProg& P, std::string* why, bool* ok) {
+}  // namespace
+
+void emit_prelude(Text& t, const GProg& P, const char* header, std::string* why, bool* ok) {
   t("namespace __hip_internal {}");
   t("using namespace __hip_internal;");
-  t("#include \"dev_generic.hpp\"");
+  t("#include \"%s\"", header);
   t("#include \"gen_abi.h\"");
   t("namespace hvx {");
   t("__device__ __forceinline__ int gx_add(int a, int b) { return (int)((uint32_t)a + (uint32_t)b); }");
@@ -317,12 +281,14 @@ void emit_prelude(Text& t, const GProg& P, std::string* why, bool* ok) {
   t("using namespace hvx;");
 }
 
+namespace {
+
 // ---- the point form ----------------------------------------------------------
 
 bool emit_points(const GProg& P, uint32_t stream, GenSource* out, std::string* why) {
   Text t;
   bool ok = true;
-  emit_prelude(t, P, why, &ok);
+  emit_prelude(t, P, "dev_generic.hpp", why, &ok);
   if (!ok) return false;
   t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen(const GProg* __restrict__ P, const IOTable io0,",
     kGenThreads);
@@ -855,6 +821,7 @@ struct StageEmitter {
   }
 };
 
+// the tile form without the prelude
 bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSource* out, std::string* why) {
   Layout L;
   plan_stages(P, L);
@@ -891,9 +858,6 @@ bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSour
   const int LW = std::max(4, L.lds_words + hist_words);
 
   Text t;
-  bool ok = true;
-  emit_prelude(t, P, why, &ok);
-  if (!ok) return false;
   t("__device__ constexpr int gx_zero4[4] = {0, 0, 0, 0};");
   // LDS is read and written in whole 16-byte units: consecutive lanes then
   // touch consecutive banks.  A read whose components are not all used would
@@ -999,6 +963,7 @@ bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSour
 
 struct GenKernel {
   int form = 0, tw = 0, th = 0;
+  int ext = 0;
   bool red = false;
   int lds_words = 0;
   std::vector<char> code;
@@ -1037,14 +1002,37 @@ bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out,
     any_red |= is_reduce_op(kind);
   }
   if (!any_local && !any_red) return emit_points(P, stream, out, why);
-  return emit_tiles(P, tw, th, stream, out, why);
+  // One source holds the forms the group can take; the kernel compiled from
+  // it is the tile form, or with HVX_GEN_STREAM_ONLY defined the streaming one.
+  GenSource strip, tiles;
+  std::string no_strip;
+  const bool can_stream = emit_stream(P, stream, &strip, &no_strip);
+  const bool can_tile = emit_tiles(P, tw, th, stream, &tiles, why);
+  if (tw > 0 ? !can_tile : !can_tile && !can_stream) return false;
+  Text t;
+  bool ok = true;
+  emit_prelude(t, P, can_stream ? "dev_stream.hpp" : "dev_generic.hpp", why, &ok);
+  if (!ok) return false;
+  // The streaming form is the faster one at every size measured, from
+  // 320x240 (Tomasi 15.2 against 8.0 us a frame) to 32 frames of 3840x2160
+  // (1305 against 515 us); small images of the graphs that a launch's fixed
+  // cost bounds take the same time either way.  A chosen tile asks for tiles.
+  const bool use_stream = can_stream && tw == 0;
+  *out = use_stream ? strip : tiles;
+  if (can_tile) t.s += can_stream ? "#ifndef HVX_GEN_STREAM_ONLY\n" + tiles.text + "#endif\n" : tiles.text;
+  if (can_stream) t.s += strip.text;
+  out->text = t.s;
+  return true;
 }
 
 const GenKernel* gen_compile(const GenSource& src, std::string* why) {
   std::lock_guard<std::mutex> l(g_cache_mu);
-  auto it = g_cache->find(src.text);
+  const bool stream = src.form == GEN_STREAM;
+  const std::string key = (stream ? "stream " : "") + src.text;
+  auto it = g_cache->find(key);
   if (it != g_cache->end()) return it->second;
-  if (const char* dir = getenv("HVX_GEN_DUMP")) {  // the sources, for reading
+  const char* dir = getenv("HVX_GEN_DUMP");  // the sources, for reading
+  if (dir && !g_cache->count(src.text) && !g_cache->count("stream " + src.text)) {
     const std::string path = std::string(dir) + "/hvx_gen_" + std::to_string(g_cache->size()) + ".hip";
     if (FILE* f = fopen(path.c_str(), "w")) {
       fputs(src.text.c_str(), f);
@@ -1059,7 +1047,7 @@ const GenKernel* gen_compile(const GenSource& src, std::string* why) {
     return nullptr;
   }
   const char* opts[] = {"--offload-arch=" HVX_ARCH, "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-                        "-packed-fp32-ops", "-w"};
+                        "-packed-fp32-ops", "-w", stream ? "-DHVX_GEN_STREAM_ONLY" : "-DHVX_GEN_TILES"};
   const hiprtcResult r = hiprtcCompileProgram(prog, (int)(sizeof opts / sizeof opts[0]), opts);
   if (r != HIPRTC_SUCCESS) {
     size_t n = 0;
@@ -1079,9 +1067,10 @@ const GenKernel* gen_compile(const GenSource& src, std::string* why) {
   k->form = src.form;
   k->tw = src.tw;
   k->th = src.th;
+  k->ext = src.ext;
   k->red = src.red;
   k->lds_words = src.lds_words;
-  (*g_cache)[src.text] = k;
+  (*g_cache)[key] = k;
   return k;
 }
 
@@ -1094,7 +1083,7 @@ hipError_t gen_load(const GenKernel* kc, int device) {
   hipError_t e = hipModuleLoadData(&m, k->code.data());
   if (e != hipSuccess) return e;
   hipFunction_t f = nullptr;
-  e = hipModuleGetFunction(&f, m, "hvx_gen");
+  e = hipModuleGetFunction(&f, m, k->form == GEN_STREAM ? "hvx_gen_stream" : "hvx_gen");
   if (e != hipSuccess) {
     (void)hipModuleUnload(m);
     return e;
@@ -1104,20 +1093,18 @@ hipError_t gen_load(const GenKernel* kc, int device) {
   return hipSuccess;
 }
 
+// threads of a work-group: a streamed item is one wave's
+static unsigned gen_threads(const GenKernel* k) { return k->form == GEN_STREAM ? 64 : kGenThreads; }
+
 hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
                       int num_cus, hipStream_t s, uint32_t* ws) {
   if (device < 0 || device >= kMaxDevices || !k->fn[device]) return hipErrorInvalidDeviceFunction;
-  long long grid;
-  if (k->form == GEN_POINTS) {
-    grid = (long long)((P.w + 1023) >> 10) * P.h;
-  } else {
-    // One work-group per tile (a persistent grid of as many groups as fit
-    // the CUs measured slower: the hardware's own dispatch of short groups
-    // overlaps one group's loads with another's arithmetic as well).  A
-    // group that reduces writes its partial results to its slot of `ws`.
-    grid = (long long)((P.w + k->tw - 1) / k->tw) * ((P.h + k->th - 1) / k->th);
-    (void)num_cus;
-  }
+  // One work-group per tile (a persistent grid of as many groups as fit
+  // the CUs measured slower: the hardware's own dispatch of short groups
+  // overlaps one group's loads with another's arithmetic as well).  A
+  // group that reduces writes its partial results to its slot of `ws`.
+  int rows = gen_rows(k, (long long)gen_strips(k, P.w) * P.h, num_cus);
+  const long long grid = gen_blocks(k, P.w, P.h, rows);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (k->red && !ws) return hipErrorInvalidValue;
@@ -1125,12 +1112,30 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GPro
   IOTable t = io;
   const GenBatchImage* none = nullptr;
   int zero = 0;
-  void* args[] = {(void*)&p, (void*)&t, (void*)&none, (void*)&zero, (void*)&ws};
-  return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, kGenThreads, 1, 1, 0, s, args, nullptr);
+  void* args[] = {(void*)&p, (void*)&t, (void*)&none, (void*)&zero, (void*)&ws, (void*)&rows};
+  return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
-long long gen_blocks(const GenKernel* k, int w, int h) {
+int gen_rows(const GenKernel* k, long long strip_rows, int num_cus) {
+  if (k->form != GEN_STREAM) return 0;
+  // Bands of r rows cost strip_rows / r items of r + ext + 3 steps each (the
+  // steps before the first output row run part of the operators; 3 stand for
+  // an item's start), shared by the SIMDs, plus about one item's latency at
+  // the end, a step of a wave alone taking some 2.5 times its issue: the sum
+  // is least at r^2 = 0.4 strip_rows (ext + 3) / SIMDs.  Measured: 1080p and
+  // smaller frames are fastest at 4 rows (Tomasi 14.5 us against 20.0 at 16),
+  // one 4K frame at 4 to 12, batches at 20 to 32 (32 4K frames: Tomasi
+  // 515 us at 32 rows, 647 at 4, 553 at 96).
+  const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
+  const double r = sqrt(0.4 * (double)strip_rows * (k->ext + 3) / simds);
+  return std::min(std::max((int)(r / k->th + 0.5), 1), 32 / k->th) * k->th;
+}
+
+int gen_strips(const GenKernel* k, int w) { return k->form == GEN_STREAM ? (w + k->tw - 1) / k->tw : 0; }
+
+long long gen_blocks(const GenKernel* k, int w, int h, int rows) {
   if (k->form == GEN_POINTS) return (long long)((w + 1023) >> 10) * h;
+  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * ((h + rows - 1) / rows);
   return (long long)((w + k->tw - 1) / k->tw) * ((h + k->th - 1) / k->th);
 }
 
@@ -1146,13 +1151,9 @@ hipError_t gen_launch_batch(const GenKernel* k, int device, const GenBatchImage*
   IOTable t;
   memset(&t, 0, sizeof t);
   uint32_t* ws = nullptr;
-  void* args[] = {(void*)&p, (void*)&t, (void*)&imgs, (void*)&n, (void*)&ws};
-  return hipModuleLaunchKernel(k->fn[device], (unsigned)blocks, 1, 1, kGenThreads, 1, 1, 0, s, args, nullptr);
-}
-
-void gen_tile(const GenKernel* k, int* tw, int* th) {
-  *tw = k->tw;
-  *th = k->th;
+  int rows = 0;  // each image's own
+  void* args[] = {(void*)&p, (void*)&t, (void*)&imgs, (void*)&n, (void*)&ws, (void*)&rows};
+  return hipModuleLaunchKernel(k->fn[device], (unsigned)blocks, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
 }  // namespace hvx

@@ -25,12 +25,14 @@ struct GenKernel;
 enum GenForm : int32_t {
   GEN_POINTS = 1,  // point operators only: four pixels of one row per thread, no LDS
   GEN_TILES = 2,   // LDS tiles with halos; work-groups loop over tiles when the group reduces
+  GEN_STREAM = 3,  // a wave streams a strip of columns down a band of rows, values in registers
 };
 
 struct GenSource {
   std::string text;
   int form = 0;
-  int tw = 0, th = 0;  // output tile (GEN_TILES)
+  int tw = 0, th = 0;  // output tile (GEN_TILES); columns of a strip, and what a band's rows are a multiple of (GEN_STREAM)
+  int ext = 0;         // rows a band reads beyond its own, on each side (GEN_STREAM)
   bool red = false;    // reduces global operators over the image
   int lds_words = 0;   // static LDS of one work-group
 };
@@ -42,8 +44,9 @@ struct GenSource {
 // that kernel reads at run time).
 bool gen_wanted(const GProg& P);
 
-// Emit the kernel of program P with an output tile of tw x th (0: the
-// largest that fits the LDS budget).  Bit i of `stream` marks value i as an
+// Emit the kernel of program P: with an output tile of tw x th, or, where
+// they are 0, streamed if P and its size allow it, else with the largest tile
+// that fits the LDS budget.  Bit i of `stream` marks value i as an
 // output that no later kernel reads (written with non-temporal stores).
 // False, with the reason, if P cannot be generated at that tile.
 bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out, std::string* why);
@@ -61,12 +64,15 @@ hipError_t gen_load(const GenKernel* k, int device);
 hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
                       int num_cus, hipStream_t s, uint32_t* ws);
 
-// Tile of a generated kernel (0 x 0 for the point form).
-void gen_tile(const GenKernel* k, int* tw, int* th);
+// Strips of an image of the given width, and the rows of a band where one
+// launch runs strips of the given total height (0 for the other forms).
+int gen_strips(const GenKernel* k, int w);
+int gen_rows(const GenKernel* k, long long strip_rows, int num_cus);
 
 // Work-groups the kernel launches for one w x h image when run over a batch
-// (one per tile, or one per 1024 pixels of a row for the point form).
-long long gen_blocks(const GenKernel* k, int w, int h);
+// (one per tile, one per 1024 pixels of a row for the point form, one per
+// strip and band of `rows` rows for the streaming form).
+long long gen_blocks(const GenKernel* k, int w, int h, int rows);
 
 // Whether one launch can run the kernel over a batch of images (a kernel
 // that reduces global operators cannot: each image has its own result).

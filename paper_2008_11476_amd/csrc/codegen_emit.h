@@ -1,0 +1,63 @@
+// Source emission shared by the forms of generated kernels (codegen.cpp: tiles
+// and points; codegen_stream.cpp: streamed strips).
+#pragma once
+#include <cstdarg>
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "codegen.h"
+
+namespace hvx {
+
+inline std::string fmt(const char* f, ...) __attribute__((format(printf, 1, 2)));
+inline std::string fmt(const char* f, ...) {
+  char buf[512];
+  va_list ap;
+  va_start(ap, f);
+  vsnprintf(buf, sizeof buf, f, ap);
+  va_end(ap);
+  return buf;
+}
+
+struct Text {
+  std::string s;
+  void operator()(const char* fmt, ...) __attribute__((format(printf, 2, 3))) {
+    char buf[1024];
+    va_list ap;
+    va_start(ap, fmt);
+    int n = vsnprintf(buf, sizeof buf, fmt, ap);
+    va_end(ap);
+    if (n >= (int)sizeof buf) {
+      std::vector<char> big(n + 1);
+      va_start(ap, fmt);
+      vsnprintf(big.data(), big.size(), fmt, ap);
+      va_end(ap);
+      s += big.data();
+    } else {
+      s += buf;
+    }
+    s += '\n';
+  }
+};
+
+// an operator that reads its input at window offsets
+inline bool is_local(int kind) { return !is_point_op(kind) && !is_global_op(kind); }
+
+// A Convolve mask that is the outer product of a column and a row of
+// integers, m[j][i] = a[j] b[i], as those two factors (b divided by the gcd
+// of its entries; every integer factorisation is a multiple of that one).
+// Summing each window column with the weights a and then the column sums
+// with the weights b gives the same 32-bit wrapped sum as the mask itself,
+// since the two double sums are equal as integers.
+bool conv_rank_one(const GOp& o, int a[5], int b[5]);
+
+// Includes, user kernels as functions (gx_expr<k>) and each operator as a
+// constant (gop<k>); `header` is the device header the form needs.
+void emit_prelude(Text& t, const GProg& P, const char* header, std::string* why, bool* ok);
+
+// The streaming form of program P without the prelude (codegen_stream.cpp);
+// false, with the reason, for a program it does not cover.
+bool emit_stream(const GProg& P, uint32_t nt, GenSource* out, std::string* why);
+
+}  // namespace hvx

@@ -1,0 +1,711 @@
+// The streaming form of a generated kernel: a wave streams a strip of image
+// columns down a band of rows, every value of the group in registers.
+//
+// At step t the newest row of value v is row t + ext(v) (ext: the rows of v
+// its consumers still need beyond the outputs), so the outputs' row t is
+// complete at the end of the step.  Each value keeps the rows its readers
+// reach back to; the loop is unrolled, so advancing them is renaming.  A
+// local operator combines its window rows vertically first and fetches the
+// neighbouring lanes' pixels of the result only.  The steps before a band's
+// first output row run only the operators whose rows are needed.
+//
+// Against the tile form, nothing passes through LDS and nothing waits for
+// other waves, rows above and below are computed once per band instead of
+// once per tile, and 16-bit values are held two to a register.  The 16-bit
+// arithmetic is used only where every intermediate result provably fits (the
+// ranges of all values are tracked below, from the formats and the
+// operators); everything else runs in 32 bits, with the same definitions as
+// the tile form.  Waves whose strip and band lie inside the image run a body
+// without border code.
+//
+// What bounds it: over batches VALU issue (Tomasi: 264 instructions a row of
+// 248 pixels, 32 3840x2160 frames 0.52 ms, all of it issue; in tiles 1.35 ms),
+// on single frames the latency of one wave's steps and the launch.  Measured
+// a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.4 us, FChain 4K
+// 35.2 -> 19.2, Tomasi 4K 49 -> 28, the F32 corner response at 1021x1019
+// 13.7 -> 8.2, Median -> Sobel -> Magnitude -> NonMaxSuppression at 1080p
+// 19.4 -> 14.1.
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+
+#include "codegen_emit.h"
+
+namespace hvx {
+namespace {
+
+// Rows per loop iteration, of which bands are a multiple; the next four rows
+// are loaded while four are computed.
+constexpr int kUnroll = 4;
+
+struct Val {
+  bool wide = false;       // S32 / F32: one register per pixel
+  long long lo = 0, hi = 0;  // integer values (border constants of its readers included)
+  bool nz = false;         // F32: never -0
+  int depth = 1;           // rows held
+  int rx = 0, ry = 0;      // largest radius of the local operators reading it
+  int mode = -1, c = 0;    // their border rule (-1: no local reader)
+};
+
+struct Term {  // a user kernel's subexpression on pairs
+  std::string s;
+  long long lo, hi;
+  bool lit;
+};
+
+bool fits16(long long lo, long long hi) { return lo >= -32768 && hi <= 32767; }
+
+struct Planner {
+  const GProg& P;
+  uint32_t nt;
+  std::string* why;
+  Val v[kMaxGVals];
+  int E = 0, LP = 8, halo = 0;
+  Text t;
+
+  Planner(const GProg& p, uint32_t nt_, std::string* w) : P(p), nt(nt_), why(w) {}
+
+  bool no(const char* m) {
+    *why = m;
+    return false;
+  }
+
+  // user kernel k on pairs: an expression of pair index k, or false where a
+  // subexpression may leave 16 bits
+  template <class LEAF>
+  bool pair_expr(const GOp& o, const LEAF& leaf, Term* out) const {
+    std::vector<Term> st;
+    for (int i = 0; i < o.p0; ++i) {
+      const int op = o.code[i] & 0xFF, arg = o.code[i] >> 8;
+      Term r{"", 0, 0, false};
+      auto pop = [&]() {
+        Term x = st.back();
+        st.pop_back();
+        return x;
+      };
+      const size_t need = (op == X_IN || op == X_INW || op == X_CONST) ? 0
+                          : (op == X_NEG || op == X_ABS || op == X_SQRT) ? 1
+                          : (op == X_CLAMP || op == X_SEL)               ? 3
+                                                                         : 2;
+      if (st.size() < need) return false;
+      switch (op) {
+        case X_IN:
+        case X_INW: r = leaf(op, arg); break;
+        case X_CONST: r = {fmt("pk_c(%d)", o.kc[arg]), o.kc[arg], o.kc[arg], true}; break;
+        case X_ADD: {
+          const Term b = pop(), a = pop();
+          r = {"pk_add(" + a.s + ", " + b.s + ")", a.lo + b.lo, a.hi + b.hi, false};
+          break;
+        }
+        case X_SUB: {
+          const Term b = pop(), a = pop();
+          r = {"pk_sub(" + a.s + ", " + b.s + ")", a.lo - b.hi, a.hi - b.lo, false};
+          break;
+        }
+        case X_MUL: {
+          const Term b = pop(), a = pop();
+          const long long p[4] = {a.lo * b.lo, a.lo * b.hi, a.hi * b.lo, a.hi * b.hi};
+          r = {"pk_mul(" + a.s + ", " + b.s + ")", *std::min_element(p, p + 4), *std::max_element(p, p + 4), false};
+          break;
+        }
+        case X_DIV: {
+          const Term b = pop(), a = pop();
+          if (!b.lit || b.lo < 1 || (b.lo & (b.lo - 1))) return false;
+          int s = 0;
+          while ((1LL << s) < b.lo) ++s;
+          if (s > 14) return false;
+          r = {a.lo >= 0 ? fmt("pk_shr(%s, %d)", a.s.c_str(), s) : fmt("pk_div2(%s, %d)", a.s.c_str(), s), a.lo / b.lo,
+               a.hi / b.lo, false};
+          break;
+        }
+        case X_NEG: {
+          const Term a = pop();
+          r = {"pk_sub(0u, " + a.s + ")", -a.hi, -a.lo, false};
+          break;
+        }
+        case X_MIN:
+        case X_MAX: {
+          const Term b = pop(), a = pop();
+          const bool mx = op == X_MAX;
+          r = {(mx ? "pk_max(" : "pk_min(") + a.s + ", " + b.s + ")", mx ? std::max(a.lo, b.lo) : std::min(a.lo, b.lo),
+               mx ? std::max(a.hi, b.hi) : std::min(a.hi, b.hi), false};
+          break;
+        }
+        case X_ABS: {
+          const Term a = pop();
+          r = {"pk_max(" + a.s + ", pk_sub(0u, " + a.s + "))", a.lo >= 0 ? a.lo : (a.hi <= 0 ? -a.hi : 0),
+               std::max(std::llabs(a.lo), std::llabs(a.hi)), false};
+          break;
+        }
+        case X_CLAMP: {
+          const Term c = pop(), b = pop(), a = pop();
+          r = {"pk_min(pk_max(" + a.s + ", " + b.s + "), " + c.s + ")", std::min(std::max(a.lo, b.lo), c.lo),
+               std::min(std::max(a.hi, b.hi), c.hi), false};
+          break;
+        }
+        case X_GT: {
+          const Term b = pop(), a = pop();
+          r = {"pk_gt(" + a.s + ", " + b.s + ")", 0, 1, false};
+          break;
+        }
+        case X_SEL: {
+          const Term c = pop(), b = pop(), a = pop();
+          r = {"pk_selnz(" + a.s + ", " + b.s + ", " + c.s + ")", std::min(b.lo, c.lo), std::max(b.hi, c.hi), false};
+          break;
+        }
+        default: return false;
+      }
+      if (!fits16(r.lo, r.hi) || r.s.size() > 600) return false;
+      st.push_back(r);
+    }
+    if (st.size() != 1) return false;
+    *out = st[0];
+    return true;
+  }
+
+  bool plan() {
+    const int nv = P.nvals, no_ = P.nops;
+    bool any_wide = false, any_local = false;
+    std::vector<int> eh(nv, 0), produced(nv, 0);
+    for (int k = no_ - 1; k >= 0; --k) {
+      const GOp& o = P.ops[k];
+      if (is_global_op(o.kind) || o.kind == OP_LUT || o.kind == OP_NONLINEAR)
+        return no("holds an operator the streaming form does not cover");
+      any_local |= is_local(o.kind);
+      produced[o.out] = 1;
+      for (int i = 0; i < 3; ++i) {
+        if (o.in[i] < 0) continue;
+        Val& x = v[o.in[i]];
+        const int rx = is_local(o.kind) ? o.rx : 0, ry = is_local(o.kind) ? o.ry : 0;
+        eh[o.in[i]] = std::max(eh[o.in[i]], eh[o.out] + rx);
+        x.depth = std::max(x.depth, P.vals[o.in[i]].ext - P.vals[o.out].ext + ry + 1);
+        x.rx = std::max(x.rx, rx);
+        x.ry = std::max(x.ry, ry);
+      }
+      if (is_local(o.kind)) {
+        if (o.border == B_REPEAT) return no("a periodic border");
+        Val& x = v[o.in[0]];
+        const int mode = o.border == B_UNDEFINED ? B_REPLICATE : o.border;
+        uint32_t cb = (uint32_t)o.cint;
+        if (P.vals[o.in[0]].df == DF_F32) memcpy(&cb, &o.cf, 4);
+        const int c = mode == B_CONSTANT ? (int)cb : 0;
+        if (x.mode >= 0 && (x.mode != mode || x.c != c)) return no("one value read under several border rules");
+        x.mode = mode;
+        x.c = c;
+      }
+    }
+    if (!any_local) return no("no local operator");
+    for (int i = 0; i < nv; ++i) {
+      const GVal& g = P.vals[i];
+      if (g.df == DF_BUF || (g.df == DF_UYVY && !g.input)) return no("a format the streaming form does not cover");
+      v[i].wide = g.df == DF_S32 || g.df == DF_F32;
+      any_wide |= v[i].wide;
+      if (g.store) v[i].depth = std::max(v[i].depth, g.ext + 1);
+      E = std::max(E, g.ext);
+      v[i].lo = g.df == DF_S16 ? -32768 : 0;
+      v[i].hi = g.df == DF_U8 ? 255 : (g.df == DF_UYVY ? 65535 : 32767);
+    }
+    LP = any_wide ? 4 : 8;
+    int emax = 0;
+    for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
+    halo = (emax + LP - 1) / LP;
+    for (int k = 0; k < no_; ++k)
+      for (int i = 0; i < 3; ++i)
+        if (P.ops[k].in[i] >= 0 && P.vals[P.ops[k].in[i]].df == DF_UYVY && P.ops[k].kind != OP_CHANNEL_Y)
+          return no("a UYVY frame read other than for its luma");
+    return true;
+  }
+
+  // element range of a value as its local readers see it
+  void local_range(int i, long long* lo, long long* hi) const {
+    *lo = v[i].lo;
+    *hi = v[i].hi;
+    if (v[i].mode == B_CONSTANT && !v[i].wide) {
+      *lo = std::min<long long>(*lo, v[i].c);
+      *hi = std::max<long long>(*hi, v[i].c);
+    }
+  }
+
+  // row t + ext(out) + dy of value i, as operator k reads it
+  std::string row(int k, int i, int dy) const {
+    return fmt("st.r%d[%d]", i, v[i].depth - 1 - (P.vals[i].ext - P.vals[P.ops[k].out].ext - dy));
+  }
+
+  // "c[0] e[0] + c[1] e[1] + ..." on pairs, modulo 2^16
+  static std::string pair_sum(const std::vector<int>& c, const std::vector<std::string>& e) {
+    std::string s;
+    // start from a term of weight one, if there is one
+    size_t first = 0;
+    while (first < c.size() && c[first] != 1) ++first;
+    if (first == c.size()) {
+      first = 0;
+      while (first < c.size() && !c[first]) ++first;
+      if (first == c.size()) return "0u";
+      s = c[first] == -1 ? "pk_sub(0u, " + e[first] + ")" : fmt("pk_mul(pk_c(%d), ", c[first]) + e[first] + ")";
+    } else {
+      s = e[first];
+    }
+    for (size_t i = 0; i < c.size(); ++i) {
+      if (i == first || !c[i]) continue;
+      if (c[i] == 1) s = "pk_add(" + s + ", " + e[i] + ")";
+      else if (c[i] == -1) s = "pk_sub(" + s + ", " + e[i] + ")";
+      else s = fmt("pk_mad<%d>(", c[i]) + e[i] + ", " + s + ")";
+    }
+    return s;
+  }
+
+  // Convolve on pairs, if every sum fits 16 bits
+  bool emit_convolve_pairs(int k) {
+    const GOp& o = P.ops[k];
+    const int in = o.in[0], cols = o.p0, rows = o.p1, rx = o.rx, ry = o.ry;
+    if (v[in].wide) return false;
+    long long lo, hi, smin = 0, smax = 0;
+    local_range(in, &lo, &hi);
+    for (int i = 0; i < cols * rows; ++i) {
+      const long long m = o.mask[i];
+      if (m < -32768 || m > 32767) return false;
+      smin += std::min(m * lo, m * hi);
+      smax += std::max(m * lo, m * hi);
+    }
+    const bool uns = smin >= 0 && smax <= 65535;  // the sum as an unsigned half
+    if (!uns && !fits16(smin, smax)) return false;
+    int a[5], b[5];
+    const char* PRn = LP == 8 ? "PR<8>" : "PR<4>";
+    auto column = [&](const char* name, const std::vector<int>& c) {
+      std::vector<std::string> e;
+      for (int j = 0; j < rows; ++j) e.push_back(row(k, in, -(j - ry)) + ".v[k]");
+      t("      %s %s;", PRn, name);
+      t("#pragma unroll");
+      t("      for (int k = 0; k < %d; ++k) %s.v[k] = %s;", LP / 2, name, pair_sum(c, e).c_str());
+    };
+    std::vector<int> hc;
+    std::vector<std::string> he;
+    if (conv_rank_one(o, a, b)) {
+      column("cs", std::vector<int>(a, a + rows));
+      t("      const PX<%d, %d> cx = ext<%d>(cs);", LP, rx, rx);
+      for (int i = 0; i < cols; ++i) {
+        hc.push_back(b[i]);
+        he.push_back(fmt("cx.v[k + %d]", rx - (i - rx)));
+      }
+    } else {
+      for (int i = 0; i < cols; ++i) {
+        std::vector<int> c;
+        bool any = false;
+        for (int j = 0; j < rows; ++j) {
+          c.push_back(o.mask[j * cols + i]);
+          any |= c.back() != 0;
+        }
+        if (!any) continue;
+        const int d = i - rx, r = std::abs(d);
+        column(fmt("cs%d", i).c_str(), c);
+        t("      const PX<%d, %d> cx%d = ext<%d>(cs%d);", LP, r, i, r, i);
+        hc.push_back(1);
+        he.push_back(fmt("cx%d.v[k + %d]", i, r - d));
+      }
+    }
+    t("#pragma unroll");
+    t("      for (int k = 0; k < %d; ++k) {", LP / 2);
+    t("        uint32_t s = %s;", pair_sum(hc, he).c_str());
+    long long dlo = smin >= 0 ? smin >> o.p2 : -((-smin) >> o.p2), dhi = smax >= 0 ? smax >> o.p2 : -((-smax) >> o.p2);
+    if (o.p2) t(smin >= 0 ? "        s = pk_shr(s, %d);" : "        s = pk_div2(s, %d);", o.p2);
+    const bool u8 = P.vals[o.out].df == DF_U8;
+    const long long tlo = u8 ? 0 : -32768, thi = u8 ? 255 : 32767;
+    if (dhi > thi) t(dhi > 32767 ? "        s = pk_minu(s, pk_c(%lld));" : "        s = pk_min(s, pk_c(%lld));", thi);
+    if (dlo < tlo) t("        s = pk_max(s, pk_c(%lld));", tlo);
+    t("        n.v[k] = s;");
+    t("      }");
+    v[o.out].lo = std::max(tlo, std::min(dlo, thi));
+    v[o.out].hi = std::min(thi, std::max(dhi, tlo));
+    return true;
+  }
+
+  // pixel by pixel, in 32 bits, with the tile form's definitions
+  void emit_pixels(int k) {
+    const GOp& o = P.ops[k];
+    const bool pk = !v[o.out].wide;
+    if (pk) t("      WR<%d> w;", LP);
+    const char* dst = pk ? "w" : "n";
+    if (is_local(o.kind)) {
+      t("      const WX<%d, %d> win[%d] = {", LP, o.rx, 2 * o.ry + 1);
+      for (int j = -o.ry; j <= o.ry; ++j) t("        ext<%d>(wide(%s)),", o.rx, row(k, o.in[0], j).c_str());
+      t("      };");
+      t("#pragma unroll");
+      t("      for (int q = 0; q < %d; ++q) {", LP);
+      t("        const RowsRd<%d, %d, %d> rd{win, q};", LP, o.rx, o.ry);
+      if (o.kind == OP_EXPR_LOCAL) t("        %s.v[q] = gx_expr%d(rd);", dst, k);
+      else t("        %s.v[q] = local_eval<false>(gop%d, %d, rd);", dst, k, P.vals[o.out].df);
+      t("      }");
+    } else {
+      std::string a[3];
+      for (int i = 0; i < 3; ++i) {
+        a[i] = "0";
+        if (o.in[i] < 0) continue;
+        t("      const WR<%d> a%d = wide(%s);", LP, i, row(k, o.in[i], 0).c_str());
+        a[i] = fmt("a%d.v[q]", i);
+      }
+      t("#pragma unroll");
+      t("      for (int q = 0; q < %d; ++q)", LP);
+      if (o.kind == OP_EXPR)
+        t("        %s.v[q] = gx_expr%d(%s, %s, %s);", dst, k, a[0].c_str(), a[1].c_str(), a[2].c_str());
+      else
+        t("        %s.v[q] = point_eval(gop%d, %d, %s, %s, %s, %s);", dst, k, P.vals[o.out].df,
+          P.vals[o.in[0]].df == DF_F32 ? "true" : "false", a[0].c_str(), a[1].c_str(), a[2].c_str());
+    }
+    if (pk) t("      n = packed(w);");
+  }
+
+  // the code that computes row n of operator k's output, and its range
+  bool emit_op(int k) {
+    const GOp& o = P.ops[k];
+    const int in = o.in[0], out = o.out, odf = P.vals[out].df;
+    const bool ipk = in >= 0 && !v[in].wide, opk = !v[out].wide;
+    auto r = [&](int dy) { return row(k, in, dy); };
+    auto call3 = [&](const char* f) { t("      n = %s(%s, %s, %s);", f, r(-1).c_str(), r(0).c_str(), r(1).c_str()); };
+    long long lo = 0, hi = 0;
+    if (ipk) local_range(in, &lo, &hi);
+    switch (o.kind) {
+      case OP_CHANNEL_Y: t("      n = row_channel_y(%s);", r(0).c_str()); return true;
+      case OP_GAUSS3: call3("row_gauss3"); return true;
+      case OP_BOX3: call3("row_box3"); return true;
+      case OP_DILATE3: call3("row_rank3<true>"); return true;
+      case OP_ERODE3: call3("row_rank3<false>"); return true;
+      case OP_MEDIAN3: call3("row_median3"); return true;
+      case OP_GAUSS5:
+        t("      n = row_gauss5(%s, %s, %s, %s, %s);", r(-2).c_str(), r(-1).c_str(), r(0).c_str(), r(1).c_str(),
+          r(2).c_str());
+        return true;
+      case OP_SOBEL_X:
+      case OP_SOBEL_Y:
+        if (o.kind == OP_SOBEL_X) call3("row_sobel_x");
+        else t("      n = row_sobel_y(%s, %s);", r(-1).c_str(), r(1).c_str());
+        v[out].lo = -4 * (hi - lo);
+        v[out].hi = 4 * (hi - lo);
+        return true;
+      case OP_NONMAX: {
+        const int R = o.p0;
+        t("      const PR<%d>* const w[%d] = {", LP, 2 * R + 1);
+        for (int j = -R; j <= R; ++j) t("        &%s,", r(j).c_str());
+        t("      };");
+        t("      n = row_nonmax<%d, %d>(w);", R, odf);
+        return true;
+      }
+      case OP_MAGNITUDE:
+        t("      n = row_magnitude(%s, %s);", r(0).c_str(), row(k, o.in[1], 0).c_str());
+        v[out].lo = 0;
+        return true;
+      case OP_PHASE: {
+        bool small = true;
+        for (int i = 0; i < 2; ++i) small &= v[o.in[i]].lo >= -1023 && v[o.in[i]].hi <= 1023;
+        if (small) t("      n = row_phase(%s, %s);", r(0).c_str(), row(k, o.in[1], 0).c_str());
+        else emit_pixels(k);
+        return true;
+      }
+      case OP_THRESHOLD:
+        if (!ipk) {
+          emit_pixels(k);
+        } else {
+          t("#pragma unroll");
+          t("      for (int k = 0; k < %d; ++k)", LP / 2);
+          if (o.p2 > 32767 || o.p2 < -32768)
+            t("        n.v[k] = pk_c(%d);", o.p2 > 32767 ? o.p1 : o.p0);
+          else
+            t("        n.v[k] = bit_sel(pk_neg_mask(pk_subs(%s.v[k], pk_c(%d))), pk_c(%d), pk_c(%d));", r(0).c_str(), o.p2,
+              o.p1, o.p0);
+        }
+        v[out].lo = std::min(o.p0, o.p1);
+        v[out].hi = std::max(o.p0, o.p1);
+        return true;
+      case OP_ADD: {
+        const std::string a = r(0) + ".v[k]", b = row(k, o.in[1], 0) + ".v[k]";
+        t("#pragma unroll");
+        t("      for (int k = 0; k < %d; ++k)", LP / 2);
+        if (o.p0 == 0 && odf == DF_U8)
+          t("        n.v[k] = pk_max(pk_min(pk_adds(%s, %s), pk_c(255)), 0u);", a.c_str(), b.c_str());
+        else if (o.p0 == 0) t("        n.v[k] = pk_adds(%s, %s);", a.c_str(), b.c_str());
+        else if (odf == DF_U8) t("        n.v[k] = pk_add(%s, %s) & 0x00FF00FFu;", a.c_str(), b.c_str());
+        else t("        n.v[k] = pk_add(%s, %s);", a.c_str(), b.c_str());
+        return true;
+      }
+      case OP_MULF: {
+        bool only_box = !P.vals[out].store;
+        for (int j = 0; j < P.nops; ++j)
+          for (int i = 0; i < 3; ++i)
+            if (P.ops[j].in[i] == out) only_box &= P.ops[j].kind == OP_BOX5F;
+        v[out].nz = only_box;
+        t("      n = row_mulf<%s>(%s, %s);", only_box ? "true" : "false", r(0).c_str(), row(k, o.in[1], 0).c_str());
+        return true;
+      }
+      case OP_BOX5F:
+        t("      n = row_box5f<%s>(%s, %s, %s, %s, %s);", v[in].nz ? "true" : "false", r(-2).c_str(), r(-1).c_str(),
+          r(0).c_str(), r(1).c_str(), r(2).c_str());
+        return true;
+      case OP_CONVOLVE:
+        if (!emit_convolve_pairs(k)) emit_pixels(k);
+        return true;
+      case OP_EXPR: {
+        Term e;
+        bool pk = opk && o.p1 == 0;
+        for (int i = 0; i < 3; ++i) pk &= o.in[i] < 0 || !v[o.in[i]].wide;
+        if (pk && pair_expr(o,
+                            [&](int, int arg) {
+                              const int i = o.in[arg];
+                              return Term{row(k, i, 0) + ".v[k]", v[i].lo, v[i].hi, false};
+                            },
+                            &e)) {
+          store_expr(out, e);
+        } else {
+          emit_pixels(k);
+        }
+        return true;
+      }
+      case OP_EXPR_LOCAL: {
+        Term e;
+        if (ipk && opk && o.p1 == 0 &&
+            pair_expr(o,
+                      [&](int op, int arg) {
+                        const int dx = op == X_IN ? 0 : arg % 5 - 2, dy = op == X_IN ? 0 : arg / 5 - 2;
+                        return Term{fmt("xr%d.v[k + %d]", dy + 2, o.rx + dx), lo, hi, false};
+                      },
+                      &e)) {
+          for (int j = -o.ry; j <= o.ry; ++j)
+            t("      const PX<%d, %d> xr%d = ext<%d>(%s);", LP, o.rx, j + 2, o.rx, r(j).c_str());
+          store_expr(out, e);
+        } else {
+          emit_pixels(k);
+        }
+        return true;
+      }
+      case OP_HARRIS: emit_pixels(k); return true;
+    }
+    return no("holds an operator the streaming form does not cover");
+  }
+  void store_expr(int out, const Term& e) {
+    const bool u8 = P.vals[out].df == DF_U8;
+    const long long tlo = u8 ? 0 : -32768, thi = u8 ? 255 : 32767;
+    std::string s = e.s;
+    if (e.hi > thi) s = fmt("pk_min(%s, pk_c(%lld))", s.c_str(), thi);
+    if (e.lo < tlo) s = fmt("pk_max(%s, pk_c(%lld))", s.c_str(), tlo);
+    t("#pragma unroll");
+    t("      for (int k = 0; k < %d; ++k) n.v[k] = %s;", LP / 2, s.c_str());
+    v[out].lo = std::max(tlo, std::min(e.lo, thi));
+    v[out].hi = std::min(thi, std::max(e.hi, tlo));
+  }
+
+  std::string row_type(int i) const { return fmt(v[i].wide ? "WR<%d>" : "PR<%d>", LP); }
+  int raw_bytes(int i) const { return LP * df_bytes(P.vals[i].df); }
+
+  // row n becomes value i's newest
+  void emit_push(int i) {
+    const int D = v[i].depth;
+    if (D > 1) {
+      t("#pragma unroll");
+      t("      for (int j = 0; j < %d; ++j) st.r%d[j] = st.r%d[j + 1];", D - 1, i, i);
+    }
+    t("      st.r%d[%d] = n;", i, D - 1);
+  }
+
+  bool emit() {
+    const int nv = P.nvals;
+    t("namespace hvx {");
+    t("constexpr int SX_LP = %d;", LP);
+    // the rows each value holds, oldest first
+    t("struct SxState {");
+    for (int i = 0; i < nv; ++i) t("  %s r%d[%d];", row_type(i).c_str(), i, v[i].depth);
+    t("};");
+    std::string args, in_list;
+    std::vector<int> ins;
+    for (int i = 0; i < nv; ++i)
+      if (P.vals[i].input) {
+        ins.push_back(i);
+        args += fmt(", const Raw<%d>& x%d", raw_bytes(i), i);
+      }
+    // step S of a band (0 .. 2 E - 1 before its first output row, then 2 E):
+    // the outputs' row is t; EDGE: the strip or band touches the image's border
+    t("template <int S, bool EDGE>");
+    t("__device__ __forceinline__ void sx_step(SxState& st, const Strip& g, const IOTable& io, const uint32_t (&off)[%d], int t%s) {",
+      kMaxIO, args.c_str());
+    for (int i : ins) {
+      const GVal& gv = P.vals[i];
+      t("  if constexpr (S >= %d) {  // input %d, row t + %d", 2 * E - 2 * gv.ext, i, gv.ext);
+      if (v[i].wide) t("      %s n = unpack_wd<SX_LP>(x%d);", row_type(i).c_str(), i);
+      else t("      %s n = unpack_pk<%d, SX_LP>(x%d);", row_type(i).c_str(), gv.df, i);
+      if (v[i].mode >= 0) {
+        t("      if constexpr (EDGE) {");
+        t("        fix_cols<%d, %d>(n, g, (int)0x%08xu);", v[i].mode, v[i].rx, (uint32_t)v[i].c);
+        if (v[i].mode == B_CONSTANT)
+          t("        if (t + %d < 0 || t + %d >= g.H) fill(n, (int)0x%08xu);", gv.ext, gv.ext, (uint32_t)v[i].c);
+        t("      }");
+      }
+      emit_push(i);
+      t("  }");
+    }
+    for (int k = 0; k < P.nops; ++k) {
+      const int i = P.ops[k].out;
+      const GVal& gv = P.vals[i];
+      const bool bord = v[i].mode >= 0;
+      const int D = v[i].depth;
+      t("  if constexpr (S >= %d) {  // value %d, row t + %d", 2 * E - 2 * gv.ext, i, gv.ext);
+      t("    %s n;", row_type(i).c_str());
+      if (bord) {
+        t("    const int r = t + %d;", gv.ext);
+        t("    if (!EDGE || (r >= 0 && r < g.H)) {");
+      } else {
+        t("    {");
+      }
+      if (!emit_op(k)) return false;
+      if (bord) {
+        t("      if constexpr (EDGE) fix_cols<%d, %d>(n, g, (int)0x%08xu);", v[i].mode, v[i].rx, (uint32_t)v[i].c);
+        t("    } else {");
+        if (v[i].mode == B_CONSTANT) {
+          t("      fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
+        } else if (v[i].mode == B_REPLICATE) {
+          t("      n = st.r%d[%d];", i, D - 1);  // above the image: set when row 0 is known
+        } else {
+          // 1, 2 or 4 rows back
+          t("      const int d = r - mirror_near(r, g.H);");
+          t("      n = st.r%d[%d];", i, D - 1);
+          if (D >= 2) t("      if (d == 2) n = st.r%d[%d];", i, D - 2);
+          if (D >= 4) t("      if (d == 4) n = st.r%d[%d];", i, D - 4);
+        }
+      }
+      t("    }");
+      emit_push(i);
+      if (bord && v[i].mode != B_CONSTANT && D > 1) {
+        t("    if constexpr (EDGE) {");
+        if (v[i].mode == B_REPLICATE) {
+          t("      if (r == 0) {");
+          for (int j = 0; j < D - 1; ++j) t("        st.r%d[%d] = st.r%d[%d];", i, j, i, D - 1);
+          t("      }");
+        } else {
+          // row -1 reads row 1, row -2 row 2; images of one or two rows repeat
+          auto set = [&](const char* when, int back) {
+            if (back < D) t("      if (%s) st.r%d[%d] = st.r%d[%d];", when, i, D - 1 - back, i, D - 1);
+          };
+          if (v[i].ry >= 1) {
+            set("r == 0 && g.H == 1", 1);
+            set("r == 1", 2);
+          }
+          if (v[i].ry >= 2) {
+            set("r == 0 && g.H <= 2", 2);
+            set("r == 2", 4);
+          }
+        }
+        t("    }");
+      }
+      t("  }");
+    }
+    t("  if constexpr (S == %d) {", 2 * E);
+    for (int i = 0; i < nv; ++i) {
+      const GVal& gv = P.vals[i];
+      if (!gv.store) continue;
+      t("    emit_row<%d, SX_LP, EDGE, %s>(st.r%d[%d], io.ptr[%d], io.pitch[%d], t, g, off[%d]);", gv.df,
+        (nt >> i) & 1 ? "true" : "false", i, v[i].depth - 1 - gv.ext, gv.io, gv.io, gv.io);
+    }
+    t("  }");
+    t("}");
+    // one strip of one band
+    const int out_lanes = 64 - 2 * halo;
+    t("template <bool EDGE>");
+    t("__device__ __forceinline__ void sx_item(const IOTable& io, int W, int H, int strip, int y0, int y1) {");
+    t("  const Strip g = make_strip<SX_LP>(strip, %d, %d, W, H);", halo, out_lanes);
+    t("  const int wr = (W + SX_LP - 1) / SX_LP * SX_LP, xl = min(max(g.x0, 0), wr - SX_LP);");
+    t("  uint32_t off[%d];", kMaxIO);
+    for (int i = 0; i < nv; ++i)
+      if (P.vals[i].store) t("  off[%d] = g.keep ? (uint32_t)(g.x0 * %d) : kNoLane;", P.vals[i].io, df_bytes(P.vals[i].df));
+    for (int i : ins) {
+      const GVal& gv = P.vals[i];
+      const int bpp = df_bytes(gv.df), nb = raw_bytes(i);
+      // rows past the last one the band needs are not read (an empty descriptor)
+      t("  auto ld%d = [&](int r) {", i);
+      t("    const uint32_t n = r < y1 + %d ? (uint32_t)(wr * %d) : 0u;", gv.ext, bpp);
+      t("    if constexpr (EDGE) r = src_row<%d>(r, H);", v[i].mode < 0 ? B_REPLICATE : v[i].mode);
+      t("    return row_load<%d>(io.ptr[%d], io.pitch[%d], r, n, (uint32_t)(xl * %d));", nb, gv.io, gv.io, bpp);
+      t("  };");
+      if (gv.ext) {
+        t("  Raw<%d> a%d[%d];", nb, i, 2 * gv.ext);
+        t("#pragma unroll");
+        t("  for (int j = 0; j < %d; ++j) a%d[j] = ld%d(y0 - %d + j);", 2 * gv.ext, i, i, gv.ext);
+      }
+      t("  Raw<%d> c%d[%d];", nb, i, kUnroll);
+      t("#pragma unroll");
+      t("  for (int j = 0; j < %d; ++j) c%d[j] = ld%d(y0 + %d + j);", kUnroll, i, i, gv.ext);
+    }
+    t("  SxState st = {};");
+    for (int s = 0; s < 2 * E; ++s) {
+      std::string a;
+      for (int i : ins) {
+        const int j = s - (2 * E - 2 * P.vals[i].ext);
+        a += j >= 0 ? fmt(", a%d[%d]", i, j) : fmt(", c%d[0]", i);  // not read before step 2 E - 2 ext
+      }
+      t("  sx_step<%d, EDGE>(st, g, io, off, y0 - %d%s);", s, 2 * E - s, a.c_str());
+    }
+    t("  for (int t = y0; t < y1; t += %d) {", kUnroll);
+    for (int i : ins) {
+      t("    Raw<%d> n%d[%d];", raw_bytes(i), i, kUnroll);
+      t("#pragma unroll");
+      t("    for (int j = 0; j < %d; ++j) n%d[j] = ld%d(t + %d + j);", kUnroll, i, i, kUnroll + P.vals[i].ext);
+    }
+    for (int j = 0; j < kUnroll; ++j) {
+      std::string a;
+      for (int i : ins) a += fmt(", c%d[%d]", i, j);
+      t("    sx_step<%d, EDGE>(st, g, io, off, t + %d%s);", 2 * E, j, a.c_str());
+    }
+    for (int i : ins) {
+      t("#pragma unroll");
+      t("    for (int j = 0; j < %d; ++j) c%d[j] = n%d[j];", kUnroll, i, i);
+    }
+    t("  }");
+    t("}");
+    t("}  // namespace hvx");
+    t("extern \"C\" __global__ __launch_bounds__(64) void hvx_gen_stream(const GProg* __restrict__ P, const IOTable io0,");
+    t("                                                           const GenBatchImage* __restrict__ imgs, int nimg,");
+    t("                                                           uint32_t* __restrict__ ws, int rows) {");
+    // every XCD takes a contiguous run of items (block b runs on XCD b mod 8),
+    // so that neighbouring strips and bands share an L2
+    t("  const int nb = (int)gridDim.x, b = (int)blockIdx.x;");
+    t("  const int per = nb / 8, rem = nb %% 8, xcd = b %% 8;");
+    t("  int vb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + b / 8;");
+    t("  IOTable io;");
+    t("  int W, H;");
+    t("  if (nimg == 0) {");
+    t("    io = io0;");
+    t("    W = P->w;");
+    t("    H = P->h;");
+    t("  } else {");
+    t("    const int i = gx_batch_image(imgs, nimg, vb);");
+    t("    io = imgs[i].io;");
+    t("    W = imgs[i].w;");
+    t("    H = imgs[i].h;");
+    t("    rows = imgs[i].rows;");
+    t("    vb -= imgs[i].block0;");
+    t("  }");
+    t("  const int strips = (W + %d) / %d;", out_lanes * LP - 1, out_lanes * LP);
+    t("  const int strip = vb %% strips, y0 = vb / strips * rows, y1 = min(y0 + rows, H);");
+    t("  if (y0 >= H) return;");
+    // inside the image: every pixel of every lane, and every row the band reads
+    t("  const bool inside = strip > 0 && (strip * %d + %d) * SX_LP <= W && y0 >= %d && y0 + rows + %d <= H;", out_lanes,
+      out_lanes + halo, E, E);
+    t("  if (inside) sx_item<false>(io, W, H, strip, y0, y1);");
+    t("  else sx_item<true>(io, W, H, strip, y0, y1);");
+    t("}");
+    return true;
+  }
+};
+
+}  // namespace
+
+bool emit_stream(const GProg& P, uint32_t nt, GenSource* out, std::string* why) {
+  Planner p(P, nt, why);
+  if (!p.plan()) return false;
+  if (!p.emit()) return false;
+  out->text = p.t.s;
+  out->form = GEN_STREAM;
+  out->tw = (64 - 2 * p.halo) * p.LP;
+  out->th = kUnroll;
+  out->red = false;
+  out->lds_words = 0;
+  out->ext = p.E;
+  return true;
+}
+
+}  // namespace hvx

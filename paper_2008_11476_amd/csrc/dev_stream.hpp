@@ -1,0 +1,610 @@
+// Building blocks of the generated streaming kernels (codegen_stream.cpp).
+//
+// One wave owns a strip of image columns, LP (4 or 8) consecutive pixels per
+// lane, and streams a band of rows top to bottom.  A row of a value is held
+// as pairs of 16-bit elements (PR: pixel k and pixel k + LP/2 share a
+// register, so one packed instruction handles two pixels) or, for F32, S32
+// and wide intermediate results, as one register per pixel (WR).  With the
+// pair layout the horizontal neighbour of both halves of pair k is pair
+// k +- 1; only the pairs at the lane's ends need pixels of the adjacent lane,
+// which arrive through DPP wave shifts.  The outermost lanes of a strip hold
+// halo pixels and store nothing.
+#pragma once
+#include "dev_generic.hpp"
+
+namespace hvx {
+
+typedef short v2s __attribute__((ext_vector_type(2)));
+typedef unsigned short v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v2w __attribute__((ext_vector_type(2)));
+typedef uint32_t v4w __attribute__((ext_vector_type(4)));
+
+// ---- packed 16-bit arithmetic (two pixels per instruction) -------------------
+#define HVX_PK2(name, T, expr)                                          \
+  __device__ __forceinline__ uint32_t name(uint32_t a_, uint32_t b_) {  \
+    const T a = __builtin_bit_cast(T, a_), b = __builtin_bit_cast(T, b_); \
+    return __builtin_bit_cast(uint32_t, (T)(expr));                     \
+  }
+HVX_PK2(pk_add, v2u, a + b)
+HVX_PK2(pk_sub, v2u, a - b)
+HVX_PK2(pk_mul, v2u, a* b)
+HVX_PK2(pk_max, v2s, __builtin_elementwise_max(a, b))
+HVX_PK2(pk_min, v2s, __builtin_elementwise_min(a, b))
+HVX_PK2(pk_minu, v2u, __builtin_elementwise_min(a, b))
+HVX_PK2(pk_adds, v2s, __builtin_elementwise_add_sat(a, b))
+HVX_PK2(pk_subs, v2s, __builtin_elementwise_sub_sat(a, b))
+#undef HVX_PK2
+__device__ __forceinline__ uint32_t pk_shr(uint32_t a, int s) {
+  return __builtin_bit_cast(uint32_t, (v2u)(__builtin_bit_cast(v2u, a) >> (unsigned short)s));
+}
+__device__ __forceinline__ uint32_t pk_sar(uint32_t a, int s) {
+  return __builtin_bit_cast(uint32_t, (v2s)(__builtin_bit_cast(v2s, a) >> (short)s));
+}
+__device__ __forceinline__ constexpr uint32_t pk_c(int c) { return ((uint32_t)c & 0xFFFFu) * 0x10001u; }
+// acc + c e, one instruction (the compiler does not form it from a product and a sum)
+template <int C>
+__device__ __forceinline__ uint32_t pk_mad(uint32_t e, uint32_t acc) {
+  uint32_t r;
+  if constexpr (C >= 1 && C <= 64)  // an inline constant, taken from the low half for both halves
+    asm("v_pk_mad_u16 %0, %1, %3, %2 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(e), "v"(acc), "n"(C));
+  else
+    asm("v_pk_mad_u16 %0, %1, %3, %2" : "=v"(r) : "v"(e), "v"(acc), "s"(pk_c(C)));
+  return r;
+}
+__device__ __forceinline__ uint32_t bit_sel(uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); }
+// all ones in the halves whose element is negative
+__device__ __forceinline__ uint32_t pk_neg_mask(uint32_t a) { return pk_sar(a, 15); }
+// a / 2^s toward zero (signed)
+__device__ __forceinline__ uint32_t pk_div2(uint32_t a, int s) {
+  return s == 0 ? a : pk_sar(pk_add(a, pk_shr(pk_sar(a, 15), 16 - s)), s);
+}
+// user kernels' comparison and selection on pairs (gt: 1 or 0)
+__device__ __forceinline__ uint32_t pk_gt(uint32_t a, uint32_t b) { return pk_shr(pk_subs(b, a), 15); }
+__device__ __forceinline__ uint32_t pk_selnz(uint32_t p, uint32_t x, uint32_t y) {
+  return bit_sel(pk_neg_mask(p | pk_sub(0u, p)), x, y);
+}
+
+// ---- neighbouring lanes ---------------------------------------------------------
+// Lane i receives lane i - 1's (i + 1's) register.  The empty asm keeps the
+// move a separate instruction: folded into a consuming add or subtract, a
+// whole-wave shift gave wrong results on gfx950.
+__device__ __forceinline__ uint32_t lane_left(uint32_t v) {
+  uint32_t r = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, true);
+  asm("" : "+v"(r));
+  return r;
+}
+__device__ __forceinline__ uint32_t lane_right(uint32_t v) {
+  uint32_t r = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true);
+  asm("" : "+v"(r));
+  return r;
+}
+
+template <int LP>
+struct PR {  // a row's pixels of one lane as 16-bit pairs
+  uint32_t v[LP / 2];
+};
+template <int LP>
+struct WR {  // one register per pixel
+  int v[LP];
+};
+// rows extended by R pixels on each side: entry R + k is pair (pixel) k
+template <int LP, int R>
+struct PX {
+  uint32_t v[LP / 2 + 2 * R];
+};
+template <int LP, int R>
+struct WX {
+  int v[LP + 2 * R];
+};
+
+template <int R, int LP>
+__device__ __forceinline__ PX<LP, R> ext(const PR<LP>& p) {
+  PX<LP, R> e;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k) e.v[R + k] = p.v[k];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint32_t l = p.v[LP / 2 - 1 - i], r = p.v[i];
+    e.v[R - 1 - i] = __builtin_amdgcn_alignbit(l, lane_left(l), 16);
+    e.v[R + LP / 2 + i] = __builtin_amdgcn_alignbit(lane_right(r), r, 16);
+  }
+  return e;
+}
+template <int R, int LP>
+__device__ __forceinline__ WX<LP, R> ext(const WR<LP>& p) {
+  WX<LP, R> e;
+#pragma unroll
+  for (int k = 0; k < LP; ++k) e.v[R + k] = p.v[k];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    e.v[R - 1 - i] = (int)lane_left((uint32_t)p.v[LP - 1 - i]);
+    e.v[R + LP + i] = (int)lane_right((uint32_t)p.v[i]);
+  }
+  return e;
+}
+
+template <int LP>
+__device__ __forceinline__ void fill(PR<LP>& r, int c) {
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k) r.v[k] = pk_c(c);
+}
+template <int LP>
+__device__ __forceinline__ void fill(WR<LP>& r, int c) {
+#pragma unroll
+  for (int k = 0; k < LP; ++k) r.v[k] = c;
+}
+template <int LP>
+__device__ __forceinline__ WR<LP> wide(const PR<LP>& p) {  // signed 16-bit elements
+  WR<LP> w;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k) {
+    w.v[k] = (int)(int16_t)(uint16_t)p.v[k];
+    w.v[k + LP / 2] = (int)p.v[k] >> 16;
+  }
+  return w;
+}
+template <int LP>
+__device__ __forceinline__ const WR<LP>& wide(const WR<LP>& w) {
+  return w;
+}
+template <int LP>
+__device__ __forceinline__ PR<LP> packed(const WR<LP>& w) {
+  PR<LP> p;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k)
+    p.v[k] = __builtin_amdgcn_perm((uint32_t)w.v[k + LP / 2], (uint32_t)w.v[k], 0x05040100u);
+  return p;
+}
+
+// ---- rows in memory ----------------------------------------------------------------
+// Rows are read and written through buffer descriptors of one row each, made
+// from its (wave-uniform) address: the lane's byte offset is the only vector
+// operand, a lane that must not store has an offset outside the descriptor
+// (the hardware drops it) and a row that must not be touched has an empty
+// one.  So a row's code has no branch around its loads and stores, and the
+// compiler counts the outstanding ones exactly.
+constexpr uint32_t kNoLane = 0x80000000u;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int64_t pitch, int row, uint32_t bytes) {
+  const uint64_t a = (uint64_t)base + (uint64_t)((int64_t)row * pitch);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)((uint64_t)hi << 32 | lo), 0, (int)n, 0x00027000);
+}
+
+template <int NB>  // bytes per lane: 4, 8, 16 or 32
+struct Raw {
+  uint32_t d[NB / 4];
+};
+template <int NB>
+__device__ __forceinline__ Raw<NB> row_load(const void* base, int64_t pitch, int row, uint32_t bytes, uint32_t off) {
+  const __amdgpu_buffer_rsrc_t r = row_rsrc(base, pitch, row, bytes);
+  Raw<NB> x;
+  if constexpr (NB == 4) {
+    x.d[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+  } else if constexpr (NB == 8) {
+    const v2w q = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    x.d[0] = q.x;
+    x.d[1] = q.y;
+  } else {
+#pragma unroll
+    for (int i = 0; i < NB / 16; ++i) {
+      const v4w q = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * i, 0, 0);
+      x.d[4 * i] = q.x;
+      x.d[4 * i + 1] = q.y;
+      x.d[4 * i + 2] = q.z;
+      x.d[4 * i + 3] = q.w;
+    }
+  }
+  return x;
+}
+// AUX 2: non-temporal
+template <int NB, int AUX>
+__device__ __forceinline__ void row_store(const Raw<NB>& x, void* base, int64_t pitch, int row, uint32_t bytes,
+                                          uint32_t off) {
+  const __amdgpu_buffer_rsrc_t r = row_rsrc(base, pitch, row, bytes);
+  if constexpr (NB == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32(x.d[0], r, off, 0, AUX);
+  } else if constexpr (NB == 8) {
+    __builtin_amdgcn_raw_buffer_store_b64(v2w{x.d[0], x.d[1]}, r, off, 0, AUX);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NB / 16; ++i)
+      __builtin_amdgcn_raw_buffer_store_b128(v4w{x.d[4 * i], x.d[4 * i + 1], x.d[4 * i + 2], x.d[4 * i + 3]}, r,
+                                             off + 16 * i, 0, AUX);
+  }
+}
+
+// loaded bytes -> a row (U8, S16 and UYVY elements packed; S32 and F32 wide)
+template <int DF, int LP>
+__device__ __forceinline__ PR<LP> unpack_pk(const Raw<LP*(DF == DF_U8 ? 1 : 2)>& x) {
+  PR<LP> p;
+  if constexpr (DF == DF_U8 && LP == 4) {
+    p.v[0] = __builtin_amdgcn_perm(0u, x.d[0], 0x0c020c00u);
+    p.v[1] = __builtin_amdgcn_perm(0u, x.d[0], 0x0c030c01u);
+  } else if constexpr (DF == DF_U8) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) p.v[k] = __builtin_amdgcn_perm(x.d[1], x.d[0], 0x0c040c00u + 0x00010001u * k);
+  } else {
+#pragma unroll
+    for (int k = 0; k < LP / 2; ++k)
+      p.v[k] = __builtin_amdgcn_perm(x.d[LP / 4 + k / 2], x.d[k / 2], (k & 1) ? 0x07060302u : 0x05040100u);
+  }
+  return p;
+}
+template <int LP>
+__device__ __forceinline__ WR<LP> unpack_wd(const Raw<LP * 4>& x) {
+  WR<LP> w;
+#pragma unroll
+  for (int k = 0; k < LP; ++k) w.v[k] = (int)x.d[k];
+  return w;
+}
+// a row -> bytes to store
+template <int DF, int LP>
+__device__ __forceinline__ Raw<LP*(DF == DF_U8 ? 1 : 2)> pack_row(const PR<LP>& p) {
+  Raw<LP*(DF == DF_U8 ? 1 : 2)> x;
+  if constexpr (DF == DF_U8) {
+    const uint32_t t0 = p.v[0] | p.v[1] << 8;  // elements lie in 0..255
+    if constexpr (LP == 4) {
+      x.d[0] = t0;
+    } else {
+      const uint32_t t1 = p.v[2] | p.v[3] << 8;
+      x.d[0] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+      x.d[1] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < LP / 4; ++k) {
+      x.d[k] = __builtin_amdgcn_perm(p.v[2 * k + 1], p.v[2 * k], 0x05040100u);
+      x.d[LP / 4 + k] = __builtin_amdgcn_perm(p.v[2 * k + 1], p.v[2 * k], 0x07060302u);
+    }
+  }
+  return x;
+}
+template <int DF, int LP>
+__device__ __forceinline__ Raw<LP * 4> pack_row(const WR<LP>& w) {
+  Raw<LP * 4> x;
+#pragma unroll
+  for (int k = 0; k < LP; ++k) x.d[k] = (uint32_t)w.v[k];
+  return x;
+}
+
+// ---- the strip, and positions outside the image --------------------------------------
+struct Strip {
+  int x0;        // first pixel of the lane
+  int W, H;
+  int zl;        // lane holding x = 0, or -1
+  int rl, rq;    // lane and pixel within it holding x = W - 1 (the lane may lie outside the wave)
+  bool left;     // the lane lies left of the image
+  bool keep;     // the lane stores all its pixels
+  bool ragged;   // the lane stores the first W - x0 of its pixels
+};
+template <int LP>
+__device__ __forceinline__ Strip make_strip(int strip, int halo, int out_lanes, int W, int H) {
+  Strip s;
+  const int lane = (int)(threadIdx.x & 63);
+  const int base = (strip * out_lanes - halo) * LP;  // the first lane's first pixel (may be negative)
+  s.x0 = base + lane * LP;
+  s.W = W;
+  s.H = H;
+  s.zl = strip == 0 ? halo : -1;
+  s.rl = (W - 1 - base) / LP;
+  s.rq = (W - 1) % LP;
+  s.left = s.x0 < 0;
+  const bool own = lane >= halo && lane < halo + out_lanes && s.x0 < W;
+  s.keep = own && s.x0 + LP <= W;
+  s.ragged = own && s.x0 + LP > W;
+  return s;
+}
+
+// pixel q (uniform) of lane `lane` (uniform), in every lane; picked with
+// uniform masks (a chain of selects would become an indexed access to scratch
+// memory)
+template <int LP>
+__device__ __forceinline__ int strip_px(const PR<LP>& p, int lane, int q) {
+  uint32_t v = 0;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k) v |= p.v[k] & (q % (LP / 2) == k ? ~0u : 0u);
+  const uint32_t s = (uint32_t)__builtin_amdgcn_readlane((int)v, lane & 63);
+  return (int)(q >= LP / 2 ? s >> 16 : s & 0xFFFFu);
+}
+template <int LP>
+__device__ __forceinline__ int strip_px(const WR<LP>& p, int lane, int q) {
+  int v = 0;
+#pragma unroll
+  for (int k = 0; k < LP; ++k) v |= p.v[k] & (q == k ? ~0 : 0);
+  return __builtin_amdgcn_readlane(v, lane & 63);
+}
+// the element c where `m` holds for the pixel
+template <int LP, class M>
+__device__ __forceinline__ void put_where(PR<LP>& p, int c, const M& m) {
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k)
+    p.v[k] = bit_sel((m(k) ? 0xFFFFu : 0u) | (m(k + LP / 2) ? 0xFFFF0000u : 0u), pk_c(c), p.v[k]);
+}
+template <int LP, class M>
+__device__ __forceinline__ void put_where(WR<LP>& p, int c, const M& m) {
+#pragma unroll
+  for (int k = 0; k < LP; ++k) p.v[k] = m(k) ? c : p.v[k];
+}
+
+// Position read for x in [-2, n + 1] under the MIRROR border (reflect-101,
+// repeated: a two-pixel axis has period two).
+__device__ __forceinline__ int mirror_near(int x, int n) {
+  if (n <= 2) return n == 1 ? 0 : x & 1;
+  return x < 0 ? -x : (x < n ? x : 2 * (n - 1) - x);
+}
+
+// Columns outside the image take the border rule MODE of the operators that
+// read the value (R: their largest horizontal radius; R = 0: none).  Only
+// the strips at the image's left and right edge hold such columns.
+template <int MODE, int R, template <int> class ROW, int LP>
+__device__ __forceinline__ void fix_cols(ROW<LP>& p, const Strip& s, int c) {
+  if constexpr (R > 0) {
+    const int x0 = s.x0, W = s.W;
+    if constexpr (MODE == B_CONSTANT) {
+      put_where(p, c, [&](int q) { return s.left || x0 + q >= W; });
+    } else if constexpr (MODE == B_MIRROR) {
+      int lv[R], rv[R];
+#pragma unroll
+      for (int j = 1; j <= R; ++j) {
+        const int l = mirror_near(-j, W), r = s.rl * LP + s.rq - (W - 1 - mirror_near(W - 1 + j, W));
+        lv[j - 1] = strip_px(p, max(s.zl, 0) + l / LP, l % LP);
+        rv[j - 1] = strip_px(p, r / LP, r % LP);
+      }
+#pragma unroll
+      for (int j = 1; j <= R; ++j) {
+        put_where(p, lv[j - 1], [&](int q) { return x0 + q == -j; });
+        put_where(p, rv[j - 1], [&](int q) { return x0 + q == W - 1 + j; });
+      }
+    } else {
+      const int lv = strip_px(p, max(s.zl, 0), 0), rv = strip_px(p, s.rl, s.rq);
+      put_where(p, lv, [&](int) { return s.left; });
+      put_where(p, rv, [&](int q) { return x0 + q >= W; });
+    }
+  }
+}
+
+// Row of memory that row r of a group input reads (MODE as above).
+template <int MODE>
+__device__ __forceinline__ int src_row(int r, int H) {
+  if constexpr (MODE == B_MIRROR) r = mirror_pos(r, H);
+  return min(max(r, 0), H - 1);
+}
+
+// Stores row `row` of a value.  EDGE: the item touches the image's border;
+// rows past the image are dropped, and the lane that holds W - 1 amid its
+// pixels stores them one by one.
+template <int DF, int LP, bool EDGE, bool NT, class ROW>
+__device__ __forceinline__ void emit_row(const ROW& p, void* base, int64_t pitch, int row, const Strip& s, uint32_t off) {
+  constexpr int BPP = DF == DF_U8 ? 1 : (DF == DF_S16 ? 2 : 4);
+  const Raw<LP * BPP> x = pack_row<DF, LP>(p);
+  uint32_t bytes = (uint32_t)(s.W * BPP);
+  if (EDGE && row >= s.H) bytes = 0;
+  row_store<LP * BPP, NT ? 2 : 0>(x, base, pitch, row, bytes, off);
+  if constexpr (EDGE) {
+    if (row < s.H && s.ragged) {
+      uint8_t* r = (uint8_t*)base + (size_t)row * pitch + (size_t)s.x0 * BPP;
+      const int n = s.W - s.x0;
+#pragma unroll
+      for (int q = 0; q < LP - 1; ++q)
+        if (q < n) {
+          const uint32_t w = x.d[q * BPP / 4] >> (q * BPP % 4 * 8);
+          if constexpr (BPP == 1) r[q] = (uint8_t)w;
+          else if constexpr (BPP == 2) ((uint16_t*)r)[q] = (uint16_t)w;
+          else ((uint32_t*)r)[q] = w;
+        }
+    }
+  }
+}
+
+// ---- operators on rows ------------------------------------------------------------------
+// Each computes what local_eval / point_eval define, pixel for pixel.
+#define HVX_ROW for (int k = 0; k < LP / 2; ++k)
+
+template <int LP>
+__device__ __forceinline__ PR<LP> row_channel_y(const PR<LP>& a) {
+  PR<LP> r;
+#pragma unroll
+  HVX_ROW r.v[k] = pk_shr(a.v[k], 8);
+  return r;
+}
+template <int LP>
+__device__ __forceinline__ PR<LP> row_gauss3(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c) {
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = pk_mad<2>(b.v[k], pk_add(a.v[k], c.v[k]));
+  const PX<LP, 1> e = ext<1>(t);
+#pragma unroll
+  HVX_ROW r.v[k] = pk_shr(pk_mad<2>(e.v[k + 1], pk_add(e.v[k], e.v[k + 2])), 4);
+  return r;
+}
+__device__ __forceinline__ uint32_t pk_14641(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t e) {
+  return pk_mad<6>(c, pk_mad<4>(pk_add(b, d), pk_add(a, e)));
+}
+template <int LP>  // sums up to 65280, in unsigned 16-bit halves
+__device__ __forceinline__ PR<LP> row_gauss5(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c, const PR<LP>& d,
+                                             const PR<LP>& e) {
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = pk_14641(a.v[k], b.v[k], c.v[k], d.v[k], e.v[k]);
+  const PX<LP, 2> x = ext<2>(t);
+#pragma unroll
+  HVX_ROW r.v[k] = pk_shr(pk_14641(x.v[k], x.v[k + 1], x.v[k + 2], x.v[k + 3], x.v[k + 4]), 8);
+  return r;
+}
+template <int LP>  // floor(s / 9) = (7282 s) >> 16 for s <= 2295
+__device__ __forceinline__ PR<LP> row_box3(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c) {
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = pk_add(pk_add(a.v[k], b.v[k]), c.v[k]);
+  const PX<LP, 1> e = ext<1>(t);
+#pragma unroll
+  HVX_ROW {
+    const uint32_t s = pk_add(pk_add(e.v[k], e.v[k + 1]), e.v[k + 2]);
+    r.v[k] = __builtin_amdgcn_perm((s >> 16) * 7282u, (s & 0xFFFFu) * 7282u, 0x07060302u);
+  }
+  return r;
+}
+template <bool MAX, int LP>
+__device__ __forceinline__ PR<LP> row_rank3(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c) {
+  auto f = [](uint32_t x, uint32_t y) { return MAX ? pk_max(x, y) : pk_min(x, y); };
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = f(f(a.v[k], b.v[k]), c.v[k]);
+  const PX<LP, 1> e = ext<1>(t);
+#pragma unroll
+  HVX_ROW r.v[k] = f(f(e.v[k], e.v[k + 1]), e.v[k + 2]);
+  return r;
+}
+__device__ __forceinline__ uint32_t pk_med3(uint32_t a, uint32_t b, uint32_t c) {
+  return pk_max(pk_min(a, b), pk_min(pk_max(a, b), c));
+}
+template <int LP>  // columns sorted, then the largest minimum, the median of medians, the smallest maximum
+__device__ __forceinline__ PR<LP> row_median3(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c) {
+  PR<LP> lo, md, hi, r;
+#pragma unroll
+  HVX_ROW {
+    const uint32_t mn = pk_min(b.v[k], c.v[k]), mx = pk_max(b.v[k], c.v[k]);
+    lo.v[k] = pk_min(a.v[k], mn);
+    md.v[k] = pk_min(pk_max(a.v[k], mn), mx);
+    hi.v[k] = pk_max(a.v[k], mx);
+  }
+  const PX<LP, 1> l = ext<1>(lo), m = ext<1>(md), h = ext<1>(hi);
+#pragma unroll
+  HVX_ROW r.v[k] = pk_med3(pk_max(pk_max(l.v[k], l.v[k + 1]), l.v[k + 2]), pk_med3(m.v[k], m.v[k + 1], m.v[k + 2]),
+                           pk_min(pk_min(h.v[k], h.v[k + 1]), h.v[k + 2]));
+  return r;
+}
+template <int LP>
+__device__ __forceinline__ PR<LP> row_sobel_x(const PR<LP>& a, const PR<LP>& b, const PR<LP>& c) {
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = pk_mad<2>(b.v[k], pk_add(a.v[k], c.v[k]));
+  const PX<LP, 1> e = ext<1>(t);
+#pragma unroll
+  HVX_ROW r.v[k] = pk_sub(e.v[k + 2], e.v[k]);
+  return r;
+}
+template <int LP>
+__device__ __forceinline__ PR<LP> row_sobel_y(const PR<LP>& a, const PR<LP>& c) {
+  PR<LP> t, r;
+#pragma unroll
+  HVX_ROW t.v[k] = pk_sub(c.v[k], a.v[k]);
+  const PX<LP, 1> e = ext<1>(t);
+#pragma unroll
+  HVX_ROW r.v[k] = pk_mad<2>(e.v[k + 1], pk_add(e.v[k], e.v[k + 2]));
+  return r;
+}
+// NonMaxSuppression over a (2 R + 1)^2 window (w: its rows, top to bottom)
+template <int R, int DF, int LP>
+__device__ __forceinline__ PR<LP> row_nonmax(const PR<LP>* const (&w)[2 * R + 1]) {
+  PX<LP, R> m[2];  // the largest of each column above and below the row
+  {
+    PR<LP> u = *w[0], d = *w[R + 1];
+#pragma unroll
+    for (int j = 1; j < R; ++j)
+#pragma unroll
+      HVX_ROW {
+        u.v[k] = pk_max(u.v[k], w[j]->v[k]);
+        d.v[k] = pk_max(d.v[k], w[R + 1 + j]->v[k]);
+      }
+    m[0] = ext<R>(u);
+    m[1] = ext<R>(d);
+  }
+  const PX<LP, R> e = ext<R>(*w[R]);
+  PR<LP> r;
+#pragma unroll
+  HVX_ROW {
+    uint32_t before = m[0].v[k], after = m[1].v[k];
+#pragma unroll
+    for (int i = 1; i <= 2 * R; ++i) {
+      before = pk_max(before, m[0].v[k + i]);
+      after = pk_max(after, m[1].v[k + i]);
+    }
+#pragma unroll
+    for (int i = 1; i <= R; ++i) {
+      before = pk_max(before, e.v[R + k - i]);
+      after = pk_max(after, e.v[R + k + i]);
+    }
+    const uint32_t p = e.v[R + k];
+    r.v[k] = bit_sel(pk_neg_mask(pk_subs(before, p) & ~pk_subs(p, after)), p, DF == DF_U8 ? 0u : 0x80008000u);
+  }
+  return r;
+}
+// Magnitude of gradients up to 32768: the integer root from the hardware's
+// square root (its error is far below one half), rounded by the exact
+// remainder: with q within one of the root and d = s - q^2, the rounded root
+// is q where d <= q and q + 1 where d > q.
+__device__ __forceinline__ int magnitude_of(uint32_t s) {
+  const uint32_t q = (uint32_t)__builtin_amdgcn_sqrtf((float)s);
+  const uint32_t m = q + ((int)(s - __umul24(q, q)) > (int)q ? 1u : 0u);
+  return (int)min(m, 32767u);
+}
+template <int LP>
+__device__ __forceinline__ PR<LP> row_magnitude(const PR<LP>& a, const PR<LP>& b) {
+  const WR<LP> x = wide(a), y = wide(b);
+  WR<LP> r;
+#pragma unroll
+  for (int q = 0; q < LP; ++q)
+    r.v[q] = magnitude_of((uint32_t)(x.v[q] * x.v[q]) + (uint32_t)(y.v[q] * y.v[q]));
+  return packed(r);
+}
+template <int LP>  // |gradients| <= 1023
+__device__ __forceinline__ PR<LP> row_phase(const PR<LP>& a, const PR<LP>& b) {
+  PR<LP> r;
+#pragma unroll
+  HVX_ROW r.v[k] = phase_pair(a.v[k], b.v[k]) & 0x00FF00FFu;
+  return r;
+}
+// exact products of 16-bit gradients.  NZ: a product of zero and a negative
+// number is +0 rather than -0 (the sums that read it do not tell them apart)
+template <bool NZ, int LP>
+__device__ __forceinline__ WR<LP> row_mulf(const PR<LP>& a, const PR<LP>& b) {
+#pragma clang fp contract(off)
+  const WR<LP> x = wide(a), y = wide(b);
+  WR<LP> r;
+#pragma unroll
+  for (int q = 0; q < LP; ++q)
+    r.v[q] = __float_as_int(NZ ? __builtin_fmaf((float)x.v[q], (float)y.v[q], 0.f) : (float)x.v[q] * (float)y.v[q]);
+  return r;
+}
+// F32 Box5x5 in the fixed order of local_eval: each column top to bottom,
+// then the columns left to right.  NZ: no element is -0, so the leading
+// additions of zero change nothing.
+template <bool NZ, int LP>
+__device__ __forceinline__ WR<LP> row_box5f(const WR<LP>& a, const WR<LP>& b, const WR<LP>& c, const WR<LP>& d,
+                                            const WR<LP>& e) {
+#pragma clang fp contract(off)
+  WR<LP> t, r;
+#pragma unroll
+  for (int q = 0; q < LP; ++q) {
+    float s = NZ ? __int_as_float(a.v[q]) : 0.f + __int_as_float(a.v[q]);
+    s = s + __int_as_float(b.v[q]);
+    s = s + __int_as_float(c.v[q]);
+    s = s + __int_as_float(d.v[q]);
+    t.v[q] = __float_as_int(s + __int_as_float(e.v[q]));
+  }
+  const WX<LP, 2> x = ext<2>(t);
+#pragma unroll
+  for (int q = 0; q < LP; ++q) {
+    float s = NZ ? __int_as_float(x.v[q]) : 0.f + __int_as_float(x.v[q]);
+    s = s + __int_as_float(x.v[q + 1]);
+    s = s + __int_as_float(x.v[q + 2]);
+    s = s + __int_as_float(x.v[q + 3]);
+    r.v[q] = __float_as_int(s + __int_as_float(x.v[q + 4]));
+  }
+  return r;
+}
+#undef HVX_ROW
+
+// Window of wide rows around pixel q, for operators evaluated pixel by pixel.
+template <int LP, int RX, int RY>
+struct RowsRd {
+  const WX<LP, RX> (&w)[2 * RY + 1];
+  int q;
+  __device__ __forceinline__ int operator()(int dx, int dy) const { return w[RY + dy].v[RX + q + dx]; }
+};
+
+}  // namespace hvx

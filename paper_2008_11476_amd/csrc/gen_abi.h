@@ -6,12 +6,12 @@
 namespace hvx {
 
 // One image of a batch run by one generated kernel: its I/O table, its size
-// and the first work-group of the launch that works on it.
+// the first work-group of the launch that works on it and the rows of its bands.
 struct GenBatchImage {
   IOTable io;
   int32_t w, h;
   int32_t block0;
-  int32_t pad;
+  int32_t rows;  // rows of a band (streamed kernels)
 };
 
 // Partial results of one work-group of a generated kernel that reduces

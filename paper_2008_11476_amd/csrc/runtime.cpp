@@ -92,7 +92,7 @@ static hvx_status ensure_scratch(Graph* g) {
     const Group& gr = p.groups[gi];
     if (!gr.gen || gen_batchable(gr.gen)) continue;
     g->ws_off[gi] = total;
-    const size_t bytes = (size_t)gen_blocks(gr.gen, gr.prog.w, gr.prog.h) * red_slot_words(gr.prog) * 4;
+    const size_t bytes = (size_t)gen_blocks(gr.gen, gr.prog.w, gr.prog.h, 0) * red_slot_words(gr.prog) * 4;
     total += (bytes + 255) & ~(size_t)255;
   }
   if (total && hipMalloc((void**)&g->scratch_base, total) != hipSuccess) {
@@ -314,7 +314,7 @@ static hvx_status launch_group(Graph* g, const Group& gr, hipStream_t s, const B
       uint32_t* ws = (uint32_t*)(base + g->ws_off[gi]);
       e = gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, ws);
       if (e == hipSuccess)
-        e = launch_merge_partials(g->dev_progs + gi, io, ws, (int)gen_blocks(gr.gen, P.w, P.h), red_slot_words(P), s);
+        e = launch_merge_partials(g->dev_progs + gi, io, ws, (int)gen_blocks(gr.gen, P.w, P.h, 0), red_slot_words(P), s);
     } else if (e == hipSuccess) {
       e = gr.gen ? gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, nullptr)
                  : launch_generic(P, g->dev_progs + gi, io, g->ctx->num_cus, s);
@@ -481,6 +481,11 @@ static hvx_status batch_build(Batch* b) {
       for (size_t stage = 0; stage < kv.first.size(); ++stage) {
         Batch::GenSet set;
         set.k = kv.first[stage];
+        long long strip_rows = 0;
+        for (Graph* g : kv.second) {
+          const GProg& P = g->plan->groups[stage].prog;
+          strip_rows += (long long)gen_strips(set.k, P.w) * P.h;
+        }
         for (Graph* g : kv.second) {
           const Group& gr = g->plan->groups[stage];
           GenBatchImage im;
@@ -490,7 +495,8 @@ static hvx_status batch_build(Batch* b) {
           im.w = gr.prog.w;
           im.h = gr.prog.h;
           im.block0 = (int32_t)set.blocks;
-          set.blocks += gen_blocks(set.k, gr.prog.w, gr.prog.h);
+          im.rows = gen_rows(set.k, strip_rows, c->num_cus);
+          set.blocks += gen_blocks(set.k, gr.prog.w, gr.prog.h, im.rows);
           if (set.blocks > 0x7FFFFFFF) return set_error(c, HVX_ERROR_NOT_SUPPORTED, "batch launch too large");
           set.imgs.push_back(im);
         }

@@ -1044,11 +1044,11 @@ hvx_status verify_graph(Graph* g) {
         for (int c : p.vals[gr.gvals[i]].consumers) later |= !own.count(c);
         if (!later) stream |= 1u << i;
       }
-      // a chosen tile that does not fit falls back to the default one
+      // a chosen tile that does not fit falls back to the default form
       if (!(tw && gen_source(gr.prog, tw, th, stream, &src, &why)) && !gen_source(gr.prog, 0, 0, stream, &src, &why))
         src.text.clear();
       if (!src.text.empty()) gr.gen = gen_compile(src, &why);
-      if (gr.gen && src.form == GEN_TILES) p.tiles.push_back({gr.ops[0], src.tw, src.th});
+      if (gr.gen && src.form != GEN_POINTS) p.tiles.push_back({gr.ops[0], src.tw, src.th});
       if (gr.gen) {
         ++p.num_generated;
       } else {
