@@ -427,18 +427,19 @@ hvx_status hvx_batch_schedule(hvx_batch b, void* hip_stream);
 hvx_status hvx_process_batch(hvx_context ctx, const hvx_graph* graphs, uint32_t n, void* hip_stream);
 /* HVX_QUERY_ALG_BYTES (bytes one schedule must move), _NUM_KERNELS (launches
  * per schedule), _NUM_OPS (work items of the single launch), _ROWS_PER_ITEM
- * (rows per work item chosen for the batch, 0 = each graph's own). */
+ * (rows per work item set for the batch, 0 = the library's choice). */
 hvx_status hvx_batch_query(hvx_batch b, int attr, int64_t* out);
-/* Batch options.  HVX_BATCH_PERSISTENT (default 1): a grid sized to the
- * machine pulls chunks of work items from per-XCD atomic counters; 0: one
- * wave per work item.  HVX_BATCH_USE_GRAPH (default 1): when a schedule
- * takes more than one launch, capture them once into a HIP graph and replay
- * it (a single launch, or the legacy null stream, is launched plainly).  HVX_BATCH_ROWS (default 0): rows per
- * work item for every image of the single launch (1..65535), 0 = each
- * graph's own; it is what hvx_batch_autotune sets, and setting it pins a
- * launch shape (e.g. a tuned one) without re-tuning.  Changing an option
- * drops the capture; INVALID_PARAMETERS for an unknown option or a value out
- * of range. */
+/* Batch options.  HVX_BATCH_PERSISTENT: 1: a grid sized to the machine pulls
+ * chunks of work items from per-XCD atomic counters; 0: one wave per work
+ * item; never set: the faster of the two as measured by the library.
+ * HVX_BATCH_USE_GRAPH (default 1): when a schedule takes more than one launch,
+ * capture them once into a HIP graph and replay it (a single launch, or the
+ * legacy null stream, is launched plainly).  HVX_BATCH_ROWS (default 0): rows
+ * per work item for every image of the single launch (1..65535), 0 = as pinned
+ * in each graph (HVX_OPT_TILE), else chosen for the batch's sizes; it is what
+ * hvx_batch_autotune sets, and setting it pins a launch shape (e.g. a tuned
+ * one) without re-tuning.  Changing an option drops the capture;
+ * INVALID_PARAMETERS for an unknown option or a value out of range. */
 #define HVX_BATCH_PERSISTENT 1
 #define HVX_BATCH_USE_GRAPH 2
 #define HVX_BATCH_ROWS 3

@@ -136,6 +136,7 @@ struct Group {
   GProg prog{};       // generic program (kind == FK_GENERIC)
   const GenKernel* gen = nullptr;  // kernel generated for `prog` (null: the tile interpreter)
   int rows = 0;       // rows per work item (fast kinds); 0 = tuned or default
+  int own_rows = 0;   // the default for the group alone (set when the graph is prepared)
   int xcd = 1;        // XCD-contiguous work mapping
   uint32_t w = 0, h = 0;
   // indices (into Plan::vals) bound to the fast descriptors' pointers
@@ -228,6 +229,8 @@ hvx_status schedule_graph(Graph* g, void* stream);
 hvx_status schedule_bound(Graph* g, void* stream, const Bind* b);
 void free_graph_device(Graph* g);
 int default_rows(const Group& gr, int num_cus);
+// rows per work item for hand-fused groups that run in one launch
+int rows_together(const std::vector<const Group*>& groups, int num_cus, int waves_per_cu);
 int rows_for(const Graph* g, const Group& gr);  // rows per work item in effect (option, tuned, default)
 void fill_fast_desc(const Graph* g, const Group& gr, BatchImage* bi, int rows_override = 0, const Bind* b = nullptr);
 int64_t fast_items(const Group& gr);

@@ -67,6 +67,8 @@ static hvx_status ensure_scratch(Graph* g) {
       if (e != hipSuccess)
         return set_error(g->ctx, HVX_ERROR_DEVICE, "cannot load a generated kernel: %s", hipGetErrorString(e));
     }
+  for (Group& gr : p.groups)
+    if (is_strip_kind(gr.kind)) gr.own_rows = default_rows(gr, g->ctx->num_cus);
   std::vector<GProg> progs(p.groups.size());
   for (size_t i = 0; i < p.groups.size(); ++i) progs[i] = p.groups[i].prog;
   if (hipMalloc((void**)&g->dev_progs, progs.size() * sizeof(GProg)) != hipSuccess ||
@@ -136,33 +138,83 @@ static const LOp* find_op(const Plan& p, const Group& gr, int kind) {
 
 static std::string tune_key(const Graph* g) { return g->ctx->dev_name + "|" + graph_signature(g); }
 
+static int strip_px(int kind) { return kind == FK_CORNER ? 62 * 4 : kStripPx; }
+
+// Images a launch's rows per work item are chosen for: strips and height of
+// each, and the rows' worth of work an item does before its first output row
+// (halo rows run part of the stages).
+struct RowsFor {
+  std::vector<std::pair<int64_t, int64_t>> images;
+  double start = 0, strip_rows = 0;
+  void add(int kind, int64_t w, int64_t h) {
+    const int64_t strips = (w + strip_px(kind) - 1) / strip_px(kind);
+    images.push_back({strips, h});
+    start += (kind == FK_CORNER ? 2.5 : 1.5) * (double)(strips * h);
+    strip_rows += (double)(strips * h);
+  }
+};
+
+// Rows per work item.  With `w` waves to run on the fullest SIMD an item of
+// r rows and a start of s costs about (r + s)(w + 1) row issues while all
+// waves are resident (a wave alone takes about twice its issue) and
+// (r + s)(w + 2) beyond that (the last round is uneven); the least of it
+// over r weighs the halo rows of short items against the idle SIMDs of tall
+// ones, and lands on item counts just under a whole number of waves per SIMD.
+// Against rows from a power-of-two rule of one image (4 items per CU), which
+// batches used too: one 3840x2160 frame edge + Phase 14.3 -> 9.3 us (8 -> 3
+// rows), Harris 33.2 -> 19.9 (32 -> 9), 640x480 edge + Phase 6.0 -> 3.6
+// (4 -> 1); 64 mixed images 266 -> 140 (2 to 32 rows each -> 17 for all),
+// 32 1920x1080 UYVY frames 43 -> 34.
+static int pick_rows(const RowsFor& f, int64_t simds, int64_t resident) {
+  if (f.images.empty() || f.strip_rows <= 0) return 4;
+  const double start = f.start / f.strip_rows;
+  double best = 1e300;
+  int rows = 4;
+  for (int r = 1; r <= 64; ++r) {
+    int64_t items = 0;
+    for (const auto& i : f.images) items += i.first * ((i.second + r - 1) / r);
+    const double c = (r + start) * ((double)((items + simds - 1) / simds) + (items > resident ? 2 : 1));
+    if (c < best) {
+      best = c;
+      rows = r;
+    }
+  }
+  return rows;
+}
+
+int rows_together(const std::vector<const Group*>& groups, int num_cus, int waves_per_cu) {
+  RowsFor f;
+  for (const Group* g : groups) f.add(g->kind, g->w, g->h);
+  return pick_rows(f, 4LL * num_cus, (int64_t)num_cus * waves_per_cu);
+}
+
 int default_rows(const Group& gr, int num_cus) {
-  // enough work items to give every CU several waves, without letting the
-  // halo rows (footprint on each side) dominate a work item
-  const int sp = gr.kind == FK_CORNER ? 62 * 4 : kStripPx;
-  const int nstrips = ((int)gr.w + sp - 1) / sp;
-  int64_t target = 4LL * num_cus;
-  int64_t rows = ((int64_t)gr.h * nstrips) / std::max<int64_t>(1, target);
-  int r = 4;
-  while (r * 2 <= rows && r < 64) r *= 2;
-  return r;
+  RowsFor f;
+  f.add(gr.kind, gr.w, gr.h);
+  const int64_t simds = 4LL * (num_cus > 0 ? num_cus : 256);
+  return pick_rows(f, simds, 4 * simds);
+}
+
+// The launch shape tuned for the graph, if any.  The key is only built when
+// the context holds tuned shapes: a schedule of a small frame takes a few
+// microseconds of host time in all.
+static const TuneEntry* tuned_shape(const Graph* g) {
+  if (g->ctx->tune.empty()) return nullptr;
+  auto it = g->ctx->tune.find(tune_key(g));
+  return it != g->ctx->tune.end() && it->second.rows > 0 ? &it->second : nullptr;
 }
 
 int rows_for(const Graph* g, const Group& gr) {
   if (gr.rows > 0) return gr.rows;
-  auto it = g->ctx->tune.find(tune_key(g));
-  if (it != g->ctx->tune.end() && it->second.rows > 0) return it->second.rows;
-  return default_rows(gr, g->ctx->num_cus);
+  if (const TuneEntry* t = tuned_shape(g)) return t->rows;
+  return gr.own_rows > 0 ? gr.own_rows : default_rows(gr, g->ctx->num_cus);
 }
 
 static int xcd_for(const Graph* g, const Group& gr) {
   if (gr.rows > 0) return gr.xcd;
-  auto it = g->ctx->tune.find(tune_key(g));
-  if (it != g->ctx->tune.end() && it->second.rows > 0) return it->second.xcd;
+  if (const TuneEntry* t = tuned_shape(g)) return t->xcd;
   return gr.xcd;
 }
-
-static int strip_px(int kind) { return kind == FK_CORNER ? 62 * 4 : kStripPx; }
 
 static StripGrid strip_grid(const Group& gr, int rows) {
   StripGrid s;
@@ -378,11 +430,12 @@ struct Batch : Object {
   uint16_t* d_item_img = nullptr;
   unsigned* d_counter = nullptr;
   int total = 0, grid = 0;
-  bool persistent = true, use_graph = true;
+  int mode = -1;  // HVX_BATCH_PERSISTENT as set, -1 never set: the library's choice
+  bool use_graph = true;
   hipGraph_t hg = nullptr;
   hipGraphExec_t exec = nullptr;
   int64_t alg_bytes = 0;
-  int rows_override = 0;  // rows per work item for every image (0: each graph's own)
+  int rows_override = 0;  // rows per work item for every image (0: chosen for the batch)
   int kinds = 0;          // bit set of the kinds in the single batch launch
   // chains of generated kernels shared by several graphs: one launch per kernel
   struct GenSet {
@@ -436,6 +489,7 @@ static hvx_status batch_build(Batch* b) {
   b->imgs.clear();
   b->separate.clear();
   b->alg_bytes = 0;
+  std::vector<const Graph*> strips;  // graphs that are one hand-fused kernel
   for (Graph* g : b->graphs) {
     if (!g->verified) {
       hvx_status s = verify_graph(g);
@@ -445,13 +499,28 @@ static hvx_status batch_build(Batch* b) {
     if (s) return s;
     b->alg_bytes += g->plan->alg_bytes;
     const auto& gs = g->plan->groups;
-    if (gs.size() == 1 && is_strip_kind(gs[0].kind)) {
+    if (gs.size() == 1 && is_strip_kind(gs[0].kind)) strips.push_back(g);
+    else b->separate.push_back(g);
+  }
+  // the single launch's work items: rows as set for the batch, else as
+  // pinned in a graph, else (several images) the rows that suit them together
+  int together = 0;
+  if (!b->rows_override && strips.size() > 1) {
+    std::vector<const Group*> groups;
+    int kinds = 0;
+    for (const Graph* g : strips) {
+      groups.push_back(&g->plan->groups[0]);
       BatchImage bi;
-      fill_fast_desc(g, gs[0], &bi, b->rows_override);
-      b->imgs.push_back(bi);
-    } else {
-      b->separate.push_back(g);
+      fill_fast_desc(g, *groups.back(), &bi, 1);
+      kinds |= kind_bit(bi);
     }
+    together = rows_together(groups, c->num_cus, batch_waves_per_cu(kinds));
+  }
+  for (const Graph* g : strips) {
+    const Group& gr = g->plan->groups[0];
+    BatchImage bi;
+    fill_fast_desc(g, gr, &bi, b->rows_override ? b->rows_override : (gr.rows > 0 ? 0 : together));
+    b->imgs.push_back(bi);
   }
   // graphs whose plan is a chain of generated kernels: the graphs with the
   // same chain run it as one launch per kernel over all their tiles (a work
@@ -557,7 +626,12 @@ static int64_t batch_launches(const Batch* b) {
 
 static hvx_status batch_enqueue(Batch* b, hipStream_t s) {
   if (b->total > 0) {
-    hipError_t e = launch_batch(b->d_imgs, b->d_item_img, b->total, b->d_counter, b->grid, b->persistent, b->kinds, s);
+    // one wave per item unless asked otherwise: the persistent grid, whose
+    // waves wait out each item's start and end themselves and share counters,
+    // took 5 to 55% longer on every batch measured (64 edge + Phase 4K frames
+    // 331 against 371 us, 64 mixed images 140 against 161, 4 UYVY 1080p frames
+    // 8 against 19)
+    hipError_t e = launch_batch(b->d_imgs, b->d_item_img, b->total, b->d_counter, b->grid, b->mode == 1, b->kinds, s);
     if (e != hipSuccess) return set_error(b->ctx, HVX_ERROR_DEVICE, "batch launch: %s", hipGetErrorString(e));
   }
   for (const auto& set : b->gensets) {
@@ -665,7 +739,7 @@ hvx_status hvx_batch_query(hvx_batch hb, int attr, int64_t* out) {
     case HVX_QUERY_ALG_BYTES: *out = b->alg_bytes; break;
     case HVX_QUERY_NUM_KERNELS: *out = batch_launches(b); break;
     case HVX_QUERY_NUM_OPS: *out = b->total; break;  // work items of the single batch launch
-    case HVX_QUERY_ROWS_PER_ITEM: *out = b->rows_override; break;  // 0: each graph's own
+    case HVX_QUERY_ROWS_PER_ITEM: *out = b->rows_override; break;  // 0: chosen for the batch
     default: return set_error(b->ctx, HVX_ERROR_INVALID_PARAMETERS, "unknown batch query %d", attr);
   }
   return HVX_SUCCESS;
@@ -718,7 +792,7 @@ hvx_status hvx_batch_autotune(hvx_batch hb, void* stream, int iters) {
   std::vector<std::vector<uint8_t>> ref, cur;
   double best = 1e30;
   int best_rows = b->rows_override;
-  bool best_persistent = b->persistent;
+  int best_mode = b->mode;
   hvx_status s = HVX_SUCCESS;
   std::vector<int> cand_rows = {0, 8, 16, 24, 32, 40, 48, 64, 128};
   for (int r : balanced_rows(b))
@@ -728,7 +802,7 @@ hvx_status hvx_batch_autotune(hvx_batch hb, void* stream, int iters) {
     s = batch_build(b);
     if (s) break;
     for (int pers = 0; pers <= 1 && !s; ++pers) {
-      b->persistent = pers != 0;
+      b->mode = pers;
       s = batch_enqueue(b, st);
       if (!s && hipStreamSynchronize(st) != hipSuccess) s = set_error(b->ctx, HVX_ERROR_DEVICE, "tune sync failed");
       if (s) break;
@@ -772,7 +846,7 @@ hvx_status hvx_batch_autotune(hvx_batch hb, void* stream, int iters) {
       if (ms / iters < best) {
         best = ms / iters;
         best_rows = rows;
-        best_persistent = b->persistent;
+        best_mode = b->mode;
       }
     }
     if (s) break;
@@ -780,7 +854,7 @@ hvx_status hvx_batch_autotune(hvx_batch hb, void* stream, int iters) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   b->rows_override = best_rows;
-  b->persistent = best_persistent;
+  b->mode = best_mode;
   b->use_graph = saved_graph;
   hvx_status s2 = batch_build(b);
   return s ? s : s2;
@@ -796,7 +870,7 @@ hvx_status hvx_batch_set_option(hvx_batch hb, int option, int64_t value) {
   b->exec = nullptr;
   b->hg = nullptr;
   switch (option) {
-    case HVX_BATCH_PERSISTENT: b->persistent = value != 0; break;
+    case HVX_BATCH_PERSISTENT: b->mode = value != 0; break;
     case HVX_BATCH_USE_GRAPH: b->use_graph = value != 0; break;
     case HVX_BATCH_ROWS:
       if (value < 0 || value > 65535) return set_error(b->ctx, HVX_ERROR_INVALID_PARAMETERS, "rows %lld", (long long)value);

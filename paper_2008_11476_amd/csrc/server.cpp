@@ -234,10 +234,17 @@ static bool launch_step(Server* sv, StreamSlot& sl, std::vector<Request*>& reqs)
                                         s) != hipSuccess)
           return false;
   std::vector<BatchImage> imgs;
+  auto in_step = [&](const Request* r) { return batchable(r->templ) && sv->mode == HVX_SERVER_CONTINUOUS; };
+  std::vector<const Group*> groups;
+  for (const Request* r : live)
+    if (in_step(r)) groups.push_back(&r->templ->plan->groups[0]);
+  // one request alone: its own rows; several: rows that suit them together
+  const int rows = groups.size() > 1 ? rows_together(groups, sv->ctx->num_cus, 16) : 0;
   for (Request* r : live) {
-    if (batchable(r->templ) && sv->mode == HVX_SERVER_CONTINUOUS) {
+    if (in_step(r)) {
+      const Group& gr = r->templ->plan->groups[0];
       imgs.emplace_back();
-      fill_fast_desc(r->templ, r->templ->plan->groups[0], &imgs.back(), 0, &r->bind);
+      fill_fast_desc(r->templ, gr, &imgs.back(), gr.rows > 0 ? 0 : rows, &r->bind);
     } else if (schedule_bound(r->templ, s, &r->bind) != HVX_SUCCESS) {
       return false;
     }
