@@ -1,10 +1,9 @@
 // Global operators (Table 2): operators that read every pixel of an image
 // and produce a few values.  Each kernel streams the image once in 16-byte
-// chunks (a row split into chunks across the 256 threads of a work-group,
-// four rows a grid size apart loaded together, so that every lane has four
-// independent loads in flight), reduces inside the wave with lane
-// exchanges, and combines work-groups with one global atomic per wave (per
-// bin for the histogram).  The caller's result buffer is
+// chunks (the chunks of all rows dealt out over all threads, four loaded
+// together, so that every lane has four independent loads in flight),
+// reduces inside the wave with lane exchanges, and combines work-groups with
+// one global atomic per group (per bin for the histogram).  The caller's result buffer is
 // initialised by a small kernel in the same stream, so the sequence can be
 // captured into a HIP graph.
 #include <hip/hip_runtime.h>
@@ -22,40 +21,95 @@ namespace hvx {
 
 constexpr int kGThreads = 256;
 
-// Launch shapes, measured on a 16384 x 16384 image.  The histogram combines
-// work-groups through 256 different counters and runs best on many 256-thread
-// groups with two rows in flight.  Min/max and the sums combine through two
-// words each: same-address atomics serialise, so those kernels reduce a
-// whole 1024-thread group in LDS first and launch one group per CU.
+// Launch shapes.  The histogram's groups each add up to 256 counts to the
+// result, so there are few of them and each lane loads eight chunks at a time
+// (3840x2160: 253 groups 9.9 us, 506 of four chunks 13.8, 2025 of one 41); on
+// large images two groups a CU feed the LDS (four where the bins are
+// computed).  Min/max and the sums combine through two words each:
+// same-address atomics serialise, so those kernels reduce a whole 1024-thread
+// group in LDS first and launch one group per CU.
 constexpr int kRThreads = 1024;
 constexpr int kRGroups = 256;
 static_assert(kRGroups <= kMMSubKeys, "one counting key per group");
 
-static int global_grid(const GlobalImg& im, int rows_in_flight, int cap) {
-  const int g = (im.h + rows_in_flight - 1) / rows_in_flight;
-  return g < cap ? g : cap;
+// Work-groups of NT threads for an image read in steps of K chunks a thread.
+static int global_grid(const GlobalImg& im, int per, int nt, int k, int cap) {
+  const long long chunks = (long long)((im.w + per - 1) / per) * im.h, step = (long long)nt * k;
+  const long long g = (chunks + step - 1) / step;
+  return (int)(g < cap ? g : cap);
 }
 
-// Calls f(chunk, valid elements) for every 16-byte chunk of the image
-// (PER elements per chunk) that this thread of an NT-thread group reads.
-// Rows y, y + G, ..., y + (K - 1) G (G the grid size) are loaded together;
-// together the work-groups cover every row once.
+// Calls f(chunks, valid elements) for the 16-byte chunks of the image (PER
+// elements each) that this thread of an NT-thread group reads, K of them
+// loaded together; chunks past the image's end have no valid elements.  The
+// rows' chunks are taken as one sequence, so images of any width keep every
+// lane busy (dealt out by rows, 330x15000 pixels took 21.7 us for min / max,
+// 8.5 so), and f is called by whole waves.  Only the last step tests its
+// loads, and images of whole chunks have no element counts: min / max of
+// 268 MB 44 -> 41 us (6.5 TB/s); with the tests in every step it took 52.
 template <int PER, int NT, int K, class F>
 __device__ __forceinline__ void stream_image(const GlobalImg& im, F&& f) {
-  const int G = gridDim.x;
-  const int chunks = (im.w + PER - 1) / PER;
-  for (int y = blockIdx.x; y < im.h; y += K * G) {
-    for (int c = threadIdx.x; c < chunks; c += NT) {
-      uint4 q[K];
+  const uint32_t h = (uint32_t)im.h, chunks = (uint32_t)(im.w + PER - 1) / PER, total = chunks * h;
+  const uint32_t stride = gridDim.x * NT;  // chunks from one load of a thread to its next
+  const uint32_t dy = stride / chunks, dc = stride - dy * chunks;
+  const uint32_t first = blockIdx.x * NT + threadIdx.x;
+  uint32_t c = first % chunks;
+  // the chunk's address, and what a step adds to it
+  const uint8_t* p = im.base + (int64_t)(first / chunks) * im.pitch + 16 * (int64_t)c;
+  const int64_t dp = (int64_t)dy * im.pitch + 16 * (int64_t)dc, wrap = im.pitch - 16 * (int64_t)chunks;
+  auto advance = [&]() {
+    c += dc;
+    const bool over = c >= chunks;
+    p += dp + (over ? wrap : 0);
+    c -= over ? chunks : 0;
+  };
+  uint32_t i = blockIdx.x * NT;
+  uint4 q[K];
+  int n[K];
+  // steps in which every load of the group lies inside the image
+  if (im.w % PER == 0) {
 #pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (y + k * G < im.h) q[k] = *(const uint4*)(im.base + (size_t)(y + k * G) * im.pitch + 16 * c);
-      const int n = min(PER, im.w - PER * c);
+    for (int k = 0; k < K; ++k) n[k] = PER;
+    for (; i + (K - 1) * stride + NT <= total; i += K * stride) {
 #pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (y + k * G < im.h) f(q[k], n);
+      for (int k = 0; k < K; ++k) {
+        q[k] = *(const uint4*)p;
+        advance();
+      }
+      f(q, n);
+    }
+  } else {
+    for (; i + (K - 1) * stride + NT <= total; i += K * stride) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        n[k] = min(PER, im.w - (int)(PER * c));
+        q[k] = *(const uint4*)p;
+        advance();
+      }
+      f(q, n);
     }
   }
+  if (i < total) {  // the last step
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      // past the end: the first chunk again, with no valid element
+      const bool in = i + k * stride + threadIdx.x < total;
+      n[k] = in ? min(PER, im.w - (int)(PER * c)) : 0;
+      q[k] = *(const uint4*)(in ? p : im.base);
+      advance();
+    }
+    f(q, n);
+  }
+}
+
+// the same, f(chunk, valid elements) for each chunk that holds any
+template <int PER, int NT, int K, class F>
+__device__ __forceinline__ void stream_each(const GlobalImg& im, F&& f) {
+  stream_image<PER, NT, K>(im, [&](const uint4 (&q)[K], const int (&n)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (n[k] > 0) f(q[k], n[k]);
+  });
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, int n, uint32_t a, uint32_t b) {
@@ -72,50 +126,66 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, int n, uint32_t a, uint32_t
 // exact because (v - offset) * num_bins * (m * range - 2^24) < 2^16 * 2^8.
 // v lies in the interval exactly when y < R = range * num_bins * 256 (below
 // the offset y wraps past 2^32 - 2^24).  The 256-bin histogram over [0, 256)
-// takes the byte itself.  Pixels outside the interval, and the bytes past
-// the row's end in its last chunk, go to a spare counter (index 256), so that
-// every lane adds for every byte without a branch.  Each wave counts into its
-// own LDS sub-histogram, held as kCopies interleaved copies (copy c of bin b
-// at word b * kCopies + c, lane l adding to copy l mod kCopies): lanes that
-// draw the same bin, or bins in the same bank, collide less (measured on
-// uniform random bytes: 78 / 71 / 66 / 66 us for 1 / 2 / 4 / 8 copies).
+// takes the byte itself.
+//
+// A group counts into one LDS histogram held as 16 interleaved copies (copy c
+// of bin b at word b * 16 + c, lane l adding to copy l mod 16): at most four
+// lanes of a wave share a counter, whatever the data, and the lanes of a
+// quarter of a wave add to different banks.  Pixels outside the interval, and
+// the bytes past a row's end, add zero.
+// What bounds it: LDS additions, one a pixel.  268 MB, a smooth image 51 us
+// (5.3 TB/s), uniform noise 47 us; with a histogram per wave in four copies,
+// where up to sixteen lanes that drew one bin waited for each other, 101 and
+// 63 us.  (A byte counter per lane and bin, conflict-free but summed every
+// 192 pixels and 64 KB a group, took 84 and 80 us.)
 struct HistBins {
   uint32_t B, D, R, m;
 };
 
+constexpr int kHistCopies = 16, kHistLoads = 8;
+
 template <bool kIdentity>
 __global__ __launch_bounds__(kGThreads) void k_histogram(GlobalImg im, int num_bins, HistBins hb,
                                                          uint32_t* __restrict__ counts) {
-  constexpr int kSlots = 257, kCopies = 4;
-  __shared__ uint32_t sub[kGThreads / 64][kSlots * kCopies];
-  const int t = threadIdx.x, wv = t >> 6;
-  for (int k = t; k < (kGThreads / 64) * kSlots * kCopies; k += kGThreads) (&sub[0][0])[k] = 0;
+  constexpr int K = kHistLoads;
+  __shared__ __attribute__((aligned(16))) uint32_t sub[256 * kHistCopies];
+  const int t = threadIdx.x;
+  for (int k = t; k < 256 * kHistCopies / 4; k += kGThreads) ((uint4*)sub)[k] = uint4{0, 0, 0, 0};
   __syncthreads();
-  uint32_t* mine = sub[wv] + (t & (kCopies - 1));
+  uint32_t* mine = sub + (t & (kHistCopies - 1));
   const uint32_t B = hb.B & 0xFFFFFFu, m = hb.m & 0xFFFFFFu;
-  stream_image<16, kGThreads, 2>(im, [&](const uint4& q, int n) {
-    const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
+  stream_image<16, kGThreads, K>(im, [&](const uint4 (&q)[K], const int (&n)[K]) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const uint32_t v = (wd[k >> 2] >> (8 * (k & 3))) & 0xFFu;
-      uint32_t b;
-      if constexpr (kIdentity) {
-        b = k < n ? v : 256u;
-      } else {
-        const uint32_t y = v * B + hb.D;
-        const uint32_t h = (uint32_t)(((uint64_t)(y & 0xFFFFFFu) * m) >> 32);
-        b = (k < n && y < hb.R) ? h : 256u;
+    for (int r = 0; r < K; ++r) {
+      const uint32_t wd[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+      auto add = [&](int k, bool in) {
+        const uint32_t v = (wd[k >> 2] >> (8 * (k & 3))) & 0xFFu;
+        uint32_t b = v;
+        if constexpr (!kIdentity) {
+          const uint32_t y = v * B + hb.D;
+          b = (uint32_t)(((uint64_t)(y & 0xFFFFFFu) * m) >> 32) & 0xFFu;
+          in = in && y < hb.R;
+        }
+        atomicAdd(&mine[b * kHistCopies], in ? 1u : 0u);
+      };
+      if (__all(n[r] == 16)) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) add(k, true);
+      } else if (n[r] > 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) add(k, k < n[r]);
       }
-      atomicAdd(&mine[b * kCopies], 1u);
     }
   });
   __syncthreads();
   for (int b = t; b < num_bins; b += kGThreads) {
+    const uint4* p = (const uint4*)(sub + b * kHistCopies);
     uint32_t s = 0;
 #pragma unroll
-    for (int w = 0; w < kGThreads / 64; ++w)
-#pragma unroll
-      for (int c = 0; c < kCopies; ++c) s += sub[w][b * kCopies + c];
+    for (int c = 0; c < kHistCopies / 4; ++c) {
+      const uint4 q = p[(c + b) & (kHistCopies / 4 - 1)];
+      s += q.x + q.y + q.z + q.w;
+    }
     if (s) atomicAdd(&counts[b], s);
   }
 }
@@ -130,8 +200,9 @@ hipError_t launch_histogram(const GlobalImg& im, int num_bins, int offset, int r
   hb.D = 0u - (uint32_t)offset * hb.B;
   hb.R = (uint32_t)range * hb.B;
   hb.m = range == 1 ? 0u : (uint32_t)(((1u << 24) + (uint32_t)range - 1) / (uint32_t)range);
-  const dim3 grid(global_grid(im, 2, 2048));
-  if (offset == 0 && range == 256 && num_bins == 256)
+  const bool identity = offset == 0 && range == 256 && num_bins == 256;
+  const dim3 grid(global_grid(im, 16, kGThreads, kHistLoads, identity ? 512 : 1024));
+  if (identity)
     hipLaunchKernelGGL(k_histogram<true>, grid, dim3(kGThreads), 0, s, im, num_bins, hb, counts);
   else
     hipLaunchKernelGGL(k_histogram<false>, grid, dim3(kGThreads), 0, s, im, num_bins, hb, counts);
@@ -142,15 +213,15 @@ hipError_t launch_histogram(const GlobalImg& im, int num_bins, int offset, int r
 // From the 256-bin histogram: cdf(v) by an LDS scan, cdf_min the cdf at the
 // first nonzero bin, and lut[v] = round((cdf(v) - cdf_min) * 255 / (N -
 // cdf_min)) clamped to 0..255, or v itself for an image of one value.
-__global__ __launch_bounds__(256) void k_eq_lut(const uint32_t* __restrict__ hist, uint8_t* __restrict__ lut,
-                                                 long long n) {
-  __shared__ unsigned long long cdf[256];
-  __shared__ int first;
+// (256 threads; returns the entry of value threadIdx.x)
+__device__ __forceinline__ uint8_t eq_entry(const uint32_t* __restrict__ hist, long long n,
+                                            unsigned long long (&cdf)[256], int& first) {
   const int t = threadIdx.x;
+  const uint32_t h = hist[t];
   if (t == 0) first = 256;
-  cdf[t] = hist[t];
+  cdf[t] = h;
   __syncthreads();
-  if (hist[t] != 0) atomicMin(&first, t);
+  if (h != 0) atomicMin(&first, t);
   for (int d = 1; d < 256; d <<= 1) {  // inclusive scan
     const unsigned long long add = t >= d ? cdf[t - d] : 0ull;
     __syncthreads();
@@ -165,15 +236,29 @@ __global__ __launch_bounds__(256) void k_eq_lut(const uint32_t* __restrict__ his
     long long r = num >= 0 ? (2 * num + den) / (2 * den) : 0;
     v = (int)(r > 255 ? 255 : r);
   }
-  lut[t] = (uint8_t)v;
+  return (uint8_t)v;
 }
 
-// out = lut[in], 16 bytes per lane per step; rows strided over the grid.  A
-// thread reads and writes the same chunk, so in place is allowed.
-__global__ __launch_bounds__(kGThreads) void k_apply_lut(GlobalImg im, const uint8_t* __restrict__ lut,
+__global__ __launch_bounds__(256) void k_eq_lut(const uint32_t* __restrict__ hist, uint8_t* __restrict__ lut,
+                                                 long long n) {
+  __shared__ unsigned long long cdf[256];
+  __shared__ int first;
+  lut[threadIdx.x] = eq_entry(hist, n, cdf, first);
+}
+
+// out = the mapping of in, 16 bytes per lane per step; rows strided over the
+// grid.  A thread reads and writes the same chunk, so in place is allowed.
+// Every group forms the mapping from the histogram itself (about a
+// microsecond, behind the other groups' streaming; as a kernel of its own it
+// held the stream for 5 us); the first also writes it to `lut`.
+__global__ __launch_bounds__(kGThreads) void k_apply_lut(GlobalImg im, const uint32_t* __restrict__ hist, uint8_t* lut,
                                                          uint8_t* out, int64_t out_pitch) {
   __shared__ uint8_t tab[256];
-  tab[threadIdx.x] = lut[threadIdx.x];
+  __shared__ unsigned long long cdf[256];
+  __shared__ int first;
+  const uint8_t entry = eq_entry(hist, (long long)im.w * im.h, cdf, first);
+  tab[threadIdx.x] = entry;
+  if (blockIdx.x == 0) lut[threadIdx.x] = entry;
   __syncthreads();
   const int chunks = (im.w + 15) >> 4;
   for (int y = blockIdx.x; y < im.h; y += gridDim.x) {
@@ -207,10 +292,12 @@ hipError_t launch_equalize_mapping(const GlobalImg& im, void* workspace, hipStre
 
 hipError_t launch_equalize_hist(const GlobalImg& im, uint8_t* out, int64_t out_pitch, void* workspace,
                                 hipStream_t s) {
-  const uint8_t* lut = (const uint8_t*)workspace + 256 * 4;
-  hipError_t e = launch_equalize_mapping(im, workspace, s);
+  uint32_t* hist = (uint32_t*)workspace;
+  uint8_t* lut = (uint8_t*)workspace + 256 * 4;
+  hipError_t e = launch_histogram(im, 256, 0, 256, hist, s);
   if (e != hipSuccess || im.w <= 0 || im.h <= 0) return e;
-  hipLaunchKernelGGL(k_apply_lut, dim3(im.h < 2048 ? im.h : 2048), dim3(kGThreads), 0, s, im, lut, out, out_pitch);
+  hipLaunchKernelGGL(k_apply_lut, dim3(im.h < 2048 ? im.h : 2048), dim3(kGThreads), 0, s, im, (const uint32_t*)hist, lut,
+                     out, out_pitch);
   return hipGetLastError();
 }
 
@@ -251,7 +338,7 @@ __global__ __launch_bounds__(kRThreads) void k_min_max(GlobalImg im, int32_t* __
   __shared__ int part[2][kRThreads / 64];
   int mn = INT_MAX, mx = INT_MIN;
   const int t = threadIdx.x;
-  stream_image<kPer, kRThreads, 4>(im, [&](const uint4& q, int n) {
+  stream_each<kPer, kRThreads, 4>(im, [&](const uint4& q, int n) {
     const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
@@ -300,9 +387,9 @@ __device__ __forceinline__ uint32_t count_eq(uint32_t w, uint32_t splat, uint32_
 // each.  Every lane keeps a running (value, count) pair per extreme: for each
 // 16-byte chunk it takes the chunk's extremes, restarts a count when the
 // value improves, and adds the chunk's matches counted word-wise.  The pairs
-// are merged across the wave and the group, then into the group's own
-// 64-bit key of each extreme (at most kMMSubKeys groups run, so no two share
-// a key and the compare-and-swap never retries; see kMMSubKeys).
+// are merged across the wave and the group, and stored as the group's own
+// 64-bit key of each extreme (at most kMMSubKeys groups run; the keys no group
+// owns are set neutral, so nothing is initialised before).
 template <bool S16>
 __global__ __launch_bounds__(kRThreads) void k_min_max_count(GlobalImg im, unsigned long long* __restrict__ keys) {
   constexpr int kPer = S16 ? 8 : 16;
@@ -310,7 +397,7 @@ __global__ __launch_bounds__(kRThreads) void k_min_max_count(GlobalImg im, unsig
   int mn = S16 ? 32767 : 255, mx = S16 ? -32768 : 0;
   uint32_t cmn = 0, cmx = 0;
   const int t = threadIdx.x;
-  stream_image<kPer, kRThreads, 4>(im, [&](const uint4& q, int n) {
+  stream_each<kPer, kRThreads, 4>(im, [&](const uint4& q, int n) {
     const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
     if (n == kPer) {
       int a = S16 ? 32767 : 255, b = S16 ? -32768 : 0;
@@ -355,9 +442,10 @@ __global__ __launch_bounds__(kRThreads) void k_min_max_count(GlobalImg im, unsig
       kmin = mm_merge(kmin, mm_key(part[0][w], (uint32_t)part[1][w]), true);
       kmax = mm_merge(kmax, mm_key(part[2][w], (uint32_t)part[3][w]), false);
     }
-    const int sub = blockIdx.x % kMMSubKeys;
-    merge_key(&keys[sub], kmin, true);
-    merge_key(&keys[kMMSubKeys + sub], kmax, false);
+    for (int i = blockIdx.x; i < kMMSubKeys; i += gridDim.x) {  // the group's key; the rest neutral
+      keys[i] = i < (int)gridDim.x ? kmin : kMinKeyInit;
+      keys[kMMSubKeys + i] = i < (int)gridDim.x ? kmax : kMaxKeyInit;
+    }
   }
 }
 
@@ -393,11 +481,13 @@ __global__ __launch_bounds__(256) void k_init_keys(int32_t* __restrict__ mm) {
 
 hipError_t launch_min_max_count(const GlobalImg& im, int32_t* result, hipStream_t s) {
   unsigned long long* keys = (unsigned long long*)((uint8_t*)result + kMMKeyOffset);
-  hipLaunchKernelGGL(k_init_keys, dim3(1), dim3(256), 0, s, result);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (im.w > 0 && im.h > 0) {
-    const dim3 grid(global_grid(im, 4, kRGroups));
+  hipError_t e = hipSuccess;
+  if (im.w <= 0 || im.h <= 0) {
+    hipLaunchKernelGGL(k_init_keys, dim3(1), dim3(256), 0, s, result);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  } else {
+    const dim3 grid(global_grid(im, im.bpp == 2 ? 8 : 16, kRThreads, 4, kRGroups));
     if (im.bpp == 2) hipLaunchKernelGGL(k_min_max_count<true>, grid, dim3(kRThreads), 0, s, im, keys);
     else hipLaunchKernelGGL(k_min_max_count<false>, grid, dim3(kRThreads), 0, s, im, keys);
     e = hipGetLastError();
@@ -509,7 +599,8 @@ hipError_t launch_extreme_locs(const GlobalImg& im, int32_t* result, uint32_t* l
   hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)result + 4, 2, 0u, 0u);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || im.w <= 0 || im.h <= 0 || cap == 0) return e;
-  const dim3 grid(global_grid(im, 4, kRGroups));
+  const int steps = (im.h + 3) / 4;  // four rows a step
+  const dim3 grid(steps < kRGroups ? steps : kRGroups);
   if (im.bpp == 2) hipLaunchKernelGGL(k_extreme_locs<true>, grid, dim3(kRThreads), 0, s, im, result, lmin, lmax, cap);
   else hipLaunchKernelGGL(k_extreme_locs<false>, grid, dim3(kRThreads), 0, s, im, result, lmin, lmax, cap);
   return hipGetLastError();
@@ -541,7 +632,7 @@ hipError_t launch_min_max(const GlobalImg& im, int32_t* min_max, hipStream_t s) 
                      (uint32_t)INT_MIN);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || im.w <= 0 || im.h <= 0) return e;
-  const dim3 grid(global_grid(im, 4, kRGroups));
+  const dim3 grid(global_grid(im, im.bpp == 2 ? 8 : 16, kRThreads, 4, kRGroups));
   if (im.bpp == 2) hipLaunchKernelGGL(k_min_max<true>, grid, dim3(kRThreads), 0, s, im, min_max);
   else hipLaunchKernelGGL(k_min_max<false>, grid, dim3(kRThreads), 0, s, im, min_max);
   return hipGetLastError();
@@ -555,7 +646,7 @@ __global__ __launch_bounds__(kRThreads) void k_sums(GlobalImg im, unsigned long 
   __shared__ unsigned long long part[2][kRThreads / 64];
   unsigned long long s1 = 0, s2 = 0;
   const int t = threadIdx.x;
-  stream_image<16, kRThreads, 4>(im, [&](const uint4& q, int n) {
+  stream_each<16, kRThreads, 4>(im, [&](const uint4& q, int n) {
     const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
     uint32_t a = 0, b = 0;  // at most 16 * 255^2 < 2^21
 #pragma unroll
@@ -600,7 +691,7 @@ hipError_t launch_mean_std_dev(const GlobalImg& im, void* result, hipStream_t s)
   hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)result, 6, 0u, 0u);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || im.w <= 0 || im.h <= 0) return e;
-  hipLaunchKernelGGL(k_sums, dim3(global_grid(im, 4, kRGroups)), dim3(kRThreads), 0, s, im,
+  hipLaunchKernelGGL(k_sums, dim3(global_grid(im, im.bpp == 2 ? 8 : 16, kRThreads, 4, kRGroups)), dim3(kRThreads), 0, s, im,
                      (unsigned long long*)result);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
