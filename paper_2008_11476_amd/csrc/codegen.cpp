@@ -1094,7 +1094,9 @@ hipError_t gen_load(const GenKernel* kc, int device) {
 }
 
 // threads of a work-group: a streamed item is one wave's
-static unsigned gen_threads(const GenKernel* k) { return k->form == GEN_STREAM ? 64 : kGenThreads; }
+static unsigned gen_threads(const GenKernel* k) {
+  return k->form != GEN_STREAM ? kGenThreads : (k->red ? 64 * kStreamRedWaves : 64);
+}
 
 hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
                       int num_cus, hipStream_t s, uint32_t* ws) {
@@ -1104,7 +1106,7 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GPro
   // overlaps one group's loads with another's arithmetic as well).  A
   // group that reduces writes its partial results to its slot of `ws`.
   int rows = gen_rows(k, (long long)gen_strips(k, P.w) * P.h, num_cus);
-  const long long grid = gen_blocks(k, P.w, P.h, rows);
+  const long long grid = gen_slots(k, P.w, P.h, num_cus);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (k->red && !ws) return hipErrorInvalidValue;
@@ -1127,6 +1129,20 @@ int gen_rows(const GenKernel* k, long long strip_rows, int num_cus) {
   // one 4K frame at 4 to 12, batches at 20 to 32 (32 4K frames: Tomasi
   // 515 us at 32 rows, 647 at 4, 553 at 96).
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
+  if (k->red) {
+    // the waves of a reducing kernel go on from item to item: whole rounds of
+    // the waves that run at once, of short bands
+    int best = k->th;
+    double cost = 1e300;
+    for (int r = k->th; r <= 64; r += k->th) {
+      const double c = ceil((double)strip_rows / r / (4 * simds)) * (r + k->ext + 3);
+      if (c < cost) {
+        cost = c;
+        best = r;
+      }
+    }
+    return best;
+  }
   const double r = sqrt(0.4 * (double)strip_rows * (k->ext + 3) / simds);
   return std::min(std::max((int)(r / k->th + 0.5), 1), 32 / k->th) * k->th;
 }
@@ -1137,6 +1153,14 @@ long long gen_blocks(const GenKernel* k, int w, int h, int rows) {
   if (k->form == GEN_POINTS) return (long long)((w + 1023) >> 10) * h;
   if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * ((h + rows - 1) / rows);
   return (long long)((w + k->tw - 1) / k->tw) * ((h + k->th - 1) / k->th);
+}
+
+long long gen_slots(const GenKernel* k, int w, int h, int num_cus) {
+  const long long n = gen_blocks(k, w, h, gen_rows(k, (long long)gen_strips(k, w) * h, num_cus));
+  // a streamed kernel that reduces: groups of eight items' waves, at most two
+  // a CU, each going on to further items
+  if (k->form != GEN_STREAM || !k->red) return n;
+  return std::min((n + kStreamRedWaves - 1) / kStreamRedWaves, 2LL * (num_cus > 0 ? num_cus : 256));
 }
 
 bool gen_batchable(const GenKernel* k) { return !k->red; }

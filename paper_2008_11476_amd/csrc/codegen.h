@@ -21,6 +21,10 @@ namespace hvx {
 
 struct GenKernel;
 
+// Waves of a work-group of a streamed kernel that reduces global operators:
+// they share one histogram and one slot of partial results.
+constexpr int kStreamRedWaves = 8;
+
 // Launch shape of a generated kernel.
 enum GenForm : int32_t {
   GEN_POINTS = 1,  // point operators only: four pixels of one row per thread, no LDS
@@ -60,7 +64,7 @@ hipError_t gen_load(const GenKernel* k, int device);
 
 // Launch on stream s (gen_load must have succeeded on the current device).
 // A kernel that reduces global operators (not gen_batchable) writes one slot
-// of red_slot_words(P) words per work-group, gen_blocks of them, to `ws`.
+// of red_slot_words(P) words per work-group, gen_slots of them, to `ws`.
 hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
                       int num_cus, hipStream_t s, uint32_t* ws);
 
@@ -73,6 +77,9 @@ int gen_rows(const GenKernel* k, long long strip_rows, int num_cus);
 // (one per tile, one per 1024 pixels of a row for the point form, one per
 // strip and band of `rows` rows for the streaming form).
 long long gen_blocks(const GenKernel* k, int w, int h, int rows);
+
+// Work-groups of gen_launch for a w x h image.
+long long gen_slots(const GenKernel* k, int w, int h, int num_cus);
 
 // Whether one launch can run the kernel over a batch of images (a kernel
 // that reduces global operators cannot: each image has its own result).

@@ -43,4 +43,20 @@ __device__ __forceinline__ void wave_merge_extremes(int& mn, uint32_t& cmn, int&
   }
 }
 
+// Partial results (a, b) of one global operator merged with (x, y): the sums,
+// {smallest, largest} as 32-bit values, or the keys of the extremes.
+__device__ __forceinline__ void red_merge(int kind, unsigned long long& a, unsigned long long& b, unsigned long long x,
+                                          unsigned long long y) {
+  if (kind == OP_SUMS) {
+    a += x;
+    b += y;
+  } else if (kind == OP_MINMAX) {
+    a = (unsigned)min((int)(unsigned)a, (int)(unsigned)x);
+    b = (unsigned)max((int)(unsigned)b, (int)(unsigned)y);
+  } else {
+    a = mm_merge(a, x, true);
+    b = mm_merge(b, y, false);
+  }
+}
+
 }  // namespace hvx

@@ -599,6 +599,106 @@ __device__ __forceinline__ WR<LP> row_box5f(const WR<LP>& a, const WR<LP>& b, co
 }
 #undef HVX_ROW
 
+// ---- global operators reduced over the strips ---------------------------------------------
+// A group of waves keeps one LDS histogram in 16 interleaved copies (at
+// most four lanes of a wave share a counter) and each lane its partial sums or
+// extremes over its items; the group writes them to its slot at the end.
+constexpr int kStreamHistCopies = 16;
+
+// Calls f(element, counted) for the lane's pixels of row t it owns.
+template <bool EDGE, int LP, class F>
+__device__ __forceinline__ void own_pixels(const PR<LP>& p, const Strip& s, int t, F&& f) {
+  if (!(s.keep || (EDGE && s.ragged)) || (EDGE && t >= s.H)) return;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k) {
+    f((int)(int16_t)(uint16_t)p.v[k], !EDGE || s.x0 + k < s.W);
+    f((int)p.v[k] >> 16, !EDGE || s.x0 + k + LP / 2 < s.W);
+  }
+}
+// (value - OFF) * BINS / RANGE for values of [OFF, OFF + RANGE)
+template <int BINS, int OFF, int RANGE>
+__device__ __forceinline__ void hist_add(uint32_t* mine, int v, bool in) {
+  uint32_t b = (uint32_t)v;
+  if constexpr (BINS != 256 || OFF != 0 || RANGE != 256) {
+    const uint32_t x = (uint32_t)(v - OFF);
+    in = in && x < (uint32_t)RANGE;
+    b = in ? x * (uint32_t)BINS / (uint32_t)RANGE : 0u;
+  }
+  atomicAdd(&mine[b * kStreamHistCopies], in ? 1u : 0u);
+}
+__device__ __forceinline__ void sums_add(RedSlot& q, int v, bool in) {
+  const uint32_t x = in ? (uint32_t)v : 0u;
+  q.cmn += x;  // 32-bit sums of one band, widened at its end (sums_wrap)
+  q.cmx += __umul24(x, x);
+}
+__device__ __forceinline__ void sums_wrap(RedSlot& q) {
+  q.s1 += q.cmn;
+  q.s2 += q.cmx;
+  q.cmn = q.cmx = 0;
+}
+__device__ __forceinline__ void minmax_add(RedSlot& q, int v, bool in) {
+  q.mn = min(q.mn, in ? v : 2147483647);
+  q.mx = max(q.mx, in ? v : -2147483647 - 1);
+}
+__device__ __forceinline__ void mmcount_add(RedSlot& q, int v, bool in) {
+  if (!in) return;
+  q.cmn = v < q.mn ? 1u : q.cmn + (v == q.mn ? 1u : 0u);
+  q.cmx = v > q.mx ? 1u : q.cmx + (v == q.mx ? 1u : 0u);
+  q.mn = min(q.mn, v);
+  q.mx = max(q.mx, v);
+}
+__device__ __forceinline__ RedSlot red_slot() {
+  RedSlot q;
+  q.mn = 2147483647;
+  q.mx = -2147483647 - 1;
+  q.cmn = q.cmx = 0;
+  q.s1 = q.s2 = 0;
+  return q;
+}
+// The group's result of one operator, to its slot (the layout of
+// red_slot_words); `part` holds two words per wave.
+template <int KIND, int NT>
+__device__ __forceinline__ void red_store(const RedSlot& q, unsigned long long (&part)[2][NT / 64], uint32_t* slot) {
+  unsigned long long a, b;
+  int mn = q.mn, mx = q.mx;
+  uint32_t cmn = q.cmn, cmx = q.cmx;
+  if constexpr (KIND == OP_SUMS) {
+    a = q.s1;
+    b = q.s2;
+  } else if constexpr (KIND == OP_MINMAX) {
+    a = (unsigned)mn;
+    b = (unsigned)mx;
+  } else {
+    wave_merge_extremes(mn, cmn, mx, cmx);
+    a = cmn ? mm_key(mn, cmn) : kMinKeyInit;
+    b = cmx ? mm_key(mx, cmx) : kMaxKeyInit;
+  }
+  if constexpr (KIND != OP_MMCOUNT) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      red_merge(KIND, a, b, __shfl_xor(a, off), __shfl_xor(b, off));
+    }
+  }
+  __syncthreads();  // `part` is free
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = a;
+    part[1][threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NT / 64; ++w) red_merge(KIND, a, b, part[0][w], part[1][w]);
+    if constexpr (KIND == OP_MINMAX) {
+      slot[0] = (uint32_t)a;
+      slot[1] = (uint32_t)b;
+    } else {
+      slot[0] = (uint32_t)a;
+      slot[1] = (uint32_t)(a >> 32);
+      slot[2] = (uint32_t)b;
+      slot[3] = (uint32_t)(b >> 32);
+    }
+  }
+}
+
 // Window of wide rows around pixel q, for operators evaluated pixel by pixel.
 template <int LP, int RX, int RY>
 struct RowsRd {

@@ -34,15 +34,14 @@ hipError_t launch_extreme_locs(const GlobalImg& im, int32_t* result, uint32_t* l
 hipError_t launch_clamp_slots(int32_t* result, uint32_t cap, hipStream_t s);
 // histogram and EqualizeHist mapping into `workspace` (counts, then the table)
 hipError_t launch_equalize_mapping(const GlobalImg& im, void* workspace, hipStream_t s);
-// starting value and final step of a global operator (OP_*) that fused
-// kernels reduce into `result`
+// starting value and final step of a global operator (OP_*) that the
+// interpreter reduces into `result`
 hipError_t launch_reduce_init(int kind, void* result, int num_bins, hipStream_t s);
 hipError_t launch_reduce_finish(int kind, void* result, long long npix, hipStream_t s);
-// The partial results a generated reducing kernel left in `ws` (nslots
-// slots of slot_words words, red_slot_words) merged into the results of the
-// program's reduce operators (between launch_reduce_init and _finish).
-hipError_t launch_merge_partials(const GProg* dev_prog, const IOTable& io, const uint32_t* ws, int nslots,
-                                 int slot_words, hipStream_t s);
+// The partial results a generated reducing kernel left in `ws` (nslots slots
+// of red_slot_words words) made the results of the program's reduce operators.
+hipError_t launch_finish_partials(const GProg& P, const GProg* dev_prog, const IOTable& io, const uint32_t* ws,
+                                  int nslots, hipStream_t s);
 // n uint32 words of device memory set to zero
 hipError_t launch_zero_words(void* p, int n, hipStream_t s);
 

@@ -88,13 +88,14 @@ static hvx_status ensure_scratch(Graph* g) {
     total += (pitch * p.vals[v].h + 255) & ~(size_t)255;
   }
   // workspace of the generated kernels that reduce: one slot of partial
-  // results per work-group (tile)
+  // results per work-group
   g->ws_off.assign(p.groups.size(), 0);
   for (size_t gi = 0; gi < p.groups.size(); ++gi) {
     const Group& gr = p.groups[gi];
     if (!gr.gen || gen_batchable(gr.gen)) continue;
     g->ws_off[gi] = total;
-    const size_t bytes = (size_t)gen_blocks(gr.gen, gr.prog.w, gr.prog.h, 0) * red_slot_words(gr.prog) * 4;
+    const size_t bytes =
+        (size_t)gen_slots(gr.gen, gr.prog.w, gr.prog.h, g->ctx->num_cus) * red_slot_words(gr.prog) * 4;
     total += (bytes + 255) & ~(size_t)255;
   }
   if (total && hipMalloc((void**)&g->scratch_base, total) != hipSuccess) {
@@ -353,30 +354,31 @@ static hvx_status launch_group(Graph* g, const Group& gr, hipStream_t s, const B
     IOTable io;
     hvx_status fs = fill_io(g, gr, &io, b);
     if (fs) return fs;
-    // global operators reduced by the kernel: starting values before it,
-    // final values after it, in the same stream
     const GProg& P = gr.prog;
-    for (int i = 0; i < P.nops && e == hipSuccess; ++i)
-      if (is_reduce_op(P.ops[i].kind))
-        e = launch_reduce_init(P.ops[i].kind, io.ptr[P.vals[P.ops[i].out].io], P.ops[i].p0, s);
-    if (e == hipSuccess && gr.gen && !gen_batchable(gr.gen)) {
+    if (gr.gen && !gen_batchable(gr.gen)) {
       // a generated kernel that reduces leaves one slot of partial results
-      // per work-group; a second kernel merges them into the results
+      // per work-group; a second kernel forms the results from them
       char* base = b && b->scratch ? b->scratch : g->scratch_base;
       uint32_t* ws = (uint32_t*)(base + g->ws_off[gi]);
       e = gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, ws);
       if (e == hipSuccess)
-        e = launch_merge_partials(g->dev_progs + gi, io, ws, (int)gen_blocks(gr.gen, P.w, P.h, 0), red_slot_words(P), s);
-    } else if (e == hipSuccess) {
-      e = gr.gen ? gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, nullptr)
-                 : launch_generic(P, g->dev_progs + gi, io, g->ctx->num_cus, s);
+        e = launch_finish_partials(P, g->dev_progs + gi, io, ws, (int)gen_slots(gr.gen, P.w, P.h, g->ctx->num_cus), s);
+    } else if (gr.gen) {
+      e = gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, nullptr);
+    } else {
+      // global operators reduced by the interpreter: starting values before
+      // it, final values after it, in the same stream
+      for (int i = 0; i < P.nops && e == hipSuccess; ++i)
+        if (is_reduce_op(P.ops[i].kind))
+          e = launch_reduce_init(P.ops[i].kind, io.ptr[P.vals[P.ops[i].out].io], P.ops[i].p0, s);
+      if (e == hipSuccess) e = launch_generic(P, g->dev_progs + gi, io, g->ctx->num_cus, s);
+      for (int i = 0; i < P.nops && e == hipSuccess; ++i)
+        if (is_reduce_op(P.ops[i].kind)) {
+          void* out = io.ptr[P.vals[P.ops[i].out].io];
+          e = launch_reduce_finish(P.ops[i].kind, out, (long long)P.w * P.h, s);
+          if (e == hipSuccess && P.ops[i].kind == OP_MMCOUNT) e = launch_zero_words((int32_t*)out + 4, 2, s);
+        }
     }
-    for (int i = 0; i < P.nops && e == hipSuccess; ++i)
-      if (is_reduce_op(P.ops[i].kind)) {
-        void* out = io.ptr[P.vals[P.ops[i].out].io];
-        e = launch_reduce_finish(P.ops[i].kind, out, (long long)P.w * P.h, s);
-        if (e == hipSuccess && P.ops[i].kind == OP_MMCOUNT) e = launch_zero_words((int32_t*)out + 4, 2, s);
-      }
   } else if (gr.kind == FK_GLOBAL) {
     e = launch_global_group(g, gr, s, b);
   } else {

@@ -142,3 +142,41 @@ def test_streamed_batch_of_tall_bands(ctx):
         for name, (t, w, dt) in keep["outputs"].items():
             assert np.array_equal(t.cpu().numpy().view(dt)[:, :w], got[name]), name
     hvx.hvx_release_batch(b)
+
+
+# pairs of global operators fused into streamed producers: U8 and S16 inputs
+# of the reduction, bins that do and do not divide their interval
+REDUCTIONS = {
+    "hist+sums": ([("histogram", "g", {"bins": 256}), ("mean_std_dev", "g", {})], {"bins": 1024, "r1": 64}),
+    "hist10+counts": ([("histogram", "g", {"bins": 10, "offset": 5, "range": 201}), ("min_max_loc", "g", {})],
+                      {"bins": 1024, "r1": 4128}),
+    "s16": ([("min_max", "gx", {}), ("min_max_loc", "gy", {})], {"bins": 8, "r1": 4128}),
+    "point": ([("histogram", "t", {"bins": 3, "range": 256}), ("mean_std_dev", "t", {})], {"bins": 1024, "r1": 64}),
+}
+
+
+@pytest.mark.parametrize("which", list(REDUCTIONS))
+@pytest.mark.parametrize("w,h,border", [(3001, 2003, "replicate"), (497, 61, "mirror"), (3, 2, "constant"),
+                                        (1, 1, "replicate"), (64, 3000, "undefined")])
+def test_streamed_reductions(ctx, which, w, h, border):
+    """One to many items per wave, ragged last columns and bands; a second run
+    over the same buffers starts afresh."""
+    import torch
+    from tests.test_gpu_global_graph import _check_buffers
+    ops, bufs = REDUCTIONS[which]
+    b = ("replicate", 0) if border == "undefined" else (border, 9)
+    nodes = [gs.N("gaussian3x3", ["in"], ["g"], *b), gs.N("sobel3x3", ["g"], ["gx", "gy"], *b),
+             gs.N("threshold", ["in"], ["t"], params={"thresh": 99.0, "true_v": 200, "false_v": 90})]
+    used = {src for (_, src, _) in ops}
+    nodes = [n for n in nodes if used & set(n.outs) or (n.outs == ["g"] and "gx" in used)]
+    nodes += [gs.N(op, [src], [buf], params=dict(p)) for (op, src, p), buf in zip(ops, bufs)]
+    spec = gs.Spec(nodes, {"in": synth.edge_image(w, h, seed=w)}, {}, buffers=bufs)
+    log("stream reductions %s %dx%d" % (which, w, h))
+    keep = {}
+    got, g = run_spec(spec, ctx, keep=keep)
+    assert hvx.hvx_graph_query(g, hvx.HVX_QUERY_NUM_KERNELS) == 1
+    env = spec.run_oracle()
+    _check_buffers(spec, got, env)
+    hvx.hvx_graph_process(g, ctx=ctx)
+    torch.cuda.synchronize()
+    _check_buffers(spec, {n: t.cpu().numpy() for n, t in keep["buffers"].items()}, env)
