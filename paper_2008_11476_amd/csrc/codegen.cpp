@@ -1105,7 +1105,7 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GPro
   // the CUs measured slower: the hardware's own dispatch of short groups
   // overlaps one group's loads with another's arithmetic as well).  A
   // group that reduces writes its partial results to its slot of `ws`.
-  int rows = gen_rows(k, (long long)gen_strips(k, P.w) * P.h, num_cus);
+  int rows = gen_rows(k, (long long)gen_strips(k, P.w) * P.h, P.h % 4 == 0, num_cus);
   const long long grid = gen_slots(k, P.w, P.h, num_cus);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -1118,7 +1118,13 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GPro
   return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
-int gen_rows(const GenKernel* k, long long strip_rows, int num_cus) {
+// bands of an image of a streamed kernel (as the kernel computes them)
+static int stream_bands(const GenKernel* k, int h, int rows) {
+  const int tail = (k->ext + k->th - 1) / k->th * k->th;
+  return h < tail + 2 * k->th ? 1 : (h - tail + ((tail - h) & (k->th - 1)) + rows - 1) / rows + (tail > 0);
+}
+
+int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int num_cus) {
   if (k->form != GEN_STREAM) return 0;
   // Bands of r rows cost strip_rows / r items of r + ext + 3 steps each (the
   // steps before the first output row run part of the operators; 3 stand for
@@ -1129,12 +1135,15 @@ int gen_rows(const GenKernel* k, long long strip_rows, int num_cus) {
   // one 4K frame at 4 to 12, batches at 20 to 32 (32 4K frames: Tomasi
   // 515 us at 32 rows, 647 at 4, 553 at 96).
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
+  // a band holds the rows that its neighbours read and share (emit_geometry)
+  const int shift = whole_heights ? 0 : k->th - 1;
+  const int least = std::max(1, (k->ext + shift + k->th - 1) / k->th);
   if (k->red) {
     // the waves of a reducing kernel go on from item to item: whole rounds of
     // the waves that run at once, of short bands
-    int best = k->th;
+    int best = least * k->th;
     double cost = 1e300;
-    for (int r = k->th; r <= 64; r += k->th) {
+    for (int r = best; r <= 64; r += k->th) {
       const double c = ceil((double)strip_rows / r / (4 * simds)) * (r + k->ext + 3);
       if (c < cost) {
         cost = c;
@@ -1144,19 +1153,19 @@ int gen_rows(const GenKernel* k, long long strip_rows, int num_cus) {
     return best;
   }
   const double r = sqrt(0.4 * (double)strip_rows * (k->ext + 3) / simds);
-  return std::min(std::max((int)(r / k->th + 0.5), 1), 32 / k->th) * k->th;
+  return std::min(std::max((int)(r / k->th + 0.5), least), 32 / k->th) * k->th;
 }
 
 int gen_strips(const GenKernel* k, int w) { return k->form == GEN_STREAM ? (w + k->tw - 1) / k->tw : 0; }
 
 long long gen_blocks(const GenKernel* k, int w, int h, int rows) {
   if (k->form == GEN_POINTS) return (long long)((w + 1023) >> 10) * h;
-  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * ((h + rows - 1) / rows);
+  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * stream_bands(k, h, rows);
   return (long long)((w + k->tw - 1) / k->tw) * ((h + k->th - 1) / k->th);
 }
 
 long long gen_slots(const GenKernel* k, int w, int h, int num_cus) {
-  const long long n = gen_blocks(k, w, h, gen_rows(k, (long long)gen_strips(k, w) * h, num_cus));
+  const long long n = gen_blocks(k, w, h, gen_rows(k, (long long)gen_strips(k, w) * h, h % 4 == 0, num_cus));
   // a streamed kernel that reduces: groups of eight items' waves, at most two
   // a CU, each going on to further items
   if (k->form != GEN_STREAM || !k->red) return n;

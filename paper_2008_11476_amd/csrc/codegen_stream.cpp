@@ -34,8 +34,8 @@
 namespace hvx {
 namespace {
 
-// Rows per loop iteration, of which bands are a multiple; the next four rows
-// are loaded while four are computed.
+// Rows per loop iteration, of which all bands but the last are a multiple; the
+// next four rows are loaded while four are computed.
 constexpr int kUnroll = 4;
 
 struct Val {
@@ -61,6 +61,7 @@ struct Planner {
   std::string* why;
   Val v[kMaxGVals];
   int E = 0, LP = 8, halo = 0, nred = 0;
+  int T = 0;  // rows at the image's end whose steps know the rows below it: E, up to a multiple of kUnroll
   Text t;
 
   Planner(const GProg& p, uint32_t nt_, std::string* w) : P(p), nt(nt_), why(w) {}
@@ -207,6 +208,7 @@ struct Planner {
       v[i].hi = g.df == DF_U8 ? 255 : (g.df == DF_UYVY ? 65535 : 32767);
     }
     LP = any_wide ? 4 : 8;
+    T = (E + kUnroll - 1) / kUnroll * kUnroll;
     int emax = 0;
     for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
     halo = (emax + LP - 1) / LP;
@@ -505,15 +507,159 @@ struct Planner {
     t("      st.r%d[%d] = n;", i, D - 1);
   }
 
-  // the item `item` of the image: its strip and band, inside the image or not
+  // columns of row n outside the image
+  void emit_fix(int i) {
+    const char* f = "      if constexpr (COL && V == kAny) fix_cols_any<%d, %d>(n, g, (int)0x%08xu);";
+    t(f, v[i].mode, v[i].rx, (uint32_t)v[i].c);
+    t("      else if constexpr (COL) fix_cols<%d, %d>(n, g, (int)0x%08xu);", v[i].mode, v[i].rx, (uint32_t)v[i].c);
+  }
+
+  // the arguments of a step: each input's loaded row, j its number in `name`
+  static std::string raw_args(const std::vector<int>& ins, const char* name, int j) {
+    std::string a;
+    for (int i : ins) a += fmt(", %s%d[%d]", name, i, j);
+    return a;
+  }
+  std::string prologue_args(const std::vector<int>& ins, int s) const {
+    std::string a;
+    for (int i : ins) {
+      const int j = s - (2 * E - 2 * P.vals[i].ext);
+      a += j >= 0 ? fmt(", a%d[%d]", i, j) : fmt(", c%d[0]", i);  // not read before step 2 E - 2 ext
+    }
+    return a;
+  }
+  void emit_strip_setup(const std::vector<int>& ins, bool col_always) {
+    const int nv = P.nvals;
+    t("  const Strip<SX_LP> g = make_strip<SX_LP>(strip, %d, %d, W, H);", halo, 64 - 2 * halo);
+    t("  const int wr = (W + SX_LP - 1) / SX_LP * SX_LP, xl = min(max(g.x0, 0), wr - SX_LP);");
+    t("  uint32_t off[%d];", kMaxIO);
+    for (int i = 0; i < nv; ++i)
+      if (P.vals[i].store && P.vals[i].df != DF_BUF)
+        t("  off[%d] = g.keep ? (uint32_t)(g.x0 * %d) : kNoLane;", P.vals[i].io, df_bytes(P.vals[i].df));
+    for (int i : ins) {
+      const GVal& gv = P.vals[i];
+      const int bpp = df_bytes(gv.df);
+      // row r, from the row of memory its border rule gives; rows from `end`
+      // on are not needed and not read (an empty descriptor)
+      t("  auto ld%d = [&](int r, int end) {", i);
+      t("    const uint32_t n = r < end ? (uint32_t)(wr * %d) : 0u;", bpp);
+      t(col_always ? "    r = src_row<%d>(r, H);" : "    if constexpr (COL) r = src_row<%d>(r, H);",
+        v[i].mode < 0 ? B_REPLICATE : v[i].mode);
+      t("    return row_load<%d>(io.ptr[%d], io.pitch[%d], r, n, (uint32_t)(xl * %d));", raw_bytes(i), gv.io, gv.io, bpp);
+      t("  };");
+    }
+    t("  SxState st = {};");
+  }
+
+  void emit_items(const std::vector<int>& ins) {
+    // One strip of one band: rows [y0, y1), a multiple of kUnroll of them.  COL
+    // false: strip and band lie inside the image.  COL true: any strip of an
+    // image of at least eight columns; the band at the image's top starts with
+    // steps that know the rows above the image, and the last one is the
+    // image's last T rows, whose steps know the rows below it, all at compile
+    // time.
+    t("template <bool COL>");
+    t("__device__ __forceinline__ void sx_item(SxRed& red, const IOTable& io, int W, int H, int strip, int y0, int y1,");
+    t("                                        bool last, int own) {");
+    emit_strip_setup(ins, false);
+    t("  const int rows_end = COL && last ? H + %d : y1;", T);
+    for (int i : ins) {
+      const int e = P.vals[i].ext, nb = raw_bytes(i);
+      if (e) {
+        t("  Raw<%d> a%d[%d];", nb, i, 2 * e);
+        t("#pragma unroll");
+        t("  for (int j = 0; j < %d; ++j) a%d[j] = ld%d(y0 - %d + j, rows_end + %d);", 2 * e, i, i, e, e);
+      }
+      t("  Raw<%d> c%d[%d];", nb, i, kUnroll);
+      t("#pragma unroll");
+      t("  for (int j = 0; j < %d; ++j) c%d[j] = ld%d(y0 + %d + j, rows_end + %d);", kUnroll, i, i, e, e);
+    }
+    if (E > 0) {
+      t("  if (COL && y0 == 0) {");
+      for (int s = 0; s < 2 * E; ++s)
+        t("    if constexpr (COL) sx_step<%d, kTop, COL>(st, red, g, io, off, %d, 0, own%s);", s, s - 2 * E,
+          prologue_args(ins, s).c_str());
+      t("  } else {");
+      for (int s = 0; s < 2 * E; ++s)
+        t("    sx_step<%d, kMid, COL>(st, red, g, io, off, y0 - %d, 0, own%s);", s, 2 * E - s, prologue_args(ins, s).c_str());
+      t("  }");
+    }
+    t("  for (int t = y0; t < y1; t += %d) {", kUnroll);
+    for (int i : ins) {
+      t("    Raw<%d> n%d[%d];", raw_bytes(i), i, kUnroll);
+      t("#pragma unroll");
+      t("    for (int j = 0; j < %d; ++j) n%d[j] = ld%d(t + %d + j, y1 + %d);", kUnroll, i, i, kUnroll + P.vals[i].ext,
+        P.vals[i].ext);
+    }
+    for (int j = 0; j < kUnroll; ++j)
+      t("    sx_step<%d, kMid, COL>(st, red, g, io, off, t + %d, 0, own%s);", 2 * E, j, raw_args(ins, "c", j).c_str());
+    for (int i : ins) {
+      t("#pragma unroll");
+      t("    for (int j = 0; j < %d; ++j) c%d[j] = n%d[j];", kUnroll, i, i);
+    }
+    t("  }");
+    if (T > 0) {
+      t("  if constexpr (COL) {");
+      t("    if (last) {");
+      for (int i : ins) {
+        if (T <= kUnroll) continue;
+        t("      Raw<%d> b%d[%d];", raw_bytes(i), i, T - kUnroll);
+        t("#pragma unroll");
+        t("      for (int j = 0; j < %d; ++j) b%d[j] = ld%d(H - %d + j, H + %d);", T - kUnroll, i, i,
+          T - kUnroll - P.vals[i].ext, T);
+      }
+      for (int j = 0; j < T; ++j)
+        t("      sx_step<%d, kTail, COL>(st, red, g, io, off, H - %d, 0, H%s);", 2 * E + 1 + j, T - j,
+          raw_args(ins, j < kUnroll ? "c" : "b", j < kUnroll ? j : j - kUnroll).c_str());
+      t("    }");
+      t("  }");
+    }
+    t("}");
+    // any size: row by row, every rule decided as it goes
+    t("__device__ __forceinline__ void sx_small(SxRed& red, const IOTable& io, int W, int H, int strip) {");
+    emit_strip_setup(ins, true);
+    t("  for (int t = -%d; t < H; ++t) {", 2 * E);
+    std::string a;
+    for (int i : ins) {
+      t("    const Raw<%d> x%d = ld%d(t + %d, H + %d);", raw_bytes(i), i, i, P.vals[i].ext, 2 * E + 1);
+      a += fmt(", x%d", i);
+    }
+    t("    sx_step<%d, kAny, true>(st, red, g, io, off, t, 0, H%s);", 2 * E, a.c_str());
+    t("  }");
+    t("}");
+  }
+
+  // the item `item` of the image: its strip and band
   void emit_item() {
     const int out_lanes = 64 - 2 * halo;
-    t("  const int strip = item %% strips, y0 = item / strips * rows, y1 = min(y0 + rows, H);");
-    // inside the image: every pixel of every lane, and every row the band reads
-    t("  const bool inside = strip > 0 && (strip * %d + %d) * SX_LP <= W && y0 >= %d && y0 + rows + %d <= H;", out_lanes,
-      out_lanes + halo, E, E);
-    t("  if (inside) sx_item<false>(red, io, W, H, strip, y0, y1);");
-    t("  else sx_item<true>(red, io, W, H, strip, y0, y1);");
+    t("  const int strip = item %% strips, band = item / strips;");
+    if (T > 0) {
+      t("  const bool last = band + 1 == bands;");
+      t("  const int y0 = last ? H - %d : band > 0 ? band * rows - shift : 0, y1 = last ? y0 : min(y0 + rows, H - %d);", T, T);
+    } else {
+      t("  const bool last = false;");
+      t("  const int y0 = band > 0 ? band * rows - shift : 0, y1 = min(y0 + rows, H);");
+    }
+    // inside the image: every pixel of every lane, every row the band reads
+    t("  if (bands > 1 && strip > 0 && (strip * %d + %d) * SX_LP <= W && band > 0 && !last)", out_lanes,
+      out_lanes + halo);
+    t("    sx_item<false>(red, io, W, H, strip, y0, y1, false, y1);");
+    t("  else if (bands > 1 && W >= 8)");
+    t("    sx_item<true>(red, io, W, H, strip, y0, y1, last, band > 0 ? y1 : rows - shift);");
+    t("  else if (band == 0) sx_small(red, io, W, H, strip);");
+  }
+
+  // The image's last T rows are a band of their own; the rows before them, up
+  // to a multiple of kUnroll by `shift`, are dealt out in bands of `rows`.  All
+  // bands but the first start `shift` rows early, so each holds a multiple of
+  // kUnroll rows; the first still starts at row 0 and computes the `shift`
+  // rows it shares with the second again.  `rows` is at least E + shift: only
+  // the first band reads rows above the image, only the last below it.  Images
+  // of a single band, or under eight columns, go row by row.
+  void emit_geometry(int strip_px) {
+    t("  const int strips = (W + %d) / %d;", strip_px - 1, strip_px);
+    t("  const int shift = (%d - H) & %d, main_rows = H - %d + shift;", T, kUnroll - 1, T);
+    t("  const int bands = H < %d ? 1 : (main_rows + rows - 1) / rows%s;", T + 2 * kUnroll, T > 0 ? " + 1" : "");
   }
 
   void emit_entry() {
@@ -540,8 +686,8 @@ struct Planner {
     t("    item -= imgs[i].block0;");
     t("  }");
     const int strip_px = (64 - 2 * halo) * LP;
-    t("  const int strips = (W + %d) / %d;", strip_px - 1, strip_px);
-    t("  if (item / strips * rows >= H) return;");
+    emit_geometry(strip_px);
+    t("  if (item >= strips * bands) return;");
     t("  SxRed red;");
     emit_item();
     t("}");
@@ -577,7 +723,8 @@ struct Planner {
     t("  const int vb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + b / 8;");
     t("  const int W = P->w, H = P->h;");
     const int strip_px = (64 - 2 * halo) * LP;
-    t("  const int strips = (W + %d) / %d, items = strips * ((H + rows - 1) / rows);", strip_px - 1, strip_px);
+    emit_geometry(strip_px);
+    t("  const int items = strips * bands;");
     t("  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));");
     t("  for (int item = vb * %d + wave; item < items; item += nb * %d) {", NT / 64, NT / 64);
     emit_item();
@@ -629,22 +776,28 @@ struct Planner {
         ins.push_back(i);
         args += fmt(", const Raw<%d>& x%d", raw_bytes(i), i);
       }
-    // step S of a band (0 .. 2 E - 1 before its first output row, then 2 E):
-    // the outputs' row is t; EDGE: the strip or band touches the image's border
-    t("template <int S, bool EDGE>");
-    t("__device__ __forceinline__ void sx_step(SxState& st, SxRed& red, const Strip& g, const IOTable& io,");
-    t("                                        const uint32_t (&off)[%d], int t%s) {", kMaxIO, args.c_str());
+    // Step S of a band (0 .. 2 E - 1 before its first output row, then 2 E);
+    // the outputs' row is t.  V says what is known of the rows: kMid, all lie
+    // inside the image; kTop, the band starts at row 0 (t = S - 2 E); kTail,
+    // step 2 E + 1 + j is the output row H - T + j; kAny, nothing.  COL: the
+    // strip lies at the image's left or right edge.  Rows from `own` on are
+    // another band's to count.
+    t("enum { kMid, kTop, kTail, kAny };");
+    t("template <int S, int V, bool COL>");
+    t("__device__ __forceinline__ void sx_step(SxState& st, SxRed& red, const Strip<SX_LP>& g, const IOTable& io,");
+    t("                                        const uint32_t (&off)[%d], int t, int first, int own%s) {", kMaxIO, args.c_str());
+    t("  constexpr int from_top = S - %d, from_end = S - %d;  // t, t - H where they are known", 2 * E, 2 * E + 1 + T);
     for (int i : ins) {
       const GVal& gv = P.vals[i];
       t("  if constexpr (S >= %d) {  // input %d, row t + %d", 2 * E - 2 * gv.ext, i, gv.ext);
       if (v[i].wide) t("      %s n = unpack_wd<SX_LP>(x%d);", row_type(i).c_str(), i);
       else t("      %s n = unpack_pk<%d, SX_LP>(x%d);", row_type(i).c_str(), gv.df, i);
-      if (v[i].mode >= 0) {
-        t("      if constexpr (EDGE) {");
-        t("        fix_cols<%d, %d>(n, g, (int)0x%08xu);", v[i].mode, v[i].rx, (uint32_t)v[i].c);
-        if (v[i].mode == B_CONSTANT)
-          t("        if (t + %d < 0 || t + %d >= g.H) fill(n, (int)0x%08xu);", gv.ext, gv.ext, (uint32_t)v[i].c);
-        t("      }");
+      if (v[i].mode >= 0) emit_fix(i);
+      if (v[i].mode == B_CONSTANT) {
+        t("      const int r = t + %d;", gv.ext);
+        t("      if (V == kTop ? from_top + %d < 0 : V == kTail ? from_end + %d >= 0 : V == kAny && (r < 0 || r >= g.H))",
+          gv.ext, gv.ext);
+        t("        fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
       }
       emit_push(i);
       t("  }");
@@ -653,63 +806,75 @@ struct Planner {
       const int i = P.ops[k].out;
       const GVal& gv = P.vals[i];
       if (is_reduce_op(P.ops[k].kind)) continue;
-      const bool bord = v[i].mode >= 0;
       const int D = v[i].depth;
+      // rows outside the image that no operator reads are left as they are
       t("  if constexpr (S >= %d) {  // value %d, row t + %d", 2 * E - 2 * gv.ext, i, gv.ext);
       t("    %s n;", row_type(i).c_str());
-      if (bord) {
-        t("    const int r = t + %d;", gv.ext);
-        t("    if (!EDGE || (r >= 0 && r < g.H)) {");
+      t("    const int r = t + %d;", gv.ext);
+      t("    constexpr bool above = V == kTop && from_top + %d < 0, below = V == kTail && from_end + %d >= 0;", gv.ext,
+        gv.ext);
+      t("    if constexpr (above || below) {");
+      if (v[i].mode == B_CONSTANT) {
+        t("      fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
+      } else if (v[i].mode == B_MIRROR) {
+        // r - H = 0: two rows back; 1: four
+        const int two = std::max(0, D - 2), four = std::max(0, D - 4);
+        t("      n = st.r%d[from_end + %d <= 0 ? %d : %d];", i, gv.ext, two, four);
       } else {
-        t("    {");
+        t("      n = st.r%d[%d];", i, D - 1);  // above the image: set when row 0 is known
       }
+      t("    } else if (V != kAny || (r >= 0 && r < g.H)) {");
       if (!emit_op(k)) return false;
-      if (bord) {
-        t("      if constexpr (EDGE) fix_cols<%d, %d>(n, g, (int)0x%08xu);", v[i].mode, v[i].rx, (uint32_t)v[i].c);
-        t("    } else {");
-        if (v[i].mode == B_CONSTANT) {
-          t("      fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
-        } else if (v[i].mode == B_REPLICATE) {
-          t("      n = st.r%d[%d];", i, D - 1);  // above the image: set when row 0 is known
-        } else {
-          // 1, 2 or 4 rows back
-          t("      const int d = r - mirror_near(r, g.H);");
-          t("      n = st.r%d[%d];", i, D - 1);
-          if (D >= 2) t("      if (d == 2) n = st.r%d[%d];", i, D - 2);
-          if (D >= 4) t("      if (d == 4) n = st.r%d[%d];", i, D - 4);
-        }
+      if (v[i].mode >= 0) emit_fix(i);
+      t("    } else {");
+      if (v[i].mode == B_CONSTANT) {
+        t("      fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
+      } else if (v[i].mode == B_MIRROR) {
+        // 1, 2 or 4 rows back
+        t("      const int d = r - mirror_near(r, g.H);");
+        t("      n = st.r%d[%d];", i, D - 1);
+        if (D >= 2) t("      if (d == 2) n = st.r%d[%d];", i, D - 2);
+        if (D >= 4) t("      if (d == 4) n = st.r%d[%d];", i, D - 4);
+      } else {
+        t("      n = st.r%d[%d];", i, D - 1);
       }
       t("    }");
       emit_push(i);
-      if (bord && v[i].mode != B_CONSTANT && D > 1) {
-        t("    if constexpr (EDGE) {");
+      if ((v[i].mode == B_MIRROR || v[i].mode == B_REPLICATE) && D > 1) {
+        // rows above the image, once the rows they repeat are known
+        auto set = [&](const std::string& top, const std::string& any, int back) {
+          if (back < D)
+            t("    if ((V == kTop && %s) || (V == kAny && %s)) st.r%d[%d] = st.r%d[%d];", top.c_str(), any.c_str(), i,
+              D - 1 - back, i, D - 1);
+        };
+        const std::string tr = fmt("from_top + %d", gv.ext);
         if (v[i].mode == B_REPLICATE) {
-          t("      if (r == 0) {");
-          for (int j = 0; j < D - 1; ++j) t("        st.r%d[%d] = st.r%d[%d];", i, j, i, D - 1);
-          t("      }");
+          for (int j = 1; j < D; ++j) set(tr + " == 0", "r == 0", j);
         } else {
-          // row -1 reads row 1, row -2 row 2; images of one or two rows repeat
-          auto set = [&](const char* when, int back) {
-            if (back < D) t("      if (%s) st.r%d[%d] = st.r%d[%d];", when, i, D - 1 - back, i, D - 1);
+          // row -1 reads row 1, row -2 row 2 (at the latest in the step of the
+          // first output row); images of one or two rows repeat
+          auto mirror = [&](int j, int back) {
+            set(tr + fmt(" == %d", j), fmt("r == %d", j), back);
+            if (gv.ext == j && back < D)
+              t("    if (COL && V == kMid && t == 0) st.r%d[%d] = st.r%d[%d];", i, D - 1 - back, i, D - 1);
           };
           if (v[i].ry >= 1) {
-            set("r == 0 && g.H == 1", 1);
-            set("r == 1", 2);
+            set("false", "r == 0 && g.H == 1", 1);
+            mirror(1, 2);
           }
           if (v[i].ry >= 2) {
-            set("r == 0 && g.H <= 2", 2);
-            set("r == 2", 4);
+            set("false", "r == 0 && g.H <= 2", 2);
+            mirror(2, 4);
           }
         }
-        t("    }");
       }
       t("  }");
     }
-    t("  if constexpr (S == %d) {", 2 * E);
+    t("  if (S >= %d && (V != kAny || t >= first)) {", 2 * E);
     for (int i = 0; i < nv; ++i) {
       const GVal& gv = P.vals[i];
       if (!gv.store || gv.df == DF_BUF) continue;
-      t("    emit_row<%d, SX_LP, EDGE, %s>(st.r%d[%d], io.ptr[%d], io.pitch[%d], t, g, off[%d]);", gv.df,
+      t("    emit_row<%d, SX_LP, COL, %s>(st.r%d[%d], io.ptr[%d], io.pitch[%d], t, g, off[%d]);", gv.df,
         (nt >> i) & 1 ? "true" : "false", i, v[i].depth - 1 - gv.ext, gv.io, gv.io, gv.io);
     }
     for (int k = 0; k < P.nops; ++k) {
@@ -721,64 +886,12 @@ struct Planner {
                         : o.kind == OP_MMCOUNT
                             ? fmt("mmcount_add(red.q%d, v, in)", k)
                             : fmt("hist_add<%d, %d, %d>(red.hist, v, in)", o.p0, o.p1, o.p2);
-      t("    own_pixels<EDGE>(st.r%d[%d], g, t, [&](int v, bool in) { %s; });", in, v[in].depth - 1 - P.vals[in].ext,
+      t("    if (!COL || t < own) own_pixels<COL>(st.r%d[%d], g, [&](int v, bool in) { %s; });", in, v[in].depth - 1 - P.vals[in].ext,
         add.c_str());
     }
     t("  }");
     t("}");
-    // one strip of one band
-    const int out_lanes = 64 - 2 * halo;
-    t("template <bool EDGE>");
-    t("__device__ __forceinline__ void sx_item(SxRed& red, const IOTable& io, int W, int H, int strip, int y0, int y1) {");
-    t("  const Strip g = make_strip<SX_LP>(strip, %d, %d, W, H);", halo, out_lanes);
-    t("  const int wr = (W + SX_LP - 1) / SX_LP * SX_LP, xl = min(max(g.x0, 0), wr - SX_LP);");
-    t("  uint32_t off[%d];", kMaxIO);
-    for (int i = 0; i < nv; ++i)
-      if (P.vals[i].store && P.vals[i].df != DF_BUF) t("  off[%d] = g.keep ? (uint32_t)(g.x0 * %d) : kNoLane;", P.vals[i].io, df_bytes(P.vals[i].df));
-    for (int i : ins) {
-      const GVal& gv = P.vals[i];
-      const int bpp = df_bytes(gv.df), nb = raw_bytes(i);
-      // rows past the last one the band needs are not read (an empty descriptor)
-      t("  auto ld%d = [&](int r) {", i);
-      t("    const uint32_t n = r < y1 + %d ? (uint32_t)(wr * %d) : 0u;", gv.ext, bpp);
-      t("    if constexpr (EDGE) r = src_row<%d>(r, H);", v[i].mode < 0 ? B_REPLICATE : v[i].mode);
-      t("    return row_load<%d>(io.ptr[%d], io.pitch[%d], r, n, (uint32_t)(xl * %d));", nb, gv.io, gv.io, bpp);
-      t("  };");
-      if (gv.ext) {
-        t("  Raw<%d> a%d[%d];", nb, i, 2 * gv.ext);
-        t("#pragma unroll");
-        t("  for (int j = 0; j < %d; ++j) a%d[j] = ld%d(y0 - %d + j);", 2 * gv.ext, i, i, gv.ext);
-      }
-      t("  Raw<%d> c%d[%d];", nb, i, kUnroll);
-      t("#pragma unroll");
-      t("  for (int j = 0; j < %d; ++j) c%d[j] = ld%d(y0 + %d + j);", kUnroll, i, i, gv.ext);
-    }
-    t("  SxState st = {};");
-    for (int s = 0; s < 2 * E; ++s) {
-      std::string a;
-      for (int i : ins) {
-        const int j = s - (2 * E - 2 * P.vals[i].ext);
-        a += j >= 0 ? fmt(", a%d[%d]", i, j) : fmt(", c%d[0]", i);  // not read before step 2 E - 2 ext
-      }
-      t("  sx_step<%d, EDGE>(st, red, g, io, off, y0 - %d%s);", s, 2 * E - s, a.c_str());
-    }
-    t("  for (int t = y0; t < y1; t += %d) {", kUnroll);
-    for (int i : ins) {
-      t("    Raw<%d> n%d[%d];", raw_bytes(i), i, kUnroll);
-      t("#pragma unroll");
-      t("    for (int j = 0; j < %d; ++j) n%d[j] = ld%d(t + %d + j);", kUnroll, i, i, kUnroll + P.vals[i].ext);
-    }
-    for (int j = 0; j < kUnroll; ++j) {
-      std::string a;
-      for (int i : ins) a += fmt(", c%d[%d]", i, j);
-      t("    sx_step<%d, EDGE>(st, red, g, io, off, t + %d%s);", 2 * E, j, a.c_str());
-    }
-    for (int i : ins) {
-      t("#pragma unroll");
-      t("    for (int j = 0; j < %d; ++j) c%d[j] = n%d[j];", kUnroll, i, i);
-    }
-    t("  }");
-    t("}");
+    emit_items(ins);
     t("}  // namespace hvx");
     if (nred) emit_reducing_entry();
     else emit_entry();

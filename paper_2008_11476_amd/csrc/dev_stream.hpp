@@ -51,7 +51,9 @@ __device__ __forceinline__ uint32_t pk_mad(uint32_t e, uint32_t acc) {
     asm("v_pk_mad_u16 %0, %1, %3, %2" : "=v"(r) : "v"(e), "v"(acc), "s"(pk_c(C)));
   return r;
 }
-__device__ __forceinline__ uint32_t bit_sel(uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); }
+__device__ __forceinline__ uint32_t bit_sel(uint32_t m, uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_bitop3_b32(m, a, b, 0xCA);
+}
 // all ones in the halves whose element is negative
 __device__ __forceinline__ uint32_t pk_neg_mask(uint32_t a) { return pk_sar(a, 15); }
 // a / 2^s toward zero (signed)
@@ -201,9 +203,7 @@ __device__ __forceinline__ Raw<NB> row_load(const void* base, int64_t pitch, int
 }
 // AUX 2: non-temporal
 template <int NB, int AUX>
-__device__ __forceinline__ void row_store(const Raw<NB>& x, void* base, int64_t pitch, int row, uint32_t bytes,
-                                          uint32_t off) {
-  const __amdgpu_buffer_rsrc_t r = row_rsrc(base, pitch, row, bytes);
+__device__ __forceinline__ void row_store(const Raw<NB>& x, __amdgpu_buffer_rsrc_t r, uint32_t off) {
   if constexpr (NB == 4) {
     __builtin_amdgcn_raw_buffer_store_b32(x.d[0], r, off, 0, AUX);
   } else if constexpr (NB == 8) {
@@ -271,18 +271,22 @@ __device__ __forceinline__ Raw<LP * 4> pack_row(const WR<LP>& w) {
 }
 
 // ---- the strip, and positions outside the image --------------------------------------
+template <int LP>
 struct Strip {
   int x0;        // first pixel of the lane
   int W, H;
   int zl;        // lane holding x = 0, or -1
   int rl, rq;    // lane and pixel within it holding x = W - 1 (the lane may lie outside the wave)
   bool left;     // the lane lies left of the image
+  bool whole;    // x = W - 1 ends a lane (uniform)
+  uint32_t ml;   // the high half in the lane just left of x = 0
+  uint32_t mr[2][LP / 2];  // pairs' pixels from W, and from W + 1 on
   bool keep;     // the lane stores all its pixels
   bool ragged;   // the lane stores the first W - x0 of its pixels
 };
 template <int LP>
-__device__ __forceinline__ Strip make_strip(int strip, int halo, int out_lanes, int W, int H) {
-  Strip s;
+__device__ __forceinline__ Strip<LP> make_strip(int strip, int halo, int out_lanes, int W, int H) {
+  Strip<LP> s;
   const int lane = (int)(threadIdx.x & 63);
   const int base = (strip * out_lanes - halo) * LP;  // the first lane's first pixel (may be negative)
   s.x0 = base + lane * LP;
@@ -292,6 +296,13 @@ __device__ __forceinline__ Strip make_strip(int strip, int halo, int out_lanes, 
   s.rl = (W - 1 - base) / LP;
   s.rq = (W - 1) % LP;
   s.left = s.x0 < 0;
+  s.ml = s.x0 == -LP ? 0xFFFF0000u : 0u;
+#pragma unroll
+  for (int k = 0; k < LP / 2; ++k)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      s.mr[j][k] = (s.x0 + k >= W + j ? 0xFFFFu : 0u) | (s.x0 + k + LP / 2 >= W + j ? 0xFFFF0000u : 0u);
+  s.whole = W % LP == 0;
   const bool own = lane >= halo && lane < halo + out_lanes && s.x0 < W;
   s.keep = own && s.x0 + LP <= W;
   s.ragged = own && s.x0 + LP > W;
@@ -338,31 +349,87 @@ __device__ __forceinline__ int mirror_near(int x, int n) {
 
 // Columns outside the image take the border rule MODE of the operators that
 // read the value (R: their largest horizontal radius; R = 0: none).  Only
-// the strips at the image's left and right edge hold such columns.
+// the strips at the image's left and right edge hold such columns.  On the
+// left the R pixels beside the image lie in one lane and come from the next
+// by a lane shift; on the right the pixel they repeat may lie anywhere in
+// its lane and is read into a scalar.  No branches: they would cost more than
+// the few instructions, in registers moved where they join.
+template <int R, int LP>
+__device__ __forceinline__ void put_right(PR<LP>& p, const Strip<LP>& s, const int (&v)[R]) {
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+#pragma unroll
+    for (int k = 0; k < LP / 2; ++k) p.v[k] = bit_sel(s.mr[j][k], pk_c(v[j]), p.v[k]);
+}
+template <int R, int LP>
+__device__ __forceinline__ void put_right(WR<LP>& p, const Strip<LP>& s, const int (&v)[R]) {
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+#pragma unroll
+    for (int k = 0; k < LP; ++k) p.v[k] = s.x0 + k >= s.W + j ? v[j] : p.v[k];
+}
 template <int MODE, int R, template <int> class ROW, int LP>
-__device__ __forceinline__ void fix_cols(ROW<LP>& p, const Strip& s, int c) {
-  if constexpr (R > 0) {
-    const int x0 = s.x0, W = s.W;
-    if constexpr (MODE == B_CONSTANT) {
-      put_where(p, c, [&](int q) { return s.left || x0 + q >= W; });
-    } else if constexpr (MODE == B_MIRROR) {
-      int lv[R], rv[R];
+__device__ __forceinline__ void fix_right(ROW<LP>& p, const Strip<LP>& s, int c) {
+  if constexpr (MODE == B_MIRROR) {
+    int v[R];
 #pragma unroll
-      for (int j = 1; j <= R; ++j) {
-        const int l = mirror_near(-j, W), r = s.rl * LP + s.rq - (W - 1 - mirror_near(W - 1 + j, W));
-        lv[j - 1] = strip_px(p, max(s.zl, 0) + l / LP, l % LP);
-        rv[j - 1] = strip_px(p, r / LP, r % LP);
-      }
-#pragma unroll
-      for (int j = 1; j <= R; ++j) {
-        put_where(p, lv[j - 1], [&](int q) { return x0 + q == -j; });
-        put_where(p, rv[j - 1], [&](int q) { return x0 + q == W - 1 + j; });
-      }
-    } else {
-      const int lv = strip_px(p, max(s.zl, 0), 0), rv = strip_px(p, s.rl, s.rq);
-      put_where(p, lv, [&](int) { return s.left; });
-      put_where(p, rv, [&](int q) { return x0 + q >= W; });
+    for (int j = 1; j <= R; ++j) {
+      const int r = s.rl * LP + s.rq - (s.W - 1 - mirror_near(s.W - 1 + j, s.W));
+      v[j - 1] = strip_px(p, r / LP, r % LP);
     }
+    put_right(p, s, v);
+  } else {
+    const int v[1] = {MODE == B_CONSTANT ? c : strip_px(p, s.rl, s.rq)};
+    put_right(p, s, v);
+  }
+}
+// any width
+template <int MODE, int R, template <int> class ROW, int LP>
+__device__ __forceinline__ void fix_cols_any(ROW<LP>& p, const Strip<LP>& s, int c) {
+  if constexpr (R > 0) {
+    const int x0 = s.x0;
+    int lv[R];
+#pragma unroll
+    for (int j = 1; j <= R; ++j) {
+      const int l = MODE == B_MIRROR ? mirror_near(-j, s.W) : 0;
+      lv[j - 1] = MODE == B_CONSTANT ? c : strip_px(p, max(s.zl, 0) + l / LP, l % LP);
+    }
+    fix_right<MODE, R>(p, s, c);
+#pragma unroll
+    for (int j = 1; j <= R; ++j) put_where(p, lv[j - 1], [&](int q) { return x0 + q == -j; });
+  }
+}
+// images of at least eight columns
+template <int MODE, int R, int LP>
+__device__ __forceinline__ void fix_cols(PR<LP>& p, const Strip<LP>& s, int c) {
+  if constexpr (R > 0) {
+    constexpr int H = LP / 2;
+    uint32_t v[R];
+#pragma unroll
+    for (int j = 1; j <= R; ++j) {  // pixel -j: the high half of pair H - j
+      v[j - 1] = pk_c(c);
+      if constexpr (MODE == B_MIRROR) {
+        v[j - 1] = lane_right(p.v[j % H]);
+        if (j < H) v[j - 1] <<= 16;
+      } else if constexpr (MODE != B_CONSTANT) {
+        v[j - 1] = lane_right(p.v[0]) << 16;
+      }
+    }
+    fix_right<MODE, R>(p, s, c);
+#pragma unroll
+    for (int j = 1; j <= R; ++j) p.v[H - j] = bit_sel(s.ml, v[j - 1], p.v[H - j]);
+  }
+}
+template <int MODE, int R, int LP>
+__device__ __forceinline__ void fix_cols(WR<LP>& p, const Strip<LP>& s, int c) {
+  if constexpr (R > 0) {
+    int v[R];
+#pragma unroll
+    for (int j = 1; j <= R; ++j)
+      v[j - 1] = MODE == B_CONSTANT ? c : (int)lane_right((uint32_t)p.v[MODE == B_MIRROR ? j : 0]);
+    fix_right<MODE, R>(p, s, c);
+#pragma unroll
+    for (int j = 1; j <= R; ++j) p.v[LP - j] = s.ml ? v[j - 1] : p.v[LP - j];
   }
 }
 
@@ -373,28 +440,52 @@ __device__ __forceinline__ int src_row(int r, int H) {
   return min(max(r, 0), H - 1);
 }
 
-// Stores row `row` of a value.  EDGE: the item touches the image's border;
-// rows past the image are dropped, and the lane that holds W - 1 amid its
-// pixels stores them one by one.
-template <int DF, int LP, bool EDGE, bool NT, class ROW>
-__device__ __forceinline__ void emit_row(const ROW& p, void* base, int64_t pitch, int row, const Strip& s, uint32_t off) {
-  constexpr int BPP = DF == DF_U8 ? 1 : (DF == DF_S16 ? 2 : 4);
-  const Raw<LP * BPP> x = pack_row<DF, LP>(p);
-  uint32_t bytes = (uint32_t)(s.W * BPP);
-  if (EDGE && row >= s.H) bytes = 0;
-  row_store<LP * BPP, NT ? 2 : 0>(x, base, pitch, row, bytes, off);
-  if constexpr (EDGE) {
-    if (row < s.H && s.ragged) {
-      uint8_t* r = (uint8_t*)base + (size_t)row * pitch + (size_t)s.x0 * BPP;
-      const int n = s.W - s.x0;
+// Stores row `row` of a value.  COL: the strip lies at the image's left or
+// right edge; of the lane that holds W - 1 amid its pixels the bytes up to it
+// are stored, in pieces of 16, 8, 4, 2 and 1 by the bits of their (uniform)
+// number.
+template <int DF, int LP, bool COL, bool NT, class ROW>
+__device__ __forceinline__ void emit_row(const ROW& p, void* base, int64_t pitch, int row, const Strip<LP>& s, uint32_t off) {
+  constexpr int BPP = DF == DF_U8 ? 1 : (DF == DF_S16 ? 2 : 4), NB = LP * BPP, AUX = NT ? 2 : 0;
+  Raw<NB> x = pack_row<DF, LP>(p);
+  const __amdgpu_buffer_rsrc_t r = row_rsrc(base, pitch, row, (uint32_t)(s.W * BPP));
+  row_store<NB, AUX>(x, r, off);
+  if constexpr (COL) {
+    if (!s.whole) {
+      const int n = (s.rq + 1) * BPP;
+      uint32_t o = s.ragged ? (uint32_t)(s.x0 * BPP) : kNoLane;
+      if constexpr (NB > 16) {
+        if (n & 16) {
+          __builtin_amdgcn_raw_buffer_store_b128(v4w{x.d[0], x.d[1], x.d[2], x.d[3]}, r, o, 0, AUX);
+          o += 16;
 #pragma unroll
-      for (int q = 0; q < LP - 1; ++q)
-        if (q < n) {
-          const uint32_t w = x.d[q * BPP / 4] >> (q * BPP % 4 * 8);
-          if constexpr (BPP == 1) r[q] = (uint8_t)w;
-          else if constexpr (BPP == 2) ((uint16_t*)r)[q] = (uint16_t)w;
-          else ((uint32_t*)r)[q] = w;
+          for (int i = 0; i + 4 < NB / 4; ++i) x.d[i] = x.d[i + 4];
         }
+      }
+      if constexpr (NB > 8) {
+        if (n & 8) {
+          __builtin_amdgcn_raw_buffer_store_b64(v2w{x.d[0], x.d[1]}, r, o, 0, AUX);
+          o += 8;
+#pragma unroll
+          for (int i = 0; i + 2 < NB / 4; ++i) x.d[i] = x.d[i + 2];
+        }
+      }
+      if constexpr (NB > 4) {
+        if (n & 4) {
+          __builtin_amdgcn_raw_buffer_store_b32(x.d[0], r, o, 0, AUX);
+          o += 4;
+          x.d[0] = x.d[1];
+        }
+      }
+      if constexpr (BPP <= 2) {
+        if (n & 2) {
+          __builtin_amdgcn_raw_buffer_store_b16((uint16_t)x.d[0], r, o, 0, AUX);
+          o += 2;
+          x.d[0] >>= 16;
+        }
+      }
+      if constexpr (BPP == 1)
+        if (n & 1) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)x.d[0], r, o, 0, AUX);
     }
   }
 }
@@ -605,14 +696,14 @@ __device__ __forceinline__ WR<LP> row_box5f(const WR<LP>& a, const WR<LP>& b, co
 // extremes over its items; the group writes them to its slot at the end.
 constexpr int kStreamHistCopies = 16;
 
-// Calls f(element, counted) for the lane's pixels of row t it owns.
-template <bool EDGE, int LP, class F>
-__device__ __forceinline__ void own_pixels(const PR<LP>& p, const Strip& s, int t, F&& f) {
-  if (!(s.keep || (EDGE && s.ragged)) || (EDGE && t >= s.H)) return;
+// Calls f(element, counted) for the pixels of a row that the lane owns.
+template <bool COL, int LP, class F>
+__device__ __forceinline__ void own_pixels(const PR<LP>& p, const Strip<LP>& s, F&& f) {
+  if (!(s.keep || (COL && s.ragged))) return;
 #pragma unroll
   for (int k = 0; k < LP / 2; ++k) {
-    f((int)(int16_t)(uint16_t)p.v[k], !EDGE || s.x0 + k < s.W);
-    f((int)p.v[k] >> 16, !EDGE || s.x0 + k + LP / 2 < s.W);
+    f((int)(int16_t)(uint16_t)p.v[k], !COL || s.x0 + k < s.W);
+    f((int)p.v[k] >> 16, !COL || s.x0 + k + LP / 2 < s.W);
   }
 }
 // (value - OFF) * BINS / RANGE for values of [OFF, OFF + RANGE)

@@ -553,9 +553,11 @@ static hvx_status batch_build(Batch* b) {
         Batch::GenSet set;
         set.k = kv.first[stage];
         long long strip_rows = 0;
+        bool whole_heights = true;
         for (Graph* g : kv.second) {
           const GProg& P = g->plan->groups[stage].prog;
           strip_rows += (long long)gen_strips(set.k, P.w) * P.h;
+          whole_heights &= P.h % 4 == 0;
         }
         for (Graph* g : kv.second) {
           const Group& gr = g->plan->groups[stage];
@@ -566,7 +568,7 @@ static hvx_status batch_build(Batch* b) {
           im.w = gr.prog.w;
           im.h = gr.prog.h;
           im.block0 = (int32_t)set.blocks;
-          im.rows = gen_rows(set.k, strip_rows, c->num_cus);
+          im.rows = gen_rows(set.k, strip_rows, whole_heights, c->num_cus);
           set.blocks += gen_blocks(set.k, gr.prog.w, gr.prog.h, im.rows);
           if (set.blocks > 0x7FFFFFFF) return set_error(c, HVX_ERROR_NOT_SUPPORTED, "batch launch too large");
           set.imgs.push_back(im);
