@@ -975,7 +975,8 @@ struct GenKernel {
 namespace {
 std::mutex g_cache_mu;
 // never freed: code objects stay loaded until the process ends
-std::map<std::string, GenKernel*>* g_cache = new std::map<std::string, GenKernel*>();
+std::map<std::string, GenKernel*>* g_cache = new std::map<std::string, GenKernel*>();  // by source text
+std::map<std::string, GenKernel*>* g_by_program = new std::map<std::string, GenKernel*>();
 }  // namespace
 
 bool gen_wanted(const GProg& P) {
@@ -990,7 +991,8 @@ bool gen_wanted(const GProg& P) {
          (in_df != DF_U8 && in_df != DF_F32);
 }
 
-bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out, std::string* why) {
+// The source of a program's kernel (see gen_kernel).
+static bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out, std::string* why) {
   bool any_local = false, any_red = false;
   for (int k = 0; k < P.nops; ++k) {
     const int kind = P.ops[k].kind;
@@ -1025,8 +1027,8 @@ bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out,
   return true;
 }
 
-const GenKernel* gen_compile(const GenSource& src, std::string* why) {
-  std::lock_guard<std::mutex> l(g_cache_mu);
+// Compile the kernel for `src`, or find it by its text (g_cache_mu is held).
+static GenKernel* gen_compile(const GenSource& src, std::string* why) {
   const bool stream = src.form == GEN_STREAM;
   const std::string key = (stream ? "stream " : "") + src.text;
   auto it = g_cache->find(key);
@@ -1072,6 +1074,29 @@ const GenKernel* gen_compile(const GenSource& src, std::string* why) {
   k->lds_words = src.lds_words;
   (*g_cache)[key] = k;
   return k;
+}
+
+const GenKernel* gen_kernel(const GProg& P, int tw, int th, uint32_t stream, std::string* why) {
+  // Writing the source takes longer than the rest of a verification, so a
+  // kernel is found by the program itself first.
+  GProg q;
+  memcpy(&q, &P, sizeof q);
+  q.w = q.h = q.tiles_x = q.tiles_y = 0;
+  std::string key((const char*)&q, sizeof q);
+  for (const uint32_t x : {(uint32_t)tw, (uint32_t)th, stream}) key.append((const char*)&x, sizeof x);
+  std::lock_guard<std::mutex> l(g_cache_mu);
+  auto it = g_by_program->find(key);
+  if (it != g_by_program->end()) return it->second;
+  GenSource src;
+  if (!gen_source(P, tw, th, stream, &src, why)) return nullptr;
+  GenKernel* k = gen_compile(src, why);
+  if (k) (*g_by_program)[key] = k;
+  return k;
+}
+
+void gen_tile(const GenKernel* k, int* tw, int* th) {
+  *tw = k->tw;
+  *th = k->th;
 }
 
 hipError_t gen_load(const GenKernel* kc, int device) {

@@ -32,15 +32,6 @@ enum GenForm : int32_t {
   GEN_STREAM = 3,  // a wave streams a strip of columns down a band of rows, values in registers
 };
 
-struct GenSource {
-  std::string text;
-  int form = 0;
-  int tw = 0, th = 0;  // output tile (GEN_TILES); columns of a strip, and what a band's rows are a multiple of (GEN_STREAM)
-  int ext = 0;         // rows a band reads beyond its own, on each side (GEN_STREAM)
-  bool red = false;    // reduces global operators over the image
-  int lds_words = 0;   // static LDS of one work-group
-};
-
 // Whether a program is run by a generated kernel: everything except the
 // single operators that the interpreter's own one-operator kernels already
 // run with constant operators (a built-in point operator; a built-in local
@@ -48,16 +39,18 @@ struct GenSource {
 // that kernel reads at run time).
 bool gen_wanted(const GProg& P);
 
-// Emit the kernel of program P: with an output tile of tw x th, or, where
-// they are 0, streamed if P and its size allow it, else with the largest tile
-// that fits the LDS budget.  Bit i of `stream` marks value i as an
-// output that no later kernel reads (written with non-temporal stores).
-// False, with the reason, if P cannot be generated at that tile.
-bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSource* out, std::string* why);
+// The kernel of program P: with an output tile of tw x th, or, where they are
+// 0, streamed if P allows it, else with the largest tile that fits the LDS
+// budget.  Bit i of `stream` marks value i as an output that no later kernel
+// reads (written with non-temporal stores).  Kernels are kept per process by
+// what their source depends on: the program without its image size, the tile
+// and `stream`.  Null, with the reason or the compiler's log, if P cannot be
+// generated at that tile.  Compiling needs no device.
+const GenKernel* gen_kernel(const GProg& P, int tw, int th, uint32_t stream, std::string* why);
 
-// Compile (or find in the process cache) the kernel for `src`.  Null, with
-// the compiler's log, on failure.  Compiling needs no device.
-const GenKernel* gen_compile(const GenSource& src, std::string* why);
+// Tile of a generated kernel, or the columns of a strip and the number its
+// bands' rows are a multiple of (0 x 0 for the point form).
+void gen_tile(const GenKernel* k, int* tw, int* th);
 
 // Load the kernel's code object on the current device (once per device).
 hipError_t gen_load(const GenKernel* k, int device);

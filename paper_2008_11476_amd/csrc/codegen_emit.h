@@ -10,6 +10,15 @@
 
 namespace hvx {
 
+struct GenSource {
+  std::string text;
+  int form = 0;
+  int tw = 0, th = 0;  // output tile (GEN_TILES); columns of a strip, and what a band's rows are a multiple of (GEN_STREAM)
+  int ext = 0;         // rows a band reads beyond its own, on each side (GEN_STREAM)
+  bool red = false;    // reduces global operators over the image
+  int lds_words = 0;   // static LDS of one work-group
+};
+
 inline std::string fmt(const char* f, ...) __attribute__((format(printf, 1, 2)));
 inline std::string fmt(const char* f, ...) {
   char buf[512];

@@ -1027,7 +1027,6 @@ hvx_status verify_graph(Graph* g) {
     // the group's own kernel, its operators and formats as constants
     // (Section 6); the interpreter runs the group if it cannot be made
     if (g->opt_codegen && gen_wanted(gr.prog)) {
-      GenSource src;
       int tw = 0, th = 0;
       if (choice)
         for (const auto& t : choice->tiles)
@@ -1045,10 +1044,12 @@ hvx_status verify_graph(Graph* g) {
         if (!later) stream |= 1u << i;
       }
       // a chosen tile that does not fit falls back to the default form
-      if (!(tw && gen_source(gr.prog, tw, th, stream, &src, &why)) && !gen_source(gr.prog, 0, 0, stream, &src, &why))
-        src.text.clear();
-      if (!src.text.empty()) gr.gen = gen_compile(src, &why);
-      if (gr.gen && src.form != GEN_POINTS) p.tiles.push_back({gr.ops[0], src.tw, src.th});
+      if (tw) gr.gen = gen_kernel(gr.prog, tw, th, stream, &why);
+      if (!gr.gen) gr.gen = gen_kernel(gr.prog, 0, 0, stream, &why);
+      if (gr.gen) {
+        gen_tile(gr.gen, &tw, &th);
+        if (tw) p.tiles.push_back({gr.ops[0], tw, th});
+      }
       if (gr.gen) {
         ++p.num_generated;
       } else {
