@@ -17,6 +17,17 @@ hipError_t launch_gauss5(const Gauss5Desc& d, bool xcd, hipStream_t s);
 // kinds: bit set of the kinds present (kind_bit); selects the compiled body set.
 hipError_t launch_batch(const BatchImage* imgs, const uint16_t* item_img, int total, unsigned* counter, int grid,
                         bool persistent, int kinds, hipStream_t s);
+// The images of one launch that travel in its kernel arguments (2 KB of the
+// 4 KB a launch may carry).
+constexpr int kStepImages = 16;
+struct StepImages {
+  int32_t first[kStepImages];  // first item of each image, INT_MAX past the last
+  BatchImage img[kStepImages];
+};
+static_assert(sizeof(StepImages) <= 4096, "kernel arguments");
+// One launch over the first `n` images of `a` (their nitems set; the item
+// ranges are filled in here), one wave per item.
+hipError_t launch_images(StepImages& a, int n, hipStream_t s);
 int batch_waves_per_cu(int kinds);
 int kind_bit(const BatchImage& bi);
 // bytes of the zero-initialised counter block the persistent batch kernel needs

@@ -1,6 +1,8 @@
 // Kernel entry points and their host-side launchers.
 #include <hip/hip_runtime.h>
 
+#include <limits.h>
+
 #include <algorithm>
 
 #include "dev_fast.hpp"
@@ -159,6 +161,22 @@ __global__ __launch_bounds__(64) void k_batch_direct(const BatchImage* __restric
   run_flat<KS>(imgs, item_img, item, lds);
 }
 
+// The images of one step of the server, in the kernel's arguments: a step's
+// images change from launch to launch, and uploading their descriptors and a
+// work list of 2 bytes per item first cost two copies on the stream in front
+// of a kernel of 10 to 30 us.  A wave finds its image by counting the first
+// items that lie at or before its own, sixteen scalar compares.
+template <int KS>
+__global__ __launch_bounds__(64) void k_step(const StepImages a) {
+  __shared__ u32x4 lds[kBatchLds<KS>];
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  int im = -1;
+#pragma unroll
+  for (int i = 0; i < kStepImages; ++i) im += item >= a.first[i];
+  const BatchImage& bi = a.img[im];
+  run_item<KS>(bi, item - bi.first_item, lds);
+}
+
 // ---- host launchers ---------------------------------------------------------
 
 hipError_t launch_generic(const GProg& P, const GProg* dev_prog, const IOTable& io, int num_cus, hipStream_t s) {
@@ -252,6 +270,29 @@ hipError_t launch_batch(const BatchImage* imgs, const uint16_t* item_img, int to
     case 7: launch_batch_ks<7>(imgs, item_img, total, counter, grid, persistent, s); break;
     case 19: launch_batch_ks<19>(imgs, item_img, total, counter, grid, persistent, s); break;
     default: launch_batch_ks<31>(imgs, item_img, total, counter, grid, persistent, s); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_images(StepImages& a, int n, hipStream_t s) {
+  int total = 0, kinds = 0;
+  for (int i = 0; i < n; ++i) {
+    a.first[i] = a.img[i].first_item = total;
+    total += a.img[i].nitems;
+    kinds |= kind_bit(a.img[i]);
+  }
+  for (int i = n; i < kStepImages; ++i) a.first[i] = INT_MAX;  // no item lies there
+  if (total <= 0) return hipSuccess;
+  const dim3 g(total), b(64);
+  switch (kinds) {
+    case 1: hipLaunchKernelGGL(k_step<1>, g, b, 0, s, a); break;
+    case 2: hipLaunchKernelGGL(k_step<2>, g, b, 0, s, a); break;
+    case 4: hipLaunchKernelGGL(k_step<4>, g, b, 0, s, a); break;
+    case 8: hipLaunchKernelGGL(k_step<8>, g, b, 0, s, a); break;
+    case 16: hipLaunchKernelGGL(k_step<16>, g, b, 0, s, a); break;
+    case 7: hipLaunchKernelGGL(k_step<7>, g, b, 0, s, a); break;
+    case 19: hipLaunchKernelGGL(k_step<19>, g, b, 0, s, a); break;
+    default: hipLaunchKernelGGL(k_step<31>, g, b, 0, s, a); break;
   }
   return hipGetLastError();
 }
