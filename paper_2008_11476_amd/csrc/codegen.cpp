@@ -18,10 +18,9 @@
 
 #include <hip/hiprtc.h>
 
-#include <math.h>
-
 #include <algorithm>
 #include <array>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -117,96 +116,121 @@ void emit_gop(Text& t, int k, const GOp& o) {
     o.p2, o.p3, float_lit(o.pf).c_str(), m.c_str(), c.c_str(), kc.c_str());
 }
 
+// Grids: x lies on grid g if every finite x is a multiple of 2^g.  Integers
+// lie on grid 0, and rounding a sum or product of numbers on a grid leaves it
+// on that grid, so long as nothing falls below the normal range.
+constexpr int kNoGrid = -1000;
+
+int float_grid(uint32_t bits) {
+  float f;
+  memcpy(&f, &bits, 4);
+  if (f == 0.f) return 0;
+  if (!std::isfinite(f)) return kNoGrid;
+  int e;
+  const double m = ldexp(fabs(frexp((double)f, &e)), 24);  // an integer of 24 bits
+  return e - 24 + __builtin_ctzll((unsigned long long)m);
+}
+int product_grid(int a, int b) { return a == kNoGrid || b == kNoGrid || a + b < -120 ? kNoGrid : a + b; }
+
 // A user kernel's postfix program as one expression (Section 5.1).  The
 // arithmetic follows the interpreter's rules: 32-bit wrapping integer
 // arithmetic with the result saturated to the output format, or F32 with
-// every operation rounded (no contraction).
-bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, std::string* why) {
+// every operation rounded (no contraction).  `in`: the grids of its inputs;
+// returns its result's in `out`.
+bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, const int in[3], int* out, std::string* why) {
   const bool fl = o.p1 != 0;
-  std::vector<std::string> st;
-  auto pop = [&](std::string* s) {
-    if (st.empty()) return false;
-    *s = st.back();
-    st.pop_back();
-    return true;
+  struct Part {
+    std::string s;
+    int grid;
   };
+  std::vector<Part> st;
   if (o.p0 < 1 || o.p0 > kMaxExpr) {
     *why = "malformed user kernel";
     return false;
   }
   for (int i = 0; i < o.p0; ++i) {
     const int op = o.code[i] & 0xFF, arg = o.code[i] >> 8;
-    std::string a, b, c;
-    bool ok = true;
+    const size_t need = (op == X_IN || op == X_INW || op == X_CONST) ? 0
+                        : (op == X_NEG || op == X_ABS || op == X_SQRT) ? 1
+                        : (op == X_CLAMP || op == X_SEL)               ? 3
+                                                                       : 2;
+    if (st.size() < need || (op == X_CONST && (arg < 0 || arg >= kMaxExprConst)) || (op == X_SQRT && !fl)) {
+      *why = "malformed user kernel";
+      return false;
+    }
+    Part q[3];
+    for (size_t n = need; n-- > 0; st.pop_back()) q[n] = st.back();
+    const std::string &a = q[0].s, &b = q[1].s, &c = q[2].s;
+    Part r{"", kNoGrid};
     switch (op) {
       case X_IN:
       case X_INW: {
         std::string v = local ? (op == X_IN ? std::string("rd(0, 0)") : fmt("rd(%d, %d)", arg % 5 - 2, arg / 5 - 2))
                               : fmt("a%d", arg);
         if (fl) v = ((o.p2 >> (op == X_IN ? arg : 0)) & 1) ? "__int_as_float(" + v + ")" : "(float)(" + v + ")";
-        st.push_back(v);
+        r = {v, local ? in[0] : arg >= 0 && arg < 3 ? in[arg] : kNoGrid};
         break;
       }
       case X_CONST:
-        if (arg < 0 || arg >= kMaxExprConst) ok = false;
-        else st.push_back(fl ? fmt("__int_as_float((int)0x%08xu)", (uint32_t)o.kc[arg]) : fmt("(int)0x%08xu", (uint32_t)o.kc[arg]));
+        r.s = fmt(fl ? "__int_as_float((int)0x%08xu)" : "(int)0x%08xu", (uint32_t)o.kc[arg]);
+        r.grid = fl ? float_grid((uint32_t)o.kc[arg]) : 0;
         break;
       case X_ADD:
       case X_SUB:
       case X_MUL:
-      case X_DIV:
-      case X_MIN:
-      case X_MAX:
-      case X_GT: {
-        ok = pop(&b) && pop(&a);
-        if (!ok) break;
+      case X_DIV: {
         static const char* iname[] = {"gx_add", "gx_sub", "gx_mul", "gx_div"};
-        std::string r;
-        if (op == X_MIN) r = (fl ? "fminf(" : "min(") + a + ", " + b + ")";
-        else if (op == X_MAX) r = (fl ? "fmaxf(" : "max(") + a + ", " + b + ")";
-        else if (op == X_GT) r = "((" + a + ") > (" + b + ")" + (fl ? " ? 1.f : 0.f)" : " ? 1 : 0)");
-        else if (fl) r = "(" + a + (op == X_ADD ? " + " : op == X_SUB ? " - " : op == X_MUL ? " * " : " / ") + b + ")";
-        else r = std::string(iname[op - X_ADD]) + "(" + a + ", " + b + ")";
-        st.push_back(r);
+        static const char* fname[] = {" + ", " - ", " * ", " / "};
+        r.s = fl ? "(" + a + fname[op - X_ADD] + b + ")" : std::string(iname[op - X_ADD]) + "(" + a + ", " + b + ")";
+        r.grid = std::min(q[0].grid, q[1].grid);
+        if (op == X_MUL) r.grid = product_grid(q[0].grid, q[1].grid);
+        if (op == X_DIV) {  // by a literal power of two, or unknown
+          const int16_t w = o.code[i - 1];
+          float d = 0.f;
+          int e;
+          if ((w & 0xFF) == X_CONST) memcpy(&d, &o.kc[w >> 8], 4);
+          r.grid = fl && d > 0.f && std::isfinite(d) && frexp((double)d, &e) == 0.5 ? product_grid(q[0].grid, -q[1].grid)
+                                                                                   : kNoGrid;
+        }
         break;
       }
-      case X_NEG:
-      case X_ABS:
-      case X_SQRT:
-        ok = pop(&a);
-        if (!ok) break;
-        if (op == X_NEG) st.push_back(fl ? "(-(" + a + "))" : "gx_neg(" + a + ")");
-        else if (op == X_ABS) st.push_back(fl ? "fabsf(" + a + ")" : "gx_abs(" + a + ")");
-        else if (fl) st.push_back("__builtin_sqrtf(" + a + ")");
-        else ok = false;
+      case X_MIN:
+      case X_MAX:
+        r.s = (op == X_MIN ? (fl ? "fminf(" : "min(") : (fl ? "fmaxf(" : "max(")) + a + ", " + b + ")";
+        r.grid = std::min(q[0].grid, q[1].grid);
         break;
+      case X_GT:
+        r.s = "((" + a + ") > (" + b + ")" + (fl ? " ? 1.f : 0.f)" : " ? 1 : 0)");
+        r.grid = 0;
+        break;
+      case X_NEG: r = {fl ? "(-(" + a + "))" : "gx_neg(" + a + ")", q[0].grid}; break;
+      case X_ABS: r = {fl ? "fabsf(" + a + ")" : "gx_abs(" + a + ")", q[0].grid}; break;
+      case X_SQRT: r.s = (q[0].grid >= -96 ? "sqrt_normal(" : "__builtin_sqrtf(") + a + ")"; break;
       case X_CLAMP:
-        ok = pop(&c) && pop(&b) && pop(&a);
-        if (ok) st.push_back(fl ? "fminf(fmaxf(" + a + ", " + b + "), " + c + ")" : "min(max(" + a + ", " + b + "), " + c + ")");
+        r.s = fl ? "fminf(fmaxf(" + a + ", " + b + "), " + c + ")" : "min(max(" + a + ", " + b + "), " + c + ")";
+        r.grid = std::min(q[0].grid, std::min(q[1].grid, q[2].grid));
         break;
       case X_SEL:
-        ok = pop(&c) && pop(&b) && pop(&a);
-        if (ok) st.push_back("((" + a + ") != " + (fl ? "0.f" : "0") + " ? (" + b + ") : (" + c + "))");
+        r.s = "((" + a + ") != " + (fl ? "0.f" : "0") + " ? (" + b + ") : (" + c + "))";
+        r.grid = std::min(q[1].grid, q[2].grid);
         break;
-      default: ok = false;
+      default: *why = "malformed user kernel"; return false;
     }
-    if (!ok) {
-      *why = "malformed user kernel";
-      return false;
-    }
+    st.push_back(r);
   }
   if (st.size() != 1) {
     *why = "malformed user kernel";
     return false;
   }
+  *out = fl ? st[0].grid : 0;
   if (local) t("template <class RD> __device__ __forceinline__ int gx_expr%d(const RD& rd) {", k);
   else t("__device__ __forceinline__ int gx_expr%d(int a0, int a1, int a2) {", k);
   t("#pragma clang fp contract(off)");
   if (fl) {
-    t("  const float r = %s;", st[0].c_str());
+    t("  const float r = %s;", st[0].s.c_str());
     t("  return __float_as_int(r);");
   } else {
-    t("  const int r = %s;", st[0].c_str());
+    t("  const int r = %s;", st[0].s.c_str());
     t(out_df == DF_U8 ? "  return min(max(r, 0), 255);" : "  return min(max(r, -32768), 32767);");
   }
   t("}");
@@ -271,11 +295,23 @@ void emit_prelude(Text& t, const GProg& P, const char* header, std::string* why,
   t("  if (DF == DF_UYVY) return (int)((w >> sh) & 0xFFFFu);");
   t("  return (int)w;");
   t("}");
+  int grid[kMaxGVals];
+  for (int i = 0; i < P.nvals; ++i) grid[i] = P.vals[i].df == DF_F32 ? kNoGrid : 0;
   for (int k = 0; k < P.nops; ++k) {
     emit_gop(t, k, P.ops[k]);
     const GOp& o = P.ops[k];
+    int in[3], out = kNoGrid;
+    for (int i = 0; i < 3; ++i) in[i] = o.in[i] >= 0 ? grid[o.in[i]] : kNoGrid;
+    if (is_local(o.kind) && o.border == B_CONSTANT && P.vals[o.in[0]].df == DF_F32) {
+      uint32_t c;
+      memcpy(&c, &o.cf, 4);
+      in[0] = std::min(in[0], float_grid(c));
+    }
+    if (o.kind == OP_MULF) out = product_grid(in[0], in[1]);
+    if (o.kind == OP_BOX5F) out = in[0];
     if (o.kind == OP_EXPR || o.kind == OP_EXPR_LOCAL)
-      if (!emit_expr(t, k, o, o.kind == OP_EXPR_LOCAL, P.vals[o.out].df, why)) *ok = false;
+      if (!emit_expr(t, k, o, o.kind == OP_EXPR_LOCAL, P.vals[o.out].df, in, &out, why)) *ok = false;
+    if (o.out >= 0 && P.vals[o.out].df == DF_F32) grid[o.out] = out;
   }
   t("}  // namespace hvx");
   t("using namespace hvx;");

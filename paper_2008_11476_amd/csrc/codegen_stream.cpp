@@ -18,14 +18,14 @@
 // the tile form.  Waves whose strip and band lie inside the image run a body
 // without border code.
 //
-// What bounds it: over batches VALU issue (Tomasi: 264 instructions a row of
-// 248 pixels, 32 3840x2160 frames 0.52 ms, all of it issue; in tiles 1.35 ms),
+// What bounds it: over batches VALU issue (Tomasi: 196 instructions a row of
+// 248 pixels, 32 3840x2160 frames 0.37 ms, all of it issue; in tiles 1.35 ms),
 // on single frames the latency of one wave's steps and the launch.  Measured
-// a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.4 us, FChain 4K
-// 35.2 -> 19.2, Tomasi 4K 49 -> 28, the F32 corner response at 1021x1019
-// 13.7 -> 8.2, Median -> Sobel -> Magnitude -> NonMaxSuppression at 1080p
-// 19.4 -> 14.1.
+// a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.2 us, FChain 4K
+// 35.2 -> 15.4, the F32 corner response at 1021x1019 13.7 -> 6.9, Median ->
+// Sobel -> Magnitude -> NonMaxSuppression at 1080p 19.4 -> 12.3.
 #include <algorithm>
+#include <array>
 #include <cstdlib>
 #include <cstring>
 
@@ -45,6 +45,8 @@ struct Val {
   int depth = 1;           // rows held
   int rx = 0, ry = 0;      // largest radius of the local operators reading it
   int mode = -1, c = 0;    // their border rule (-1: no local reader)
+  bool flt = false;        // held as floats: read by sliding sums of products only
+  bool gone = false;       // a product formed inside its sliding sum
 };
 
 struct Term {  // a user kernel's subexpression on pairs
@@ -62,6 +64,7 @@ struct Planner {
   Val v[kMaxGVals];
   int E = 0, LP = 8, halo = 0, nred = 0;
   int T = 0;  // rows at the image's end whose steps know the rows below it: E, up to a multiple of kUnroll
+  std::array<char, kMaxGOps> slide{};  // per operator: 1 a sliding sum, 2 whose sums of three columns are exact
   Text t;
 
   Planner(const GProg& p, uint32_t nt_, std::string* w) : P(p), nt(nt_), why(w) {}
@@ -208,6 +211,7 @@ struct Planner {
       v[i].hi = g.df == DF_U8 ? 255 : (g.df == DF_UYVY ? 65535 : 32767);
     }
     LP = any_wide ? 4 : 8;
+    plan_slides();
     T = (E + kUnroll - 1) / kUnroll * kUnroll;
     int emax = 0;
     for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
@@ -217,6 +221,136 @@ struct Planner {
         if (P.ops[k].in[i] >= 0 && P.vals[P.ops[k].in[i]].df == DF_UYVY && P.ops[k].kind != OP_CHANNEL_Y)
           return no("a UYVY frame read other than for its luma");
     return true;
+  }
+
+  // Box sums of products of whole numbers (the structure tensor).  Where the
+  // sums of five rows are whole numbers below 2^24, they are exact in any
+  // order: each column keeps the sum of the four newest rows' products, adds
+  // the new row's and takes the oldest's away, two fused multiply-adds per
+  // pixel instead of a product and four additions, and the rings hold the
+  // factors (two planes) instead of the products (three).  Tomasi, bound by
+  // vector issue: 263 -> 196 instructions a row together with sqrt_normal and
+  // Threshold's constants as literals, 32 3840x2160 frames 0.47 -> 0.37 ms.
+  // The product's border must be one of its factors' borders: their nearest
+  // or mirrored pixels, or zero.
+  void plan_slides() {
+    std::vector<long long> amax(P.nvals, -1);  // |whole numbers| of Sobel gradients
+    for (int k = 0; k < P.nops; ++k) {
+      const GOp& o = P.ops[k];
+      if ((o.kind != OP_SOBEL_X && o.kind != OP_SOBEL_Y) || v[o.in[0]].wide) continue;
+      long long lo, hi;
+      local_range(o.in[0], &lo, &hi);
+      amax[o.out] = std::min(4 * (hi - lo), 32768LL);
+    }
+    auto readers = [&](int i, int kind) {  // how many, -1: others read it too
+      int n = 0;
+      for (int k = 0; k < P.nops; ++k)
+        for (int j = 0; j < 3; ++j)
+          if (P.ops[k].in[j] == i) {
+            if (P.ops[k].kind != kind) return -1;
+            ++n;
+          }
+      return P.vals[i].store ? -1 : n;
+    };
+    auto fits = [&](int k) {  // operator k is such a sum
+      if (P.ops[k].kind != OP_BOX5F) return false;
+      const int p = P.ops[k].in[0], m = producer(p);
+      if (m < 0 || P.ops[m].kind != OP_MULF || readers(p, OP_BOX5F) != 1) return false;
+      if (v[p].mode == B_CONSTANT && v[p].c != 0) return false;
+      const long long a = amax[P.ops[m].in[0]], b = amax[P.ops[m].in[1]];
+      return a > 0 && b > 0 && 5 * a * b <= 1 << 24;
+    };
+    // a factor is held as floats if all products that read it slide, under one
+    // border rule; products are taken out until that holds for all factors
+    std::vector<char> ok(P.nops);
+    for (int k = 0; k < P.nops; ++k) ok[k] = fits(k);
+    for (bool again = true; again;) {
+      again = false;
+      for (int k = 0; k < P.nops; ++k) {
+        if (!ok[k]) continue;
+        const int p = P.ops[k].in[0], m = producer(p);
+        for (int j = 0; j < 2 && ok[k]; ++j) {
+          const int a = P.ops[m].in[j];
+          bool all = readers(a, OP_MULF) > 0;
+          for (int i = 0; i < P.nops && all; ++i) {
+            const GOp& q = P.ops[i];
+            if (q.kind != OP_MULF || (q.in[0] != a && q.in[1] != a)) continue;
+            const int b = box_of(q.out);
+            all = b >= 0 && ok[b] && v[q.out].mode == v[p].mode;
+          }
+          if (!all) {
+            ok[k] = 0;
+            again = true;
+          }
+        }
+      }
+    }
+    for (int k = 0; k < P.nops; ++k) {
+      if (!ok[k]) continue;
+      const int p = P.ops[k].in[0], m = producer(p);
+      const long long big = amax[P.ops[m].in[0]] * amax[P.ops[m].in[1]];
+      slide[k] = 15 * big <= 1 << 24 ? 2 : 1;
+      v[p].gone = true;
+      for (int j = 0; j < 2; ++j) {
+        const int i = P.ops[m].in[j];
+        Val& a = v[i];
+        a.flt = true;
+        a.mode = v[p].mode;
+        a.c = 0;
+        a.rx = a.ry = 2;
+        a.depth = std::max(a.depth, P.vals[i].ext - P.vals[P.ops[k].out].ext + 3);
+      }
+    }
+  }
+  int producer(int i) const {
+    for (int k = 0; k < P.nops; ++k)
+      if (P.ops[k].out == i) return k;
+    return -1;
+  }
+  int box_of(int i) const {  // the box filter that reads value i
+    for (int k = 0; k < P.nops; ++k)
+      if (P.ops[k].in[0] == i && P.ops[k].kind == OP_BOX5F) return k;
+    return -1;
+  }
+
+  // row n of a sliding sum, operator k
+  void emit_slide(int k) {
+    const GOp& m = P.ops[producer(P.ops[k].in[0])];
+    const int e = P.vals[P.ops[k].out].ext;
+    auto add = [&](const char* s, bool plus, int dy) {
+      t("        row_fma<%s>(%s, %s, %s);", plus ? "true" : "false", s, row(k, m.in[0], dy).c_str(),
+        row(k, m.in[1], dy).c_str());
+    };
+    t("      WR<%d> cs = {};", LP);
+    t("      if constexpr (V == kAny) {");
+    for (int dy = -2; dy <= 2; ++dy) add("cs", true, dy);
+    t("      } else {");
+    // the four rows above the newest: for a band's first row, and where a row
+    // above the image was known only now
+    if (e > 0) t("        if constexpr (V == kTop ? from_top + %d == 0 : S == %d) {", e, 2 * E - 2 * e);
+    else if (v[m.in[0]].mode == B_MIRROR) t("        if (COL && V == kMid && t == 0) {");
+    else t("        if constexpr (false) {");
+    t("        st.s%d = {};", k);
+    const std::string s = fmt("st.s%d", k);
+    for (int dy = -2; dy <= 1; ++dy) add(s.c_str(), true, dy);
+    t("        }");
+    t("        cs = st.s%d;", k);
+    add("cs", true, 2);
+    t("        st.s%d = cs;", k);
+    add(s.c_str(), false, -2);
+    t("      }");
+    t("      n = row_columns5f<true, %s>(cs);", slide[k] == 2 ? "true" : "false");
+  }
+  // before the first step of a sliding sum without rows of its own to spare
+  void emit_slide_start(int k) {
+    const GOp& o = P.ops[k];
+    if (P.vals[o.out].ext > 0) return;
+    const GOp& m = P.ops[producer(o.in[0])];
+    t("  if constexpr (V != kAny && S == %d) {", 2 * E - 1);
+    t("    st.s%d = {};", k);
+    for (int dy = -1; dy <= 2; ++dy)
+      t("    row_fma<true>(st.s%d, %s, %s);", k, row(k, m.in[0], dy).c_str(), row(k, m.in[1], dy).c_str());
+    t("  }");
   }
 
   // element range of a value as its local readers see it
@@ -439,6 +573,10 @@ struct Planner {
         return true;
       }
       case OP_BOX5F:
+        if (slide[k]) {
+          emit_slide(k);
+          return true;
+        }
         t("      n = row_box5f<%s>(%s, %s, %s, %s, %s);", v[in].nz ? "true" : "false", r(-2).c_str(), r(-1).c_str(),
           r(0).c_str(), r(1).c_str(), r(2).c_str());
         return true;
@@ -494,7 +632,7 @@ struct Planner {
     v[out].hi = std::min(thi, std::max(e.hi, tlo));
   }
 
-  std::string row_type(int i) const { return fmt(v[i].wide ? "WR<%d>" : "PR<%d>", LP); }
+  std::string row_type(int i) const { return fmt(v[i].wide || v[i].flt ? "WR<%d>" : "PR<%d>", LP); }
   int raw_bytes(int i) const { return LP * df_bytes(P.vals[i].df); }
 
   // row n becomes value i's newest
@@ -761,7 +899,9 @@ struct Planner {
     // the rows each value holds, oldest first
     t("struct SxState {");
     for (int i = 0; i < nv; ++i)
-      if (P.vals[i].df != DF_BUF) t("  %s r%d[%d];", row_type(i).c_str(), i, v[i].depth);
+      if (P.vals[i].df != DF_BUF && !v[i].gone) t("  %s r%d[%d];", row_type(i).c_str(), i, v[i].depth);
+    for (int k = 0; k < P.nops; ++k)
+      if (slide[k]) t("  WR<%d> s%d;  // the four newest rows' products", LP, k);
     t("};");
     // partial results of the global operators over a lane's items
     t("struct SxRed {");
@@ -805,7 +945,7 @@ struct Planner {
     for (int k = 0; k < P.nops; ++k) {
       const int i = P.ops[k].out;
       const GVal& gv = P.vals[i];
-      if (is_reduce_op(P.ops[k].kind)) continue;
+      if (is_reduce_op(P.ops[k].kind) || v[i].gone) continue;
       const int D = v[i].depth;
       // rows outside the image that no operator reads are left as they are
       t("  if constexpr (S >= %d) {  // value %d, row t + %d", 2 * E - 2 * gv.ext, i, gv.ext);
@@ -824,8 +964,17 @@ struct Planner {
         t("      n = st.r%d[%d];", i, D - 1);  // above the image: set when row 0 is known
       }
       t("    } else if (V != kAny || (r >= 0 && r < g.H)) {");
+      if (v[i].flt) {
+        t("      PR<%d> whole;", LP);
+        t("      {");
+        t("      PR<%d>& n = whole;", LP);
+      }
       if (!emit_op(k)) return false;
       if (v[i].mode >= 0) emit_fix(i);
+      if (v[i].flt) {
+        t("      }");
+        t("      n = floats(whole);");
+      }
       t("    } else {");
       if (v[i].mode == B_CONSTANT) {
         t("      fill(n, (int)0x%08xu);", (uint32_t)v[i].c);
@@ -869,6 +1018,7 @@ struct Planner {
         }
       }
       t("  }");
+      if (slide[k]) emit_slide_start(k);
     }
     t("  if (S >= %d && (V != kAny || t >= first)) {", 2 * E);
     for (int i = 0; i < nv; ++i) {

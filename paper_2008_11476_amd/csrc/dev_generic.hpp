@@ -108,6 +108,19 @@ __device__ __forceinline__ uint32_t isqrt_u32(uint32_t s) {
   return q;
 }
 
+// __builtin_sqrtf of a number that is not a nonzero one below 2^-96 (shown at
+// compile time), without that function's scaling: the hardware's root is off
+// by at most one unit in the last place, and s is the rounded root of x
+// exactly where x lies in (s * below(s), s * above(s)] (Tuckerman's test).
+// Zeros, infinities, NaN and negative numbers keep the hardware's result, as
+// neither comparison holds for them.  8 instructions instead of 17.
+__device__ __forceinline__ float sqrt_normal(float x) {
+  const float s = __builtin_amdgcn_sqrtf(x);
+  const float below = __int_as_float(__float_as_int(s) - 1), above = __int_as_float(__float_as_int(s) + 1);
+  const float r = __builtin_fmaf(-below, s, x) <= 0.f ? below : s;
+  return __builtin_fmaf(-above, s, x) > 0.f ? above : r;
+}
+
 __device__ __forceinline__ int sat_u8(int v) { return min(max(v, 0), 255); }
 __device__ __forceinline__ int sat_s16(int v) { return min(max(v, -32768), 32767); }
 
@@ -239,7 +252,10 @@ __device__ __forceinline__ int point_eval(const GOp& o, int out_df, bool in_f32,
     }
     case OP_THRESHOLD: {
       bool hit = in_f32 ? (__int_as_float(a) > o.pf) : (a >= o.p2);
-      return hit ? o.p0 : o.p1;
+      // copies: a choice between the two members would be one of addresses,
+      // and a load from memory where `o` is a constant
+      const int yes = o.p0, not_ = o.p1;
+      return hit ? yes : not_;
     }
     case OP_ADD: {
       int sm = a + b;

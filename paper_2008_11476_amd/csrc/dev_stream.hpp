@@ -661,6 +661,31 @@ __device__ __forceinline__ WR<LP> row_mulf(const PR<LP>& a, const PR<LP>& b) {
     r.v[q] = __float_as_int(NZ ? __builtin_fmaf((float)x.v[q], (float)y.v[q], 0.f) : (float)x.v[q] * (float)y.v[q]);
   return r;
 }
+// Sums of five columns left to right, each addition rounded.  TRI: sums of
+// three are exact, so neighbouring pixels share the first two additions.
+template <bool NZ, bool TRI, int LP>
+__device__ __forceinline__ WR<LP> row_columns5f(const WR<LP>& t) {
+#pragma clang fp contract(off)
+  const WX<LP, 2> x = ext<2>(t);
+  WR<LP> r;
+  float p = 0.f;
+#pragma unroll
+  for (int q = 0; q < LP; ++q) {
+    auto at = [&](int i) { return __int_as_float(x.v[q + i]); };
+    float s;
+    if constexpr (TRI) {
+      if (q % 2 == 0) p = at(1) + at(2);  // of pixels q and q + 1
+      s = q % 2 == 0 ? at(0) + p : p + at(2);
+    } else {
+      s = NZ ? at(0) : 0.f + at(0);
+      s = s + at(1);
+      s = s + at(2);
+    }
+    s = s + at(3);
+    r.v[q] = __float_as_int(s + at(4));
+  }
+  return r;
+}
 // F32 Box5x5 in the fixed order of local_eval: each column top to bottom,
 // then the columns left to right.  NZ: no element is -0, so the leading
 // additions of zero change nothing.
@@ -668,7 +693,7 @@ template <bool NZ, int LP>
 __device__ __forceinline__ WR<LP> row_box5f(const WR<LP>& a, const WR<LP>& b, const WR<LP>& c, const WR<LP>& d,
                                             const WR<LP>& e) {
 #pragma clang fp contract(off)
-  WR<LP> t, r;
+  WR<LP> t;
 #pragma unroll
   for (int q = 0; q < LP; ++q) {
     float s = NZ ? __int_as_float(a.v[q]) : 0.f + __int_as_float(a.v[q]);
@@ -677,16 +702,24 @@ __device__ __forceinline__ WR<LP> row_box5f(const WR<LP>& a, const WR<LP>& b, co
     s = s + __int_as_float(d.v[q]);
     t.v[q] = __float_as_int(s + __int_as_float(e.v[q]));
   }
-  const WX<LP, 2> x = ext<2>(t);
+  return row_columns5f<NZ, false>(t);
+}
+// Whole numbers as floats, and products of such rows added to or taken from
+// sums that stay below 2^24 (exact, so in any order).
+template <int LP>
+__device__ __forceinline__ WR<LP> floats(const PR<LP>& p) {
+  WR<LP> w = wide(p);
+#pragma unroll
+  for (int q = 0; q < LP; ++q) w.v[q] = __float_as_int((float)w.v[q]);
+  return w;
+}
+template <bool ADD, int LP>
+__device__ __forceinline__ void row_fma(WR<LP>& s, const WR<LP>& a, const WR<LP>& b) {
 #pragma unroll
   for (int q = 0; q < LP; ++q) {
-    float s = NZ ? __int_as_float(x.v[q]) : 0.f + __int_as_float(x.v[q]);
-    s = s + __int_as_float(x.v[q + 1]);
-    s = s + __int_as_float(x.v[q + 2]);
-    s = s + __int_as_float(x.v[q + 3]);
-    r.v[q] = __float_as_int(s + __int_as_float(x.v[q + 4]));
+    const float x = __int_as_float(a.v[q]);
+    s.v[q] = __float_as_int(__builtin_fmaf(ADD ? x : -x, __int_as_float(b.v[q]), __int_as_float(s.v[q])));
   }
-  return r;
 }
 #undef HVX_ROW
 
