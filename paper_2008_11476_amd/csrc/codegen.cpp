@@ -326,7 +326,7 @@ bool emit_points(const GProg& P, uint32_t stream, GenSource* out, std::string* w
   bool ok = true;
   emit_prelude(t, P, "dev_generic.hpp", why, &ok);
   if (!ok) return false;
-  t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen(const GProg* __restrict__ P, const IOTable io0,",
+  t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen(const IOTable io0, int W0, int H0,",
     kGenThreads);
   t("                                                           const GenBatchImage* __restrict__ imgs, int nimg,");
   t("                                                           uint32_t* __restrict__ ws) {");
@@ -335,8 +335,8 @@ bool emit_points(const GProg& P, uint32_t stream, GenSource* out, std::string* w
   t("  int W, H, blk = (int)blockIdx.x;");
   t("  if (nimg == 0) {");
   t("    io = io0;");
-  t("    W = P->w;");
-  t("    H = P->h;");
+  t("    W = W0;");
+  t("    H = H0;");
   t("  } else {");
   t("    const int i = gx_batch_image(imgs, nimg, blk);");
   t("    io = imgs[i].io;");
@@ -940,7 +940,7 @@ bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSour
     if (s + 1 < L.nstages) t("  __syncthreads();");
   }
   t("}");
-  t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen(const GProg* __restrict__ P, const IOTable io0,",
+  t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen(const IOTable io0, int W0, int H0,",
     kGenThreads);
   t("                                                           const GenBatchImage* __restrict__ imgs, int nimg,");
   t("                                                           uint32_t* __restrict__ ws) {");
@@ -961,8 +961,8 @@ bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSour
   t("  int W, H, stride = nb, limit = 1 << 30;");
   t("  if (nimg == 0) {");
   t("    io = io0;");
-  t("    W = P->w;");
-  t("    H = P->h;");
+  t("    W = W0;");
+  t("    H = H0;");
   t("  } else {");
   t("    const int i = gx_batch_image(imgs, nimg, vb);");
   t("    io = imgs[i].io;");
@@ -1159,7 +1159,7 @@ static unsigned gen_threads(const GenKernel* k) {
   return k->form != GEN_STREAM ? kGenThreads : (k->red ? 64 * kStreamRedWaves : 64);
 }
 
-hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
+hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTable& io,
                       int num_cus, hipStream_t s, uint32_t* ws) {
   if (device < 0 || device >= kMaxDevices || !k->fn[device]) return hipErrorInvalidDeviceFunction;
   // One work-group per tile (a persistent grid of as many groups as fit
@@ -1171,11 +1171,12 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GPro
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (k->red && !ws) return hipErrorInvalidValue;
-  const GProg* p = dev_prog;
+  // the size travels in the arguments, not in the program's copy in device
+  // memory: one dependent load less before a wave's first rows
   IOTable t = io;
   const GenBatchImage* none = nullptr;
-  int zero = 0;
-  void* args[] = {(void*)&p, (void*)&t, (void*)&none, (void*)&zero, (void*)&ws, (void*)&rows};
+  int w = P.w, h = P.h, zero = 0;
+  void* args[] = {(void*)&t, (void*)&w, (void*)&h, (void*)&none, (void*)&zero, (void*)&ws, (void*)&rows};
   return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
@@ -1241,12 +1242,11 @@ hipError_t gen_launch_batch(const GenKernel* k, int device, const GenBatchImage*
   if (k->red) return hipErrorInvalidValue;
   if (n <= 0 || blocks <= 0) return hipSuccess;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const GProg* p = nullptr;
   IOTable t;
   memset(&t, 0, sizeof t);
   uint32_t* ws = nullptr;
-  int rows = 0;  // each image's own
-  void* args[] = {(void*)&p, (void*)&t, (void*)&imgs, (void*)&n, (void*)&ws, (void*)&rows};
+  int none = 0, rows = 0;  // each image's own
+  void* args[] = {(void*)&t, (void*)&none, (void*)&none, (void*)&imgs, (void*)&n, (void*)&ws, (void*)&rows};
   return hipModuleLaunchKernel(k->fn[device], (unsigned)blocks, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 

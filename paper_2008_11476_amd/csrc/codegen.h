@@ -58,8 +58,8 @@ hipError_t gen_load(const GenKernel* k, int device);
 // Launch on stream s (gen_load must have succeeded on the current device).
 // A kernel that reduces global operators (not gen_batchable) writes one slot
 // of red_slot_words(P) words per work-group, gen_slots of them, to `ws`.
-hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const GProg* dev_prog, const IOTable& io,
-                      int num_cus, hipStream_t s, uint32_t* ws);
+hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTable& io, int num_cus,
+                      hipStream_t s, uint32_t* ws);
 
 // Strips of an image of the given width, and the rows of a band where one
 // launch runs strips of the given total height (0 for the other forms);

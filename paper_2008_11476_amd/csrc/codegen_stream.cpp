@@ -21,9 +21,9 @@
 // What bounds it: over batches VALU issue (Tomasi: 196 instructions a row of
 // 248 pixels, 32 3840x2160 frames 0.37 ms, all of it issue; in tiles 1.35 ms),
 // on single frames the latency of one wave's steps and the launch.  Measured
-// a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.2 us, FChain 4K
-// 35.2 -> 15.4, the F32 corner response at 1021x1019 13.7 -> 6.9, Median ->
-// Sobel -> Magnitude -> NonMaxSuppression at 1080p 19.4 -> 12.3.
+// a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.1 us, FChain 4K
+// 35.2 -> 15.2, the F32 corner response at 1021x1019 13.7 -> 6.5, Median ->
+// Sobel -> Magnitude -> NonMaxSuppression at 1080p 19.4 -> 11.4.
 #include <algorithm>
 #include <array>
 #include <cstdlib>
@@ -526,10 +526,14 @@ struct Planner {
         t("      n = row_nonmax<%d, %d>(w);", R, odf);
         return true;
       }
-      case OP_MAGNITUDE:
-        t("      n = row_magnitude(%s, %s);", r(0).c_str(), row(k, o.in[1], 0).c_str());
+      case OP_MAGNITUDE: {
+        bool small = true;
+        for (int i = 0; i < 2; ++i) small &= v[o.in[i]].lo >= -1020 && v[o.in[i]].hi <= 1020;
+        t("      n = row_magnitude<%s>(%s, %s);", small ? "true" : "false", r(0).c_str(), row(k, o.in[1], 0).c_str());
         v[out].lo = 0;
+        if (small) v[out].hi = 1443;
         return true;
+      }
       case OP_PHASE: {
         bool small = true;
         for (int i = 0; i < 2; ++i) small &= v[o.in[i]].lo >= -1023 && v[o.in[i]].hi <= 1023;
@@ -801,7 +805,7 @@ struct Planner {
   }
 
   void emit_entry() {
-    t("extern \"C\" __global__ __launch_bounds__(64) void hvx_gen_stream(const GProg* __restrict__ P, const IOTable io0,");
+    t("extern \"C\" __global__ __launch_bounds__(64) void hvx_gen_stream(const IOTable io0, int W0, int H0,");
     t("                                                           const GenBatchImage* __restrict__ imgs, int nimg,");
     t("                                                           uint32_t* __restrict__ ws, int rows) {");
     // every XCD takes a contiguous run of items (block b runs on XCD b mod 8),
@@ -813,8 +817,8 @@ struct Planner {
     t("  int W, H;");
     t("  if (nimg == 0) {");
     t("    io = io0;");
-    t("    W = P->w;");
-    t("    H = P->h;");
+    t("    W = W0;");
+    t("    H = H0;");
     t("  } else {");
     t("    const int i = gx_batch_image(imgs, nimg, item);");
     t("    io = imgs[i].io;");
@@ -839,7 +843,7 @@ struct Planner {
   // rows and the LDS additions.
   void emit_reducing_entry() {
     constexpr int NT = 64 * kStreamRedWaves;
-    t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen_stream(const GProg* __restrict__ P, const IOTable io,", NT);
+    t("extern \"C\" __global__ __launch_bounds__(%d) void hvx_gen_stream(const IOTable io, int W, int H,", NT);
     t("                                                           const GenBatchImage* __restrict__ imgs, int nimg,");
     t("                                                           uint32_t* __restrict__ ws, int rows) {");
     t("  __shared__ unsigned long long part[2][%d];", NT / 64);
@@ -859,7 +863,6 @@ struct Planner {
     t("  const int nb = (int)gridDim.x, b = (int)blockIdx.x;");
     t("  const int per = nb / 8, rem = nb %% 8, xcd = b %% 8;");
     t("  const int vb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + b / 8;");
-    t("  const int W = P->w, H = P->h;");
     const int strip_px = (64 - 2 * halo) * LP;
     emit_geometry(strip_px);
     t("  const int items = strips * bands;");

@@ -633,13 +633,20 @@ __device__ __forceinline__ int magnitude_of(uint32_t s) {
   const uint32_t m = q + ((int)(s - __umul24(q, q)) > (int)q ? 1u : 0u);
   return (int)min(m, 32767u);
 }
-template <int LP>
+// SMALL: gradients up to 1020 (Sobel of U8): the hardware's root, rounded to
+// the nearest integer, is the rounded root of every sum up to 2 * 1020^2 (each
+// of them compared).  Adding 2^23 rounds it and leaves the integer in the low
+// half, which is all that packing takes: 5 instructions a pixel instead of 10.
+template <bool SMALL, int LP>
 __device__ __forceinline__ PR<LP> row_magnitude(const PR<LP>& a, const PR<LP>& b) {
   const WR<LP> x = wide(a), y = wide(b);
   WR<LP> r;
 #pragma unroll
-  for (int q = 0; q < LP; ++q)
-    r.v[q] = magnitude_of((uint32_t)(x.v[q] * x.v[q]) + (uint32_t)(y.v[q] * y.v[q]));
+  for (int q = 0; q < LP; ++q) {
+    const uint32_t s = (uint32_t)(x.v[q] * x.v[q]) + (uint32_t)(y.v[q] * y.v[q]);
+    if constexpr (SMALL) r.v[q] = __float_as_int(__builtin_amdgcn_sqrtf((float)s) + 8388608.f);
+    else r.v[q] = magnitude_of(s);
+  }
   return packed(r);
 }
 template <int LP>  // |gradients| <= 1023

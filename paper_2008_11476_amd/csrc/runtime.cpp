@@ -360,11 +360,11 @@ static hvx_status launch_group(Graph* g, const Group& gr, hipStream_t s, const B
       // per work-group; a second kernel forms the results from them
       char* base = b && b->scratch ? b->scratch : g->scratch_base;
       uint32_t* ws = (uint32_t*)(base + g->ws_off[gi]);
-      e = gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, ws);
+      e = gen_launch(gr.gen, g->ctx->device, P, io, g->ctx->num_cus, s, ws);
       if (e == hipSuccess)
         e = launch_finish_partials(P, g->dev_progs + gi, io, ws, (int)gen_slots(gr.gen, P.w, P.h, g->ctx->num_cus), s);
     } else if (gr.gen) {
-      e = gen_launch(gr.gen, g->ctx->device, P, g->dev_progs + gi, io, g->ctx->num_cus, s, nullptr);
+      e = gen_launch(gr.gen, g->ctx->device, P, io, g->ctx->num_cus, s, nullptr);
     } else {
       // global operators reduced by the interpreter: starting values before
       // it, final values after it, in the same stream
