@@ -116,32 +116,60 @@ void emit_gop(Text& t, int k, const GOp& o) {
     o.p2, o.p3, float_lit(o.pf).c_str(), m.c_str(), c.c_str(), kc.c_str());
 }
 
-// Grids: x lies on grid g if every finite x is a multiple of 2^g.  Integers
-// lie on grid 0, and rounding a sum or product of numbers on a grid leaves it
-// on that grid, so long as nothing falls below the normal range.
-constexpr int kNoGrid = -1000;
+// What is known of an F32 value when the kernel is written.  Grid: every
+// value is a multiple of 2^grid; top: none exceeds 2^top in magnitude.
+// Integers lie on grid 0, and rounding a sum or product of numbers on a grid
+// leaves it on that grid, so long as nothing falls below the normal range.
+constexpr int kNoGrid = -1000, kNoTop = 1000;
+struct Known {
+  int grid = kNoGrid, top = kNoTop;
+  bool nonneg = false;
+};
 
-int float_grid(uint32_t bits) {
+Known known_float(uint32_t bits) {
+  Known r;
   float f;
   memcpy(&f, &bits, 4);
-  if (f == 0.f) return 0;
-  if (!std::isfinite(f)) return kNoGrid;
+  if (!std::isfinite(f)) return r;
+  r.nonneg = f >= 0.f;
+  r.grid = r.top = 0;
+  if (f == 0.f) return r;
   int e;
   const double m = ldexp(fabs(frexp((double)f, &e)), 24);  // an integer of 24 bits
-  return e - 24 + __builtin_ctzll((unsigned long long)m);
+  r.grid = e - 24 + __builtin_ctzll((unsigned long long)m);
+  r.top = e;
+  return r;
 }
-int product_grid(int a, int b) { return a == kNoGrid || b == kNoGrid || a + b < -120 ? kNoGrid : a + b; }
+// either of two values
+Known known_either(const Known& a, const Known& b) {
+  return {std::min(a.grid, b.grid), std::max(a.top, b.top), a.nonneg && b.nonneg};
+}
+Known known_product(const Known& a, const Known& b) {
+  Known r;
+  if (a.grid != kNoGrid && b.grid != kNoGrid && a.grid + b.grid >= -120) r.grid = a.grid + b.grid;
+  if (a.top + b.top <= 126) r.top = a.top + b.top;
+  r.nonneg = a.nonneg && b.nonneg;
+  return r;
+}
+Known known_sum(const Known& a, const Known& b) {
+  Known r = known_either(a, b);
+  r.top = r.top + 1 <= 126 ? r.top + 1 : kNoTop;
+  return r;
+}
 
 // A user kernel's postfix program as one expression (Section 5.1).  The
 // arithmetic follows the interpreter's rules: 32-bit wrapping integer
 // arithmetic with the result saturated to the output format, or F32 with
-// every operation rounded (no contraction).  `in`: the grids of its inputs;
-// returns its result's in `out`.
-bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, const int in[3], int* out, std::string* why) {
+// every operation rounded (no contraction, but for a scaling by 2^-n that is
+// exact and so rounds nothing).  `in`: what is known of its inputs; returns
+// what is known of its result.
+bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, const Known in[3], Known* out, std::string* why) {
   const bool fl = o.p1 != 0;
   struct Part {
     std::string s;
-    int grid;
+    Known is;
+    std::string base;  // F32: s is base * scale, exactly
+    float scale = 0.f;
   };
   std::vector<Part> st;
   if (o.p0 < 1 || o.p0 > kMaxExpr) {
@@ -161,58 +189,100 @@ bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, const int i
     Part q[3];
     for (size_t n = need; n-- > 0; st.pop_back()) q[n] = st.back();
     const std::string &a = q[0].s, &b = q[1].s, &c = q[2].s;
-    Part r{"", kNoGrid};
+    Part r;
     switch (op) {
       case X_IN:
       case X_INW: {
         std::string v = local ? (op == X_IN ? std::string("rd(0, 0)") : fmt("rd(%d, %d)", arg % 5 - 2, arg / 5 - 2))
                               : fmt("a%d", arg);
         if (fl) v = ((o.p2 >> (op == X_IN ? arg : 0)) & 1) ? "__int_as_float(" + v + ")" : "(float)(" + v + ")";
-        r = {v, local ? in[0] : arg >= 0 && arg < 3 ? in[arg] : kNoGrid};
+        r.s = v;
+        if (local) r.is = in[0];
+        else if (arg >= 0 && arg < 3) r.is = in[arg];
         break;
       }
       case X_CONST:
         r.s = fmt(fl ? "__int_as_float((int)0x%08xu)" : "(int)0x%08xu", (uint32_t)o.kc[arg]);
-        r.grid = fl ? float_grid((uint32_t)o.kc[arg]) : 0;
+        if (fl) r.is = known_float((uint32_t)o.kc[arg]);
         break;
       case X_ADD:
-      case X_SUB:
+      case X_SUB: {
+        if (fl) {
+          const bool sub = op == X_SUB;
+          r.s = "(" + a + (sub ? " - " : " + ") + b + ")";
+          if (!q[0].base.empty())
+            r.s = fmt("__builtin_fmaf(%af, ", q[0].scale) + q[0].base + (sub ? ", -(" : ", (") + b + "))";
+          else if (!q[1].base.empty())
+            r.s = fmt("__builtin_fmaf(%af, ", sub ? -q[1].scale : q[1].scale) + q[1].base + ", " + a + ")";
+          r.is = known_sum(q[0].is, q[1].is);
+          r.is.nonneg &= !sub;
+        } else {
+          r.s = std::string(op == X_ADD ? "gx_add(" : "gx_sub(") + a + ", " + b + ")";
+        }
+        break;
+      }
       case X_MUL:
       case X_DIV: {
-        static const char* iname[] = {"gx_add", "gx_sub", "gx_mul", "gx_div"};
-        static const char* fname[] = {" + ", " - ", " * ", " / "};
-        r.s = fl ? "(" + a + fname[op - X_ADD] + b + ")" : std::string(iname[op - X_ADD]) + "(" + a + ", " + b + ")";
-        r.grid = std::min(q[0].grid, q[1].grid);
-        if (op == X_MUL) r.grid = product_grid(q[0].grid, q[1].grid);
-        if (op == X_DIV) {  // by a literal power of two, or unknown
-          const int16_t w = o.code[i - 1];
-          float d = 0.f;
-          int e;
-          if ((w & 0xFF) == X_CONST) memcpy(&d, &o.kc[w >> 8], 4);
-          r.grid = fl && d > 0.f && std::isfinite(d) && frexp((double)d, &e) == 0.5 ? product_grid(q[0].grid, -q[1].grid)
-                                                                                   : kNoGrid;
+        if (!fl) {
+          r.s = std::string(op == X_MUL ? "gx_mul(" : "gx_div(") + a + ", " + b + ")";
+          break;
+        }
+        r.s = "(" + a + (op == X_MUL ? " * " : " / ") + b + ")";
+        // a literal power of two on the right
+        const int16_t w = o.code[i - 1];
+        float d = 0.f;
+        int e;
+        if ((w & 0xFF) == X_CONST) memcpy(&d, &o.kc[w >> 8], 4);
+        const bool pow2 = d > 0.f && std::isfinite(d) && frexp((double)d, &e) == 0.5 && e > -60 && e < 60;
+        if (op == X_MUL) {
+          r.is = known_product(q[0].is, q[1].is);
+          r.is.nonneg |= a == b;
+        } else if (pow2) {
+          d = 1.f / d;
+          uint32_t u;
+          memcpy(&u, &d, 4);
+          r.is = known_product(q[0].is, known_float(u));
+        }
+        if (pow2 && d <= 1.f && r.is.grid != kNoGrid) {
+          r.base = a;
+          r.scale = d;
         }
         break;
       }
       case X_MIN:
       case X_MAX:
         r.s = (op == X_MIN ? (fl ? "fminf(" : "min(") : (fl ? "fmaxf(" : "max(")) + a + ", " + b + ")";
-        r.grid = std::min(q[0].grid, q[1].grid);
+        r.is = known_either(q[0].is, q[1].is);
+        if (op == X_MAX) r.is.nonneg = q[0].is.nonneg || q[1].is.nonneg;
         break;
       case X_GT:
         r.s = "((" + a + ") > (" + b + ")" + (fl ? " ? 1.f : 0.f)" : " ? 1 : 0)");
-        r.grid = 0;
+        r.is = {0, 0, true};
         break;
-      case X_NEG: r = {fl ? "(-(" + a + "))" : "gx_neg(" + a + ")", q[0].grid}; break;
-      case X_ABS: r = {fl ? "fabsf(" + a + ")" : "gx_abs(" + a + ")", q[0].grid}; break;
-      case X_SQRT: r.s = (q[0].grid >= -96 ? "sqrt_normal(" : "__builtin_sqrtf(") + a + ")"; break;
+      case X_NEG:
+        r.s = fl ? "(-(" + a + "))" : "gx_neg(" + a + ")";
+        r.is = q[0].is;
+        r.is.nonneg = false;
+        break;
+      case X_ABS:
+        r.s = fl ? "fabsf(" + a + ")" : "gx_abs(" + a + ")";
+        r.is = q[0].is;
+        r.is.nonneg = true;
+        break;
+      case X_SQRT: {
+        const Known& x = q[0].is;
+        const bool bounded = x.nonneg && x.grid >= -96 && x.top <= 126;
+        r.s = (bounded ? "sqrt_bounded(" : "__builtin_sqrtf(") + a + ")";
+        if (bounded) r.is = {kNoGrid, std::max(x.top, 1), true};
+        break;
+      }
       case X_CLAMP:
         r.s = fl ? "fminf(fmaxf(" + a + ", " + b + "), " + c + ")" : "min(max(" + a + ", " + b + "), " + c + ")";
-        r.grid = std::min(q[0].grid, std::min(q[1].grid, q[2].grid));
+        r.is = known_either(q[0].is, known_either(q[1].is, q[2].is));
         break;
       case X_SEL:
         r.s = "((" + a + ") != " + (fl ? "0.f" : "0") + " ? (" + b + ") : (" + c + "))";
-        r.grid = std::min(q[1].grid, q[2].grid);
+        r.is = known_either(q[1].is, q[2].is);
         break;
       default: *why = "malformed user kernel"; return false;
     }
@@ -222,7 +292,7 @@ bool emit_expr(Text& t, int k, const GOp& o, bool local, int out_df, const int i
     *why = "malformed user kernel";
     return false;
   }
-  *out = fl ? st[0].grid : 0;
+  if (fl) *out = st[0].is;
   if (local) t("template <class RD> __device__ __forceinline__ int gx_expr%d(const RD& rd) {", k);
   else t("__device__ __forceinline__ int gx_expr%d(int a0, int a1, int a2) {", k);
   t("#pragma clang fp contract(off)");
@@ -295,23 +365,34 @@ void emit_prelude(Text& t, const GProg& P, const char* header, std::string* why,
   t("  if (DF == DF_UYVY) return (int)((w >> sh) & 0xFFFFu);");
   t("  return (int)w;");
   t("}");
-  int grid[kMaxGVals];
-  for (int i = 0; i < P.nvals; ++i) grid[i] = P.vals[i].df == DF_F32 ? kNoGrid : 0;
+  Known known[kMaxGVals];
+  for (int i = 0; i < P.nvals; ++i) {
+    const int df = P.vals[i].df;
+    if (df != DF_F32) known[i] = {0, df == DF_U8 ? 8 : df == DF_S16 ? 15 : 31, df == DF_U8 || df == DF_UYVY};
+  }
   for (int k = 0; k < P.nops; ++k) {
     emit_gop(t, k, P.ops[k]);
     const GOp& o = P.ops[k];
-    int in[3], out = kNoGrid;
-    for (int i = 0; i < 3; ++i) in[i] = o.in[i] >= 0 ? grid[o.in[i]] : kNoGrid;
-    if (is_local(o.kind) && o.border == B_CONSTANT && P.vals[o.in[0]].df == DF_F32) {
+    Known in[3], out;
+    for (int i = 0; i < 3; ++i)
+      if (o.in[i] >= 0) in[i] = known[o.in[i]];
+    if (is_local(o.kind) && o.border == B_CONSTANT) {
       uint32_t c;
-      memcpy(&c, &o.cf, 4);
-      in[0] = std::min(in[0], float_grid(c));
+      const float v = P.vals[o.in[0]].df == DF_F32 ? o.cf : (float)o.cint;
+      memcpy(&c, &v, 4);
+      in[0] = known_either(in[0], known_float(c));
     }
-    if (o.kind == OP_MULF) out = product_grid(in[0], in[1]);
-    if (o.kind == OP_BOX5F) out = in[0];
+    if (o.kind == OP_MULF) {
+      out = known_product(in[0], in[1]);
+      out.nonneg |= o.in[0] == o.in[1];
+    }
+    if (o.kind == OP_BOX5F) {
+      out = in[0];  // the sum of 25
+      out.top = in[0].top <= 120 ? in[0].top + 5 : kNoTop;
+    }
     if (o.kind == OP_EXPR || o.kind == OP_EXPR_LOCAL)
       if (!emit_expr(t, k, o, o.kind == OP_EXPR_LOCAL, P.vals[o.out].df, in, &out, why)) *ok = false;
-    if (o.out >= 0 && P.vals[o.out].df == DF_F32) grid[o.out] = out;
+    if (o.out >= 0 && P.vals[o.out].df == DF_F32) known[o.out] = out;
   }
   t("}  // namespace hvx");
   t("using namespace hvx;");

@@ -18,8 +18,8 @@
 // the tile form.  Waves whose strip and band lie inside the image run a body
 // without border code.
 //
-// What bounds it: over batches VALU issue (Tomasi: 196 instructions a row of
-// 248 pixels, 32 3840x2160 frames 0.37 ms, all of it issue; in tiles 1.35 ms),
+// What bounds it: over batches VALU issue (Tomasi: 176 instructions a row of
+// 248 pixels, 32 3840x2160 frames 0.33 ms, all of it issue; in tiles 1.35 ms),
 // on single frames the latency of one wave's steps and the launch.  Measured
 // a process call, tiles -> streamed: Unsharp 4K 11.9 -> 7.1 us, FChain 4K
 // 35.2 -> 15.2, the F32 corner response at 1021x1019 13.7 -> 6.5, Median ->
@@ -229,7 +229,7 @@ struct Planner {
   // the new row's and takes the oldest's away, two fused multiply-adds per
   // pixel instead of a product and four additions, and the rings hold the
   // factors (two planes) instead of the products (three).  Tomasi, bound by
-  // vector issue: 263 -> 196 instructions a row together with sqrt_normal and
+  // vector issue: 263 -> 196 instructions a row together with cheaper roots and
   // Threshold's constants as literals, 32 3840x2160 frames 0.47 -> 0.37 ms.
   // The product's border must be one of its factors' borders: their nearest
   // or mirrored pixels, or zero.

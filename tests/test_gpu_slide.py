@@ -80,8 +80,19 @@ def _roots(img, b):
         {"in": img}, {"r%d" % i: F32 for i in range(5)})
 
 
+def _scaled(img, b):
+    """Scalings by powers of two inside sums, exact or not provably so."""
+    return gs.Spec(_products(b, b) + [
+        _point(["sxx", "sxy"], "r0", "a / 4 - b * 0.125 + sqrt(abs(a) * 0.5 + 1)"),
+        _point(["sxx", "sxy"], "r1", "(a - b) * (a - b) / 8 - b / 2 - (b - a * 0.25)"),
+        _point(["r1", "sxy"], "r2", "sqrt(a * a / 65536 + b * b) / 2 + a * 4"),
+        _point(["sxx", "sxy"], "r3", "sqrt(a * b * a * b) - sqrt(a * a * a * a) / 2"),
+        _point(["r2", "r3"], "r4", "a / 1048576 + b / 1048576 / 1048576 / 1048576 / 1048576 - a")],
+        {"in": img}, {"r%d" % i: F32 for i in range(5)})
+
+
 GRAPHS = {"plain": _plain, "read_again": _read_again, "two_rules": _two_rules, "other_readers": _other_readers,
-          "of_values": _of_values, "roots": _roots}
+          "of_values": _of_values, "roots": _roots, "scaled": _scaled}
 BORDERS = [("replicate", 0), ("mirror", 0), ("constant", 0), ("constant", 3)]
 SIZES = [(248, 40), (993, 209), (1, 40), (2, 2), (64, 1031), (500, 67)]
 
