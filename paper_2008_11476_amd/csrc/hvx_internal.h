@@ -228,9 +228,9 @@ hvx_status prepare_graph(Graph* g);
 hvx_status schedule_graph(Graph* g, void* stream);
 hvx_status schedule_bound(Graph* g, void* stream, const Bind* b);
 void free_graph_device(Graph* g);
-int default_rows(const Group& gr, int num_cus);
+int default_rows(const Plan& p, const Group& gr, int num_cus);
 // rows per work item for hand-fused groups that run in one launch
-int rows_together(const std::vector<const Group*>& groups, int num_cus, int waves_per_cu);
+int rows_together(const std::vector<const Graph*>& graphs, int num_cus);
 int rows_for(const Graph* g, const Group& gr);  // rows per work item in effect (option, tuned, default)
 void fill_fast_desc(const Graph* g, const Group& gr, BatchImage* bi, int rows_override = 0, const Bind* b = nullptr);
 int64_t fast_items(const Group& gr);

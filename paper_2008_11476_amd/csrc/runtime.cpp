@@ -68,7 +68,7 @@ static hvx_status ensure_scratch(Graph* g) {
         return set_error(g->ctx, HVX_ERROR_DEVICE, "cannot load a generated kernel: %s", hipGetErrorString(e));
     }
   for (Group& gr : p.groups)
-    if (is_strip_kind(gr.kind)) gr.own_rows = default_rows(gr, g->ctx->num_cus);
+    if (is_strip_kind(gr.kind)) gr.own_rows = default_rows(*g->plan, gr, g->ctx->num_cus);
   std::vector<GProg> progs(p.groups.size());
   for (size_t i = 0; i < p.groups.size(); ++i) progs[i] = p.groups[i].prog;
   if (hipMalloc((void**)&g->dev_progs, progs.size() * sizeof(GProg)) != hipSuccess ||
@@ -147,34 +147,42 @@ static int strip_px(int kind) { return kind == FK_CORNER ? 62 * 4 : kStripPx; }
 struct RowsFor {
   std::vector<std::pair<int64_t, int64_t>> images;
   double start = 0, strip_rows = 0;
-  void add(int kind, int64_t w, int64_t h) {
-    const int64_t strips = (w + strip_px(kind) - 1) / strip_px(kind);
-    images.push_back({strips, h});
-    start += (kind == FK_CORNER ? 2.5 : 1.5) * (double)(strips * h);
-    strip_rows += (double)(strips * h);
+  int waves = 4;  // that a SIMD runs at once: UYVY rows fill the LDS with half as many
+  void add(const Plan& p, const Group& g) {
+    const int64_t strips = (g.w + strip_px(g.kind) - 1) / strip_px(g.kind);
+    images.push_back({strips, g.h});
+    start += (g.kind == FK_CORNER ? 2.5 : 1.5) * (double)(strips * g.h);
+    strip_rows += (double)(strips * g.h);
+    if (g.kind == FK_GAUSS5 && p.vals[g.v_in].df == DF_UYVY) waves = 2;
   }
 };
 
 // Rows per work item.  With `w` waves to run on the fullest SIMD an item of
-// r rows and a start of s costs about (r + s)(w + 1) row issues while all
-// waves are resident (a wave alone takes about twice its issue) and
-// (r + s)(w + 2) beyond that (the last round is uneven); the least of it
-// over r weighs the halo rows of short items against the idle SIMDs of tall
-// ones, and lands on item counts just under a whole number of waves per SIMD.
+// r rows and a start of s costs about (r + s)(1.1 w + 1) row issues while all
+// waves are resident (a wave alone takes about twice its issue, and several
+// end unevenly) and (r + s)(w + 2) beyond that (the last round is uneven); the
+// least of it over r weighs the halo rows of short items against the idle
+// SIMDs of tall ones, and lands on item counts just under a whole number of
+// waves per SIMD.  Four waves a SIMD count as resident also where registers
+// leave room for more: eight 3840x2160 Harris frames take 86.5 us in 40 rows,
+// seven waves a SIMD, and 76.3 in 15.  UYVY counts two: eight 1920x1080 frames
+// 14.7 us in 6 rows, 11.4 in 9.
 // Against rows from a power-of-two rule of one image (4 items per CU), which
 // batches used too: one 3840x2160 frame edge + Phase 14.3 -> 9.3 us (8 -> 3
-// rows), Harris 33.2 -> 19.9 (32 -> 9), 640x480 edge + Phase 6.0 -> 3.6
-// (4 -> 1); 64 mixed images 266 -> 140 (2 to 32 rows each -> 17 for all),
+// rows), Harris 33.2 -> 17.9 (32 -> 9), 640x480 edge + Phase 6.0 -> 3.6
+// (4 -> 1); 64 mixed images 266 -> 136 (2 to 32 rows each -> 17 for all),
 // 32 1920x1080 UYVY frames 43 -> 34.
-static int pick_rows(const RowsFor& f, int64_t simds, int64_t resident) {
+static int pick_rows(const RowsFor& f, int num_cus) {
   if (f.images.empty() || f.strip_rows <= 0) return 4;
+  const int64_t simds = 4LL * (num_cus > 0 ? num_cus : 256);
   const double start = f.start / f.strip_rows;
   double best = 1e300;
   int rows = 4;
   for (int r = 1; r <= 64; ++r) {
     int64_t items = 0;
     for (const auto& i : f.images) items += i.first * ((i.second + r - 1) / r);
-    const double c = (r + start) * ((double)((items + simds - 1) / simds) + (items > resident ? 2 : 1));
+    const double w = (double)((items + simds - 1) / simds);
+    const double c = (r + start) * (items > f.waves * simds ? w + 2 : 1.1 * w + 1);
     if (c < best) {
       best = c;
       rows = r;
@@ -183,17 +191,16 @@ static int pick_rows(const RowsFor& f, int64_t simds, int64_t resident) {
   return rows;
 }
 
-int rows_together(const std::vector<const Group*>& groups, int num_cus, int waves_per_cu) {
+int rows_together(const std::vector<const Graph*>& graphs, int num_cus) {
   RowsFor f;
-  for (const Group* g : groups) f.add(g->kind, g->w, g->h);
-  return pick_rows(f, 4LL * num_cus, (int64_t)num_cus * waves_per_cu);
+  for (const Graph* g : graphs) f.add(*g->plan, g->plan->groups[0]);
+  return pick_rows(f, num_cus);
 }
 
-int default_rows(const Group& gr, int num_cus) {
+int default_rows(const Plan& p, const Group& gr, int num_cus) {
   RowsFor f;
-  f.add(gr.kind, gr.w, gr.h);
-  const int64_t simds = 4LL * (num_cus > 0 ? num_cus : 256);
-  return pick_rows(f, simds, 4 * simds);
+  f.add(p, gr);
+  return pick_rows(f, num_cus);
 }
 
 // The launch shape tuned for the graph, if any.  The key is only built when
@@ -208,7 +215,7 @@ static const TuneEntry* tuned_shape(const Graph* g) {
 int rows_for(const Graph* g, const Group& gr) {
   if (gr.rows > 0) return gr.rows;
   if (const TuneEntry* t = tuned_shape(g)) return t->rows;
-  return gr.own_rows > 0 ? gr.own_rows : default_rows(gr, g->ctx->num_cus);
+  return gr.own_rows > 0 ? gr.own_rows : default_rows(*g->plan, gr, g->ctx->num_cus);
 }
 
 static int xcd_for(const Graph* g, const Group& gr) {
@@ -506,18 +513,7 @@ static hvx_status batch_build(Batch* b) {
   }
   // the single launch's work items: rows as set for the batch, else as
   // pinned in a graph, else (several images) the rows that suit them together
-  int together = 0;
-  if (!b->rows_override && strips.size() > 1) {
-    std::vector<const Group*> groups;
-    int kinds = 0;
-    for (const Graph* g : strips) {
-      groups.push_back(&g->plan->groups[0]);
-      BatchImage bi;
-      fill_fast_desc(g, *groups.back(), &bi, 1);
-      kinds |= kind_bit(bi);
-    }
-    together = rows_together(groups, c->num_cus, batch_waves_per_cu(kinds));
-  }
+  const int together = !b->rows_override && strips.size() > 1 ? rows_together(strips, c->num_cus) : 0;
   for (const Graph* g : strips) {
     const Group& gr = g->plan->groups[0];
     BatchImage bi;

@@ -212,11 +212,11 @@ static bool launch_step(Server* sv, StreamSlot& sl, std::vector<Request*>& reqs)
                                         s) != hipSuccess)
           return false;
   auto in_step = [&](const Request* r) { return batchable(r->templ) && sv->mode == HVX_SERVER_CONTINUOUS; };
-  std::vector<const Group*> groups;
+  std::vector<const Graph*> graphs;
   for (const Request* r : live)
-    if (in_step(r)) groups.push_back(&r->templ->plan->groups[0]);
+    if (in_step(r)) graphs.push_back(r->templ);
   // one request alone: its own rows; several: rows that suit them together
-  const int rows = groups.size() > 1 ? rows_together(groups, sv->ctx->num_cus, 16) : 0;
+  const int rows = graphs.size() > 1 ? rows_together(graphs, sv->ctx->num_cus) : 0;
   StepImages imgs;  // sixteen images a launch
   int n = 0;
   for (Request* r : live) {
