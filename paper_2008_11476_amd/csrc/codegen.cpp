@@ -1,6 +1,10 @@
 // Kernels generated for fused groups: source emission, hipRTC compilation,
 // a process-wide cache of code objects and their launch.
 //
+// A group with a local operator is streamed in strips where it can be
+// (codegen_stream.cpp); groups of point operators take four pixels of a row
+// per thread; the rest, and tuned tiles, are the tile form written here.
+//
 // A generated tile kernel evaluates the group's operators in stages.  A
 // stage is a run of operators that need no barrier between them: each
 // thread sweeps the positions of the stage's extent and, at each position,
@@ -1133,9 +1137,9 @@ static bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSourc
   emit_prelude(t, P, can_stream ? "dev_stream.hpp" : "dev_generic.hpp", why, &ok);
   if (!ok) return false;
   // The streaming form is the faster one at every size measured, from
-  // 320x240 (Tomasi 15.2 against 8.0 us a frame) to 32 frames of 3840x2160
-  // (1305 against 515 us); small images of the graphs that a launch's fixed
-  // cost bounds take the same time either way.  A chosen tile asks for tiles.
+  // 320x240 (Tomasi 15.0 against 5.2 us a frame, Unsharp 5.5 against 3.3) to
+  // 32 frames of 3840x2160 (1305 against 331 us).  A chosen tile asks for
+  // tiles.
   const bool use_stream = can_stream && tw == 0;
   *out = use_stream ? strip : tiles;
   if (can_tile) t.s += can_stream ? "#ifndef HVX_GEN_STREAM_ONLY\n" + tiles.text + "#endif\n" : tiles.text;
@@ -1274,9 +1278,10 @@ int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int n
   // an item's start), shared by the SIMDs, plus about one item's latency at
   // the end, a step of a wave alone taking some 2.5 times its issue: the sum
   // is least at r^2 = 0.4 strip_rows (ext + 3) / SIMDs.  Measured: 1080p and
-  // smaller frames are fastest at 4 rows (Tomasi 14.5 us against 20.0 at 16),
-  // one 4K frame at 4 to 12, batches at 20 to 32 (32 4K frames: Tomasi
-  // 515 us at 32 rows, 647 at 4, 553 at 96).
+  // smaller frames are fastest at 4 to 8 rows (640x480 Tomasi 5.8 us against
+  // 11.7 at 16), one 4K frame at 4 to 12, batches at 20 to 48 (32 4K frames:
+  // Tomasi 327 us at 32 rows, 459 at 4, 335 at 96); over five graphs and six
+  // launches the rule is within 14% of the best rows, mostly within 5%.
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
   // a band holds the rows that its neighbours read and share (emit_geometry)
   const int shift = whole_heights ? 0 : k->th - 1;

@@ -6,9 +6,8 @@
 // these are constants: here the group's program is written out as HIP
 // source, compiled by hipRTC for the device's architecture and cached per
 // process, so a graph structure is compiled once however often it is
-// verified.  The generated kernel takes the same arguments as the
-// interpreter (the device copy of the program, for the image size and the
-// reduction epilogue, and the I/O table).
+// verified.  The generated kernel takes the I/O table and the image size, or
+// a batch's images.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -28,7 +27,7 @@ constexpr int kStreamRedWaves = 8;
 // Launch shape of a generated kernel.
 enum GenForm : int32_t {
   GEN_POINTS = 1,  // point operators only: four pixels of one row per thread, no LDS
-  GEN_TILES = 2,   // LDS tiles with halos; work-groups loop over tiles when the group reduces
+  GEN_TILES = 2,   // LDS tiles with halos: what GEN_STREAM does not cover; work-groups loop over tiles when the group reduces
   GEN_STREAM = 3,  // a wave streams a strip of columns down a band of rows, values in registers
 };
 
