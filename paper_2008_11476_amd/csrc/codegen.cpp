@@ -1265,12 +1265,6 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTa
   return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
-// bands of an image of a streamed kernel (as the kernel computes them)
-static int stream_bands(const GenKernel* k, int h, int rows) {
-  const int tail = (k->ext + k->th - 1) / k->th * k->th;
-  return h < tail + 2 * k->th ? 1 : (h - tail + ((tail - h) & (k->th - 1)) + rows - 1) / rows + (tail > 0);
-}
-
 int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int num_cus) {
   if (k->form != GEN_STREAM) return 0;
   // Bands of r rows cost strip_rows / r items of r + ext + 3 steps each (the
@@ -1283,7 +1277,7 @@ int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int n
   // Tomasi 327 us at 32 rows, 459 at 4, 335 at 96); over five graphs and six
   // launches the rule is within 14% of the best rows, mostly within 5%.
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
-  // a band holds the rows that its neighbours read and share (emit_geometry)
+  // a band holds the rows that its neighbours read and share (stream_bands)
   const int shift = whole_heights ? 0 : k->th - 1;
   const int least = std::max(1, (k->ext + shift + k->th - 1) / k->th);
   if (k->red) {
@@ -1308,7 +1302,7 @@ int gen_strips(const GenKernel* k, int w) { return k->form == GEN_STREAM ? (w + 
 
 long long gen_blocks(const GenKernel* k, int w, int h, int rows) {
   if (k->form == GEN_POINTS) return (long long)((w + 1023) >> 10) * h;
-  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * stream_bands(k, h, rows);
+  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * stream_bands(h, rows, stream_tail(k->ext)).n;
   return (long long)((w + k->tw - 1) / k->tw) * ((h + k->th - 1) / k->th);
 }
 

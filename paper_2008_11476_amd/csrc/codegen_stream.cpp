@@ -34,9 +34,7 @@
 namespace hvx {
 namespace {
 
-// Rows per loop iteration, of which all bands but the last are a multiple; the
-// next four rows are loaded while four are computed.
-constexpr int kUnroll = 4;
+constexpr int kUnroll = kStreamUnroll;
 
 struct Val {
   bool wide = false;       // S32 / F32: one register per pixel
@@ -212,7 +210,7 @@ struct Planner {
     }
     LP = any_wide ? 4 : 8;
     plan_slides();
-    T = (E + kUnroll - 1) / kUnroll * kUnroll;
+    T = stream_tail(E);
     int emax = 0;
     for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
     halo = (emax + LP - 1) / LP;
@@ -775,33 +773,20 @@ struct Planner {
   void emit_item() {
     const int out_lanes = 64 - 2 * halo;
     t("  const int strip = item %% strips, band = item / strips;");
-    if (T > 0) {
-      t("  const bool last = band + 1 == bands;");
-      t("  const int y0 = last ? H - %d : band > 0 ? band * rows - shift : 0, y1 = last ? y0 : min(y0 + rows, H - %d);", T, T);
-    } else {
-      t("  const bool last = false;");
-      t("  const int y0 = band > 0 ? band * rows - shift : 0, y1 = min(y0 + rows, H);");
-    }
+    t("  const StreamBand bn = stream_band(bd, band);");
     // inside the image: every pixel of every lane, every row the band reads
-    t("  if (bands > 1 && strip > 0 && (strip * %d + %d) * SX_LP <= W && band > 0 && !last)", out_lanes,
+    t("  if (bd.n > 1 && strip > 0 && (strip * %d + %d) * SX_LP <= W && band > 0 && !bn.last)", out_lanes,
       out_lanes + halo);
-    t("    sx_item<false>(red, io, W, H, strip, y0, y1, false, y1);");
-    t("  else if (bands > 1 && W >= 8)");
-    t("    sx_item<true>(red, io, W, H, strip, y0, y1, last, band > 0 ? y1 : rows - shift);");
+    t("    sx_item<false>(red, io, W, H, strip, bn.y0, bn.y1, false, bn.own);");
+    t("  else if (bd.n > 1 && W >= 8)");
+    t("    sx_item<true>(red, io, W, H, strip, bn.y0, bn.y1, bn.last, bn.own);");
     t("  else if (band == 0) sx_small(red, io, W, H, strip);");
   }
 
-  // The image's last T rows are a band of their own; the rows before them, up
-  // to a multiple of kUnroll by `shift`, are dealt out in bands of `rows`.  All
-  // bands but the first start `shift` rows early, so each holds a multiple of
-  // kUnroll rows; the first still starts at row 0 and computes the `shift`
-  // rows it shares with the second again.  `rows` is at least E + shift: only
-  // the first band reads rows above the image, only the last below it.  Images
-  // of a single band, or under eight columns, go row by row.
+  // (images under eight columns go row by row too)
   void emit_geometry(int strip_px) {
     t("  const int strips = (W + %d) / %d;", strip_px - 1, strip_px);
-    t("  const int shift = (%d - H) & %d, main_rows = H - %d + shift;", T, kUnroll - 1, T);
-    t("  const int bands = H < %d ? 1 : (main_rows + rows - 1) / rows%s;", T + 2 * kUnroll, T > 0 ? " + 1" : "");
+    t("  const StreamBands bd = stream_bands(H, rows, %d);", T);
   }
 
   void emit_entry() {
@@ -829,7 +814,7 @@ struct Planner {
     t("  }");
     const int strip_px = (64 - 2 * halo) * LP;
     emit_geometry(strip_px);
-    t("  if (item >= strips * bands) return;");
+    t("  if (item >= strips * bd.n) return;");
     t("  SxRed red;");
     emit_item();
     t("}");
@@ -865,7 +850,7 @@ struct Planner {
     t("  const int vb = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + b / 8;");
     const int strip_px = (64 - 2 * halo) * LP;
     emit_geometry(strip_px);
-    t("  const int items = strips * bands;");
+    t("  const int items = strips * bd.n;");
     t("  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));");
     t("  for (int item = vb * %d + wave; item < items; item += nb * %d) {", NT / 64, NT / 64);
     emit_item();

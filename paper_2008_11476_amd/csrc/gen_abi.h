@@ -5,7 +5,7 @@
 
 namespace hvx {
 
-// One image of a batch run by one generated kernel: its I/O table, its size
+// One image of a batch run by one generated kernel: its I/O table, its size,
 // the first work-group of the launch that works on it and the rows of its bands.
 struct GenBatchImage {
   IOTable io;
@@ -13,6 +13,45 @@ struct GenBatchImage {
   int32_t block0;
   int32_t rows;  // rows of a band (streamed kernels)
 };
+
+// Rows per loop iteration of a streamed kernel; the next four rows are loaded
+// while four are computed.
+constexpr int kStreamUnroll = 4;
+
+// How a streamed kernel's items divide an image of h rows, where an output row
+// reads up to `ext` rows above and below.  The image's last `tail` rows (ext,
+// up to a multiple of kStreamUnroll) are a band of their own; the rows before
+// them, up to a multiple of kStreamUnroll by `shift`, are dealt out in bands
+// of `rows`.  All bands but the first start `shift` rows early, so each holds
+// whole iterations; the first still starts at row 0 and computes the `shift`
+// rows it shares with the second again.  `rows` is at least ext + shift: only
+// the first band reads rows above the image, only the last below it.  n = 1:
+// the image goes row by row in one item; so does one whose rows before the
+// tail fit one band without being whole iterations, as that band can neither
+// start early nor run on into the tail's rows, which are not all loaded.
+struct StreamBands {
+  int32_t h, rows, tail, shift, n;
+};
+__host__ __device__ inline int stream_tail(int ext) {
+  return (ext + kStreamUnroll - 1) / kStreamUnroll * kStreamUnroll;
+}
+__host__ __device__ inline StreamBands stream_bands(int h, int rows, int tail) {
+  const int shift = (tail - h) & (kStreamUnroll - 1), main_rows = h - tail + shift;
+  const bool one = h < tail + 2 * kStreamUnroll || (shift > 0 && main_rows <= rows);
+  return {h, rows, tail, shift, one ? 1 : (main_rows + rows - 1) / rows + (tail > 0 ? 1 : 0)};
+}
+// Band `band` of several: output rows [y0, y1) (`last`: the image's last rows
+// follow), of which those from `own` on are the next band's to count.
+struct StreamBand {
+  int32_t y0, y1, own;
+  bool last;
+};
+__host__ __device__ inline StreamBand stream_band(const StreamBands& b, int band) {
+  const bool last = b.tail > 0 && band + 1 == b.n;
+  const int y0 = last ? b.h - b.tail : band > 0 ? band * b.rows - b.shift : 0;
+  const int y1 = last ? y0 : y0 + b.rows < b.h - b.tail ? y0 + b.rows : b.h - b.tail;
+  return {y0, y1, band > 0 || b.rows - b.shift > y1 ? y1 : b.rows - b.shift, last};
+}
 
 // Partial results of one work-group of a generated kernel that reduces
 // global operators: for each of its reduce operators in program order, a
