@@ -1251,7 +1251,7 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTa
   // the CUs measured slower: the hardware's own dispatch of short groups
   // overlaps one group's loads with another's arithmetic as well).  A
   // group that reduces writes its partial results to its slot of `ws`.
-  int rows = gen_rows(k, (long long)gen_strips(k, P.w) * P.h, P.h % 4 == 0, num_cus);
+  int rows = gen_rows(k, P.w, P.h, (long long)gen_strips(k, P.w) * P.h, P.h % 4 == 0, num_cus);
   const long long grid = gen_slots(k, P.w, P.h, num_cus);
   if (grid <= 0) return hipSuccess;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -1265,8 +1265,9 @@ hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTa
   return hipModuleLaunchKernel(k->fn[device], (unsigned)grid, 1, 1, gen_threads(k), 1, 1, 0, s, args, nullptr);
 }
 
-int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int num_cus) {
-  if (k->form != GEN_STREAM) return 0;
+// Rows of a band where one launch runs strips of the given total height: a
+// multiple of `unit`, and at least `least`.
+static int band_rows(const GenKernel* k, long long strip_rows, int unit, int least, int num_cus) {
   // Bands of r rows cost strip_rows / r items of r + ext + 3 steps each (the
   // steps before the first output row run part of the operators; 3 stand for
   // an item's start), shared by the SIMDs, plus about one item's latency at
@@ -1277,15 +1278,12 @@ int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int n
   // Tomasi 327 us at 32 rows, 459 at 4, 335 at 96); over five graphs and six
   // launches the rule is within 14% of the best rows, mostly within 5%.
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
-  // a band holds the rows that its neighbours read and share (stream_bands)
-  const int shift = whole_heights ? 0 : k->th - 1;
-  const int least = std::max(1, (k->ext + shift + k->th - 1) / k->th);
   if (k->red) {
     // the waves of a reducing kernel go on from item to item: whole rounds of
     // the waves that run at once, of short bands
-    int best = least * k->th;
+    int best = least;
     double cost = 1e300;
-    for (int r = best; r <= 64; r += k->th) {
+    for (int r = best; r <= 64; r += unit) {
       const double c = ceil((double)strip_rows / r / (4 * simds)) * (r + k->ext + 3);
       if (c < cost) {
         cost = c;
@@ -1295,19 +1293,29 @@ int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int n
     return best;
   }
   const double r = sqrt(0.4 * (double)strip_rows * (k->ext + 3) / simds);
-  return std::min(std::max((int)(r / k->th + 0.5), least), 32 / k->th) * k->th;
+  return std::min(std::max((int)(r / unit + 0.5) * unit, least), 32);
+}
+
+int gen_rows(const GenKernel* k, int w, int h, long long strip_rows, bool whole_heights, int num_cus) {
+  if (k->form != GEN_STREAM) return 0;
+  // a band of whole iterations holds the rows that its neighbours read and
+  // share; one that goes row by row need not
+  const int shift = whole_heights ? 0 : k->th - 1;
+  const int least = std::max(1, (k->ext + shift + k->th - 1) / k->th) * k->th;
+  const int rows = band_rows(k, strip_rows, k->th, least, num_cus);
+  return stream_bands(w, h, rows, k->ext).whole ? rows : band_rows(k, strip_rows, 1, 1, num_cus);
 }
 
 int gen_strips(const GenKernel* k, int w) { return k->form == GEN_STREAM ? (w + k->tw - 1) / k->tw : 0; }
 
 long long gen_blocks(const GenKernel* k, int w, int h, int rows) {
   if (k->form == GEN_POINTS) return (long long)((w + 1023) >> 10) * h;
-  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * stream_bands(h, rows, stream_tail(k->ext)).n;
+  if (k->form == GEN_STREAM) return (long long)gen_strips(k, w) * stream_bands(w, h, rows, k->ext).n;
   return (long long)((w + k->tw - 1) / k->tw) * ((h + k->th - 1) / k->th);
 }
 
 long long gen_slots(const GenKernel* k, int w, int h, int num_cus) {
-  const long long n = gen_blocks(k, w, h, gen_rows(k, (long long)gen_strips(k, w) * h, h % 4 == 0, num_cus));
+  const long long n = gen_blocks(k, w, h, gen_rows(k, w, h, (long long)gen_strips(k, w) * h, h % 4 == 0, num_cus));
   // a streamed kernel that reduces: groups of eight items' waves, at most two
   // a CU, each going on to further items
   if (k->form != GEN_STREAM || !k->red) return n;

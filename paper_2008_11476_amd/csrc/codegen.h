@@ -60,11 +60,11 @@ hipError_t gen_load(const GenKernel* k, int device);
 hipError_t gen_launch(const GenKernel* k, int device, const GProg& P, const IOTable& io, int num_cus,
                       hipStream_t s, uint32_t* ws);
 
-// Strips of an image of the given width, and the rows of a band where one
-// launch runs strips of the given total height (0 for the other forms);
-// whole_heights: every image's height is a multiple of 4.
+// Strips of an image of the given width, and the rows of a band of a w x h
+// image where one launch runs strips of the given total height (0 for the
+// other forms); whole_heights: every image's height is a multiple of 4.
 int gen_strips(const GenKernel* k, int w);
-int gen_rows(const GenKernel* k, long long strip_rows, bool whole_heights, int num_cus);
+int gen_rows(const GenKernel* k, int w, int h, long long strip_rows, bool whole_heights, int num_cus);
 
 // Work-groups the kernel launches for one w x h image when run over a batch
 // (one per tile, one per 1024 pixels of a row for the point form, one per

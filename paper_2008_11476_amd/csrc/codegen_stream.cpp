@@ -210,7 +210,7 @@ struct Planner {
     }
     LP = any_wide ? 4 : 8;
     plan_slides();
-    T = stream_tail(E);
+    T = stream_bands(8, 0, kUnroll, E).tail;
     int emax = 0;
     for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
     halo = (emax + LP - 1) / LP;
@@ -756,15 +756,15 @@ struct Planner {
     }
     t("}");
     // any size: row by row, every rule decided as it goes
-    t("__device__ __forceinline__ void sx_small(SxRed& red, const IOTable& io, int W, int H, int strip) {");
+    t("__device__ __forceinline__ void sx_small(SxRed& red, const IOTable& io, int W, int H, int strip, int y0, int y1) {");
     emit_strip_setup(ins, true);
-    t("  for (int t = -%d; t < H; ++t) {", 2 * E);
+    t("  for (int t = y0 - %d; t < y1; ++t) {", 2 * E);
     std::string a;
     for (int i : ins) {
       t("    const Raw<%d> x%d = ld%d(t + %d, H + %d);", raw_bytes(i), i, i, P.vals[i].ext, 2 * E + 1);
       a += fmt(", x%d", i);
     }
-    t("    sx_step<%d, kAny, true>(st, red, g, io, off, t, 0, H%s);", 2 * E, a.c_str());
+    t("    sx_step<%d, kAny, true>(st, red, g, io, off, t, y0, y1%s);", 2 * E, a.c_str());
     t("  }");
     t("}");
   }
@@ -775,18 +775,17 @@ struct Planner {
     t("  const int strip = item %% strips, band = item / strips;");
     t("  const StreamBand bn = stream_band(bd, band);");
     // inside the image: every pixel of every lane, every row the band reads
-    t("  if (bd.n > 1 && strip > 0 && (strip * %d + %d) * SX_LP <= W && band > 0 && !bn.last)", out_lanes,
+    t("  if (bd.whole && strip > 0 && (strip * %d + %d) * SX_LP <= W && band > 0 && !bn.last)", out_lanes,
       out_lanes + halo);
     t("    sx_item<false>(red, io, W, H, strip, bn.y0, bn.y1, false, bn.own);");
-    t("  else if (bd.n > 1 && W >= 8)");
+    t("  else if (bd.whole)");
     t("    sx_item<true>(red, io, W, H, strip, bn.y0, bn.y1, bn.last, bn.own);");
-    t("  else if (band == 0) sx_small(red, io, W, H, strip);");
+    t("  else sx_small(red, io, W, H, strip, bn.y0, bn.y1);");
   }
 
-  // (images under eight columns go row by row too)
   void emit_geometry(int strip_px) {
     t("  const int strips = (W + %d) / %d;", strip_px - 1, strip_px);
-    t("  const StreamBands bd = stream_bands(H, rows, %d);", T);
+    t("  const StreamBands bd = stream_bands(W, H, rows, %d);", E);
   }
 
   void emit_entry() {

@@ -759,7 +759,7 @@ __device__ __forceinline__ void hist_add(uint32_t* mine, int v, bool in) {
 }
 __device__ __forceinline__ void sums_add(RedSlot& q, int v, bool in) {
   const uint32_t x = in ? (uint32_t)v : 0u;
-  q.cmn += x;  // 32-bit sums of one band, widened at its end (sums_wrap)
+  q.cmn += x;  // 32-bit sums of one band (at most 64 rows of 8 pixels), widened at its end (sums_wrap)
   q.cmx += __umul24(x, x);
 }
 __device__ __forceinline__ void sums_wrap(RedSlot& q) {

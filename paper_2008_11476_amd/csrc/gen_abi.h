@@ -19,38 +19,48 @@ struct GenBatchImage {
 constexpr int kStreamUnroll = 4;
 
 // How a streamed kernel's items divide an image of h rows, where an output row
-// reads up to `ext` rows above and below.  The image's last `tail` rows (ext,
-// up to a multiple of kStreamUnroll) are a band of their own; the rows before
-// them, up to a multiple of kStreamUnroll by `shift`, are dealt out in bands
-// of `rows`.  All bands but the first start `shift` rows early, so each holds
-// whole iterations; the first still starts at row 0 and computes the `shift`
-// rows it shares with the second again.  `rows` is at least ext + shift: only
-// the first band reads rows above the image, only the last below it.  n = 1:
-// the image goes row by row in one item; so does one whose rows before the
-// tail fit one band without being whole iterations, as that band can neither
-// start early nor run on into the tail's rows, which are not all loaded.
+// reads up to `ext` rows above and below.
+//
+// whole: the image's last `tail` rows (ext, up to a multiple of kStreamUnroll)
+// are a band of their own; the rows before them, up to a multiple of
+// kStreamUnroll by `shift`, are dealt out in bands of `rows`.  All bands but
+// the first start `shift` rows early, so each holds whole iterations; the
+// first still starts at row 0 and computes the `shift` rows it shares with the
+// second again.  Only the first band reads rows above the image, only the last
+// below it.
+//
+// Otherwise every band goes row by row, each border rule decided as it goes:
+// images under eight columns, images too low for two such bands, `rows` that
+// are no whole iterations or below ext + shift, and a single band before the
+// tail that is not whole iterations, as it can neither start early nor run on
+// into the tail's rows, which are not all loaded.  A wave takes 0.4 to 1 us
+// for a row so, and 2 ext rows before its first: 7x4096 Unsharp 1502 us as one
+// item, 6.9 in bands (tiles 7.4), the F32 corner response 2513 and 13.1
+// (15.4), four Gaussian5x5 4003 and 24.9 (20.9); 640x19, three Gaussian5x5
+// 20.2 and 12.1 (13.6).
 struct StreamBands {
   int32_t h, rows, tail, shift, n;
+  bool whole;
 };
-__host__ __device__ inline int stream_tail(int ext) {
-  return (ext + kStreamUnroll - 1) / kStreamUnroll * kStreamUnroll;
-}
-__host__ __device__ inline StreamBands stream_bands(int h, int rows, int tail) {
+__host__ __device__ inline StreamBands stream_bands(int w, int h, int rows, int ext) {
+  const int tail = (ext + kStreamUnroll - 1) / kStreamUnroll * kStreamUnroll;
   const int shift = (tail - h) & (kStreamUnroll - 1), main_rows = h - tail + shift;
-  const bool one = h < tail + 2 * kStreamUnroll || (shift > 0 && main_rows <= rows);
-  return {h, rows, tail, shift, one ? 1 : (main_rows + rows - 1) / rows + (tail > 0 ? 1 : 0)};
+  const bool whole = w >= 8 && h >= tail + 2 * kStreamUnroll && rows % kStreamUnroll == 0 && rows >= ext + shift &&
+                     (shift == 0 || main_rows > rows);
+  return {h, rows, tail, shift, ((whole ? main_rows : h) + rows - 1) / rows + (whole && tail > 0 ? 1 : 0), whole};
 }
-// Band `band` of several: output rows [y0, y1) (`last`: the image's last rows
-// follow), of which those from `own` on are the next band's to count.
+// Band `band`: output rows [y0, y1) (`last`: the image's last rows follow), of
+// which those from `own` on are the next band's to count.
 struct StreamBand {
   int32_t y0, y1, own;
   bool last;
 };
 __host__ __device__ inline StreamBand stream_band(const StreamBands& b, int band) {
-  const bool last = b.tail > 0 && band + 1 == b.n;
-  const int y0 = last ? b.h - b.tail : band > 0 ? band * b.rows - b.shift : 0;
-  const int y1 = last ? y0 : y0 + b.rows < b.h - b.tail ? y0 + b.rows : b.h - b.tail;
-  return {y0, y1, band > 0 || b.rows - b.shift > y1 ? y1 : b.rows - b.shift, last};
+  const bool last = b.whole && b.tail > 0 && band + 1 == b.n;
+  const int end = b.whole ? b.h - b.tail : b.h, shift = b.whole && band > 0 ? b.shift : 0;
+  const int y0 = last ? end : band * b.rows - shift, y1 = last ? y0 : y0 + b.rows < end ? y0 + b.rows : end;
+  const int next = (band + 1) * b.rows - (b.whole ? b.shift : 0);  // the next band's first row
+  return {y0, y1, next < y1 ? next : y1, last};
 }
 
 // Partial results of one work-group of a generated kernel that reduces

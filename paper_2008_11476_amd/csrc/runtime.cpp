@@ -564,7 +564,7 @@ static hvx_status batch_build(Batch* b) {
           im.w = gr.prog.w;
           im.h = gr.prog.h;
           im.block0 = (int32_t)set.blocks;
-          im.rows = gen_rows(set.k, strip_rows, whole_heights, c->num_cus);
+          im.rows = gen_rows(set.k, im.w, im.h, strip_rows, whole_heights, c->num_cus);
           set.blocks += gen_blocks(set.k, gr.prog.w, gr.prog.h, im.rows);
           if (set.blocks > 0x7FFFFFFF) return set_error(c, HVX_ERROR_NOT_SUPPORTED, "batch launch too large");
           set.imgs.push_back(im);

@@ -1,10 +1,12 @@
 """GPU parity of streamed kernels on images hardly taller than the rows their
 operators reach: single frames at and around the heights where the rows
 before the tail band fit one band, and such images in one launch with large
-ones, whose bands are tall.  Bit for bit the tile interpreter's results."""
+ones, whose bands are tall; and on images narrower than a lane, which go row
+by row in bands.  Bit for bit the tile interpreter's results."""
 import numpy as np
 import pytest
 
+import oracle
 import paper_2008_11476_amd as hvx
 import synth
 from tests import graphspec as gs
@@ -12,6 +14,8 @@ from tests.gpu_util import compare, log, run_spec
 from tests.test_gpu_codegen import _fchain, _tomasi
 from tests.test_gpu_custom import unsharp_spec
 from tests.test_gpu_global_graph import _check_buffers
+from tests.test_gpu_slide import _read_again
+from tests.test_gpu_stream import _response, _thin, _two_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -105,3 +109,44 @@ def test_short_images_beside_large_ones(ctx, graph, big, frames):
     hvx.hvx_release_batch(b)
     for g in graphs:
         hvx.hvx_release_graph(g)
+
+
+ROW_BY_ROW = {"thin": _thin, "response": _response, "two_inputs": _two_inputs, "fchain": _fchain, "read_again": _read_again,
+              "four5": lambda img, border: _chain(img, CHAINS["four5"], border)}
+
+
+@pytest.mark.parametrize("border", [("replicate", 0), ("mirror", 0), ("constant", 77), ("undefined", 0)], ids=lambda b: b[0])
+@pytest.mark.parametrize("graph", list(ROW_BY_ROW))
+def test_bands_of_single_rows(ctx, graph, border):
+    """Narrow images of several bands, and low ones of one to three."""
+    sizes = [(1, 75), (2, 501), (3, 38), (5, 130), (7, 1026)] + [(w, h) for h in range(1, 14) for w in (8, 1003)]
+    for w, h in sizes:
+        spec = ROW_BY_ROW[graph](synth.edge_image(w, h, seed=w + h), border)
+        log("row by row %s %s %dx%d" % (graph, border[0], w, h))
+        got, g = run_spec(spec, ctx, specialize=False)
+        assert _streamed(g)
+        ref, _ = run_spec(spec, ctx, specialize=False, codegen=False)
+        valid = oracle.valid_masks(spec.oracle_graph(), spec.shapes())
+        for out in spec.outputs:
+            a, b = got[out], ref[out]
+            if a.dtype == np.float32:
+                a, b = a.view(np.uint32), b.view(np.uint32)
+            bad = (a != b) & valid[out]
+            assert not bad.any(), "%s differs at %dx%d, first at (y, x) = %s" % (
+                out, w, h, tuple(int(i[0]) for i in np.nonzero(bad)))
+
+
+@pytest.mark.parametrize("w,h", [(1, 65536), (2, 40000), (3, 65535), (7, 9435), (7, 20000), (8, 20000)])
+def test_sums_of_bright_narrow_images(ctx, w, h):
+    """Sums of squares past 32 bits in one column of lanes: 65025 a pixel."""
+    spec = gs.Spec([gs.N("gaussian3x3", ["in"], ["g"]), gs.N("mean_std_dev", ["g"], ["sums"]),
+                    gs.N("histogram", ["g"], ["bins"], params={"bins": 256})],
+                   {"in": np.full((h, w), 255, np.uint8)}, {}, buffers={"sums": 64, "bins": 1024})
+    log("bright %dx%d" % (w, h))
+    got, g = run_spec(spec, ctx)
+    assert _streamed(g)
+    s1, s2 = got["sums"].view(np.uint64)[:2].tolist()
+    assert (s1, s2) == (255 * w * h, 65025 * w * h)
+    mean, std = got["sums"].view(np.float32)[4:6].tolist()
+    assert (mean, std) == (255.0, 0.0)
+    assert got["bins"].view(np.uint32)[:256].tolist() == [0] * 255 + [w * h]

@@ -1,7 +1,8 @@
 """Host-side test of how a streamed kernel divides an image's rows (gen_abi.h,
 the code that the kernels and the host both run): every band holds whole loop
 iterations, only the first reads rows above the image and only the last below
-it, and the bands count every row once."""
+it, and the bands count every row once; images that cannot be divided so go
+row by row, in bands of no more rows than asked for."""
 import os
 import shutil
 import subprocess
@@ -24,12 +25,24 @@ int main() {
   };
   for (int ext = 0; ext <= 8; ++ext)
     for (int h = 1; h <= 140; ++h) {
-      const int tail = stream_tail(ext), shift = (tail - h) & (kStreamUnroll - 1);
-      for (int rows = kStreamUnroll; rows <= 64; rows += kStreamUnroll) {
-        if (rows < ext + shift) continue;
-        const StreamBands b = stream_bands(h, rows, tail);
+      const int tail = stream_bands(8, h, kStreamUnroll, ext).tail;
+      if (tail < ext || tail % kStreamUnroll) fail(h, ext, 0, 0, "tail");
+      for (int rows = 1; rows <= 64; ++rows) {
+        for (int w : {1, 7}) {  // narrow images: row by row, in bands all the same
+          const StreamBands b = stream_bands(w, h, rows, ext);
+          if (b.whole || b.n != (h + rows - 1) / rows) fail(h, ext, rows, b.n, "a narrow image");
+        }
+        const StreamBands b = stream_bands(8, h, rows, ext);
         if (b.n < 1) fail(h, ext, rows, 0, "no band");
-        if (b.n <= 1) continue;
+        if (!b.whole) {
+          for (int k = 0, y = 0; k < b.n; ++k) {
+            const StreamBand q = stream_band(b, k);
+            if (q.last || q.y0 != y || q.y1 <= y || q.y1 > y + rows || q.own != q.y1 || (k + 1 == b.n) != (q.y1 == h))
+              fail(h, ext, rows, k, "a band of single rows");
+            y = q.y1;
+          }
+          continue;
+        }
         ++several;
         std::vector<int> counted(h, 0);
         for (int k = 0; k < b.n; ++k) {
