@@ -1067,7 +1067,28 @@ bool emit_tiles(const GProg& P, int tw_req, int th_req, uint32_t stream, GenSour
   t("    else gen_tile<false>(io, W, H, tx0, ty0, L%s);", red ? ", rs" : "");
   t("    __syncthreads();  // the tile's LDS is free for the next tile");
   t("  }");
-  if (red) t("  red_end_partial<%d>(*P, rs, ws + (size_t)slot * %d);", kGenThreads, red_slot_words(P));
+  if (red) {
+    // the operators' partial results (the loop's last barrier has completed
+    // the histogram)
+    t("  __shared__ unsigned long long part[2][%d];", kGenThreads / 64);
+    t("  uint32_t* const res = ws + (size_t)slot * %d;", red_slot_words(P));
+    int n = 0, off = 0;
+    for (int k = 0; k < P.nops; ++k) {
+      const GOp& o = P.ops[k];
+      if (!is_reduce_op(o.kind)) continue;
+      if (o.kind == OP_HISTOGRAM || o.kind == OP_EQHIST) {
+        t("  for (int i = (int)threadIdx.x; i < %d; i += %d) {", o.p0, kGenThreads);
+        t("    uint32_t c = 0;");
+        t("    for (int h = 0; h < rs.copies; ++h) c += rs.hist0[h * kHistWords + i];");
+        t("    res[%d + i] = c;", off);
+        t("  }");
+      } else {
+        t("  red_store<%d, %d>(rs.%s, part, res + %d);", o.kind, kGenThreads, n == 0 ? "a" : "b", off);
+      }
+      off += red_block_words(o.kind, o.p0);
+      ++n;
+    }
+  }
   t("}");
   out->text = t.s;
   out->form = GEN_TILES;

@@ -649,86 +649,49 @@ __device__ __forceinline__ void red_end(const GProg& P, const IOTable& io, RedSt
   }
 }
 
-// As red_end, but the group writes its partial results to its own slot of
-// a workspace (red_slot_words(P) words) instead of merging them into the
-// results: a second kernel merges the slots (launch_merge_partials).
-template <int NT>
-__device__ __forceinline__ void red_end_partial(const GProg& P, RedState& r, uint32_t* slot) {
-  __shared__ unsigned long long part[2][NT / 64];
-  const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-  __syncthreads();  // the LDS histogram is complete
-  int k = 0, off = 0;
-  for (int oi = 0; oi < P.nops; ++oi) {
-    const GOp& o = P.ops[oi];
-    if (!is_reduce_op(o.kind)) continue;
-    if (o.kind == OP_HISTOGRAM || o.kind == OP_EQHIST) {
-      for (int b = t; b < o.p0; b += NT) {
-        uint32_t c = 0;
-        for (int h = 0; h < r.copies; ++h) c += r.hist0[h * kHistWords + b];
-        slot[off + b] = c;
-      }
-    } else {
-      RedSlot q;
-      r.with(k, [&](RedSlot& x) { q = x; });
-      int mn = q.mn, mx = q.mx;
-      uint32_t cmn = q.cmn, cmx = q.cmx;
-      unsigned long long s1 = q.s1, s2 = q.s2;
-      if (o.kind == OP_SUMS) {
+// A generated kernel's group writes its partial result of an operator to its
+// slot of a workspace (the layout of red_slot_words) instead of merging it into
+// the result: a second kernel forms the results from the slots
+// (launch_finish_partials).  `part` holds two words per wave.
+template <int KIND, int NT>
+__device__ __forceinline__ void red_store(const RedSlot& q, unsigned long long (&part)[2][NT / 64], uint32_t* slot) {
+  unsigned long long a, b;
+  int mn = q.mn, mx = q.mx;
+  uint32_t cmn = q.cmn, cmx = q.cmx;
+  if constexpr (KIND == OP_SUMS) {
+    a = q.s1;
+    b = q.s2;
+  } else if constexpr (KIND == OP_MINMAX) {
+    a = (unsigned)mn;
+    b = (unsigned)mx;
+  } else {
+    wave_merge_extremes(mn, cmn, mx, cmx);
+    a = cmn ? mm_key(mn, cmn) : kMinKeyInit;
+    b = cmx ? mm_key(mx, cmx) : kMaxKeyInit;
+  }
+  if constexpr (KIND != OP_MMCOUNT) {
 #pragma unroll
-        for (int sh = 32; sh > 0; sh >>= 1) {
-          s1 += __shfl_xor(s1, sh);
-          s2 += __shfl_xor(s2, sh);
-        }
-      } else if (o.kind == OP_MINMAX) {
-#pragma unroll
-        for (int sh = 32; sh > 0; sh >>= 1) {
-          mn = min(mn, __shfl_xor(mn, sh));
-          mx = max(mx, __shfl_xor(mx, sh));
-        }
-      } else {
-        wave_merge_extremes(mn, cmn, mx, cmx);
-      }
-      if (lane == 0) {
-        if (o.kind == OP_SUMS) {
-          part[0][wv] = s1;
-          part[1][wv] = s2;
-        } else if (o.kind == OP_MINMAX) {
-          part[0][wv] = (unsigned long long)(unsigned)mn;
-          part[1][wv] = (unsigned long long)(unsigned)mx;
-        } else {
-          part[0][wv] = cmn ? mm_key(mn, cmn) : kMinKeyInit;
-          part[1][wv] = cmx ? mm_key(mx, cmx) : kMaxKeyInit;
-        }
-      }
-      __syncthreads();
-      if (t == 0) {
-        unsigned long long a = part[0][0], b = part[1][0];
-        for (int w = 1; w < NT / 64; ++w) {
-          if (o.kind == OP_SUMS) {
-            a += part[0][w];
-            b += part[1][w];
-          } else if (o.kind == OP_MINMAX) {
-            a = (unsigned long long)(unsigned)min((int)(unsigned)a, (int)(unsigned)part[0][w]);
-            b = (unsigned long long)(unsigned)max((int)(unsigned)b, (int)(unsigned)part[1][w]);
-          } else {
-            a = mm_merge(a, part[0][w], true);
-            b = mm_merge(b, part[1][w], false);
-          }
-        }
-        if (o.kind == OP_MINMAX) {
-          slot[off] = (uint32_t)a;
-          slot[off + 1] = (uint32_t)b;
-        } else {
-          slot[off] = (uint32_t)a;
-          slot[off + 1] = (uint32_t)(a >> 32);
-          slot[off + 2] = (uint32_t)b;
-          slot[off + 3] = (uint32_t)(b >> 32);
-        }
-      }
-      __syncthreads();
+    for (int off = 32; off > 0; off >>= 1) {
+      red_merge(KIND, a, b, __shfl_xor(a, off), __shfl_xor(b, off));
     }
-    off += red_block_words(o.kind, o.p0);
-    ++k;
+  }
+  __syncthreads();  // `part` is free
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = a;
+    part[1][threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NT / 64; ++w) red_merge(KIND, a, b, part[0][w], part[1][w]);
+    if constexpr (KIND == OP_MINMAX) {
+      slot[0] = (uint32_t)a;
+      slot[1] = (uint32_t)b;
+    } else {
+      slot[0] = (uint32_t)a;
+      slot[1] = (uint32_t)(a >> 32);
+      slot[2] = (uint32_t)b;
+      slot[3] = (uint32_t)(b >> 32);
+    }
   }
 }
 

@@ -786,50 +786,6 @@ __device__ __forceinline__ RedSlot red_slot() {
   q.s1 = q.s2 = 0;
   return q;
 }
-// The group's result of one operator, to its slot (the layout of
-// red_slot_words); `part` holds two words per wave.
-template <int KIND, int NT>
-__device__ __forceinline__ void red_store(const RedSlot& q, unsigned long long (&part)[2][NT / 64], uint32_t* slot) {
-  unsigned long long a, b;
-  int mn = q.mn, mx = q.mx;
-  uint32_t cmn = q.cmn, cmx = q.cmx;
-  if constexpr (KIND == OP_SUMS) {
-    a = q.s1;
-    b = q.s2;
-  } else if constexpr (KIND == OP_MINMAX) {
-    a = (unsigned)mn;
-    b = (unsigned)mx;
-  } else {
-    wave_merge_extremes(mn, cmn, mx, cmx);
-    a = cmn ? mm_key(mn, cmn) : kMinKeyInit;
-    b = cmx ? mm_key(mx, cmx) : kMaxKeyInit;
-  }
-  if constexpr (KIND != OP_MMCOUNT) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      red_merge(KIND, a, b, __shfl_xor(a, off), __shfl_xor(b, off));
-    }
-  }
-  __syncthreads();  // `part` is free
-  if ((threadIdx.x & 63) == 0) {
-    part[0][threadIdx.x >> 6] = a;
-    part[1][threadIdx.x >> 6] = b;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < NT / 64; ++w) red_merge(KIND, a, b, part[0][w], part[1][w]);
-    if constexpr (KIND == OP_MINMAX) {
-      slot[0] = (uint32_t)a;
-      slot[1] = (uint32_t)b;
-    } else {
-      slot[0] = (uint32_t)a;
-      slot[1] = (uint32_t)(a >> 32);
-      slot[2] = (uint32_t)b;
-      slot[3] = (uint32_t)(b >> 32);
-    }
-  }
-}
-
 // Window of wide rows around pixel q, for operators evaluated pixel by pixel.
 template <int LP, int RX, int RY>
 struct RowsRd {
