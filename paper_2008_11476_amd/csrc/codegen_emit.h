@@ -19,33 +19,31 @@ struct GenSource {
   int lds_words = 0;   // static LDS of one work-group
 };
 
+inline std::string vfmt(const char* f, va_list ap) {
+  va_list again;
+  va_copy(again, ap);
+  const int n = vsnprintf(nullptr, 0, f, again);
+  va_end(again);
+  std::string s(n > 0 ? n : 0, '\0');
+  if (n > 0) vsnprintf(&s[0], (size_t)n + 1, f, ap);
+  return s;
+}
 inline std::string fmt(const char* f, ...) __attribute__((format(printf, 1, 2)));
 inline std::string fmt(const char* f, ...) {
-  char buf[512];
   va_list ap;
   va_start(ap, f);
-  vsnprintf(buf, sizeof buf, f, ap);
+  std::string s = vfmt(f, ap);
   va_end(ap);
-  return buf;
+  return s;
 }
 
 struct Text {
   std::string s;
-  void operator()(const char* fmt, ...) __attribute__((format(printf, 2, 3))) {
-    char buf[1024];
+  void operator()(const char* f, ...) __attribute__((format(printf, 2, 3))) {
     va_list ap;
-    va_start(ap, fmt);
-    int n = vsnprintf(buf, sizeof buf, fmt, ap);
+    va_start(ap, f);
+    s += vfmt(f, ap);
     va_end(ap);
-    if (n >= (int)sizeof buf) {
-      std::vector<char> big(n + 1);
-      va_start(ap, fmt);
-      vsnprintf(big.data(), big.size(), fmt, ap);
-      va_end(ap);
-      s += big.data();
-    } else {
-      s += buf;
-    }
     s += '\n';
   }
 };

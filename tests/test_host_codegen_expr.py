@@ -1,0 +1,35 @@
+"""Host-side test: user kernels of every length up to the longest are
+generated.  The expression written for two 16-bit pixels at a time names a
+window pixel in 14 characters and repeats the argument of abs(), so the longest
+ones pass several hundred characters."""
+import os
+
+import pytest
+
+import paper_2008_11476_amd as hvx
+from tests.expr_cases import long_expressions
+
+FAKE = 0x7f0000000000  # 16-byte aligned, never dereferenced here
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not os.path.exists(hvx.LIB_PATH):
+        from paper_2008_11476_amd import build
+        build.build()
+    c = hvx.hvx_context_create(0)
+    yield c
+    hvx.hvx_context_release(c)
+
+
+@pytest.mark.parametrize("terms", range(8, 14))
+def test_long_user_kernels_are_generated(ctx, terms):
+    for expr in long_expressions(terms):
+        g = hvx.hvx_graph_create(ctx)
+        a, o = (hvx.hvx_image_from_ptr(ctx, 640, 480, hvx.HVX_DF_U8, FAKE + k * (1 << 28), 640) for k in range(2))
+        v = hvx.hvx_image_create_virtual(g)
+        hvx.hvx_gaussian3x3_node(g, a, v)
+        hvx.hvx_custom_local_node(g, expr, v, hvx.HVX_DF_U8, o)
+        hvx.hvx_graph_verify(g)
+        assert hvx.hvx_graph_query(g, hvx.HVX_QUERY_NUM_GENERATED) == 1, expr
+        hvx.hvx_release_graph(g)
