@@ -1146,8 +1146,9 @@ static bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSourc
     any_red |= is_reduce_op(kind);
   }
   if (!any_local && !any_red) return emit_points(P, stream, out, why);
-  // One source holds the forms the group can take; the kernel compiled from
-  // it is the tile form, or with HVX_GEN_STREAM_ONLY defined the streaming one.
+  // One source holds the forms the group can take; a kernel is compiled from it
+  // with HVX_GEN_TILES or HVX_GEN_STREAM_ONLY defined, which leaves out the
+  // other form.
   GenSource strip, tiles;
   std::string no_strip;
   const bool can_stream = emit_stream(P, stream, &strip, &no_strip);
@@ -1164,7 +1165,7 @@ static bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSourc
   const bool use_stream = can_stream && tw == 0;
   *out = use_stream ? strip : tiles;
   if (can_tile) t.s += can_stream ? "#ifndef HVX_GEN_STREAM_ONLY\n" + tiles.text + "#endif\n" : tiles.text;
-  if (can_stream) t.s += strip.text;
+  if (can_stream) t.s += can_tile ? "#ifndef HVX_GEN_TILES\n" + strip.text + "#endif\n" : strip.text;
   out->text = t.s;
   return true;
 }
