@@ -634,9 +634,10 @@ __device__ __forceinline__ int magnitude_of(uint32_t s) {
   return (int)min(m, 32767u);
 }
 // SMALL: gradients up to 1020 (Sobel of U8): the hardware's root, rounded to
-// the nearest integer, is the rounded root of every sum up to 2 * 1020^2 (each
-// of them compared).  Adding 2^23 rounds it and leaves the integer in the low
-// half, which is all that packing takes: 5 instructions a pixel instead of 10.
+// the nearest integer, is the rounded root of the sum (test_gpu_roots.py
+// compares all pairs of gradients).  Adding 2^23 rounds it and leaves the
+// integer in the low half, which is all that packing takes: 5 instructions a
+// pixel instead of 10.
 template <bool SMALL, int LP>
 __device__ __forceinline__ PR<LP> row_magnitude(const PR<LP>& a, const PR<LP>& b) {
   const WR<LP> x = wide(a), y = wide(b);
