@@ -1119,6 +1119,8 @@ std::mutex g_cache_mu;
 // never freed: code objects stay loaded until the process ends
 std::map<std::string, GenKernel*>* g_cache = new std::map<std::string, GenKernel*>();  // by source text
 std::map<std::string, GenKernel*>* g_by_program = new std::map<std::string, GenKernel*>();
+// programs whose source the compiler rejected, with its log
+std::map<std::string, std::string>* g_rejected = new std::map<std::string, std::string>();
 }  // namespace
 
 bool gen_wanted(const GProg& P) {
@@ -1171,7 +1173,9 @@ static bool gen_source(const GProg& P, int tw, int th, uint32_t stream, GenSourc
 }
 
 // Compile the kernel for `src`, or find it by its text (g_cache_mu is held).
-static GenKernel* gen_compile(const GenSource& src, std::string* why) {
+// *rejected: null because the source does not compile.
+static GenKernel* gen_compile(const GenSource& src, std::string* why, bool* rejected) {
+  *rejected = false;
   const bool stream = src.form == GEN_STREAM;
   const std::string key = (stream ? "stream " : "") + src.text;
   auto it = g_cache->find(key);
@@ -1195,6 +1199,7 @@ static GenKernel* gen_compile(const GenSource& src, std::string* why) {
                         "-packed-fp32-ops", "-w", stream ? "-DHVX_GEN_STREAM_ONLY" : "-DHVX_GEN_TILES"};
   const hiprtcResult r = hiprtcCompileProgram(prog, (int)(sizeof opts / sizeof opts[0]), opts);
   if (r != HIPRTC_SUCCESS) {
+    *rejected = r == HIPRTC_ERROR_COMPILATION;
     size_t n = 0;
     hiprtcGetProgramLogSize(prog, &n);
     std::string log(n, '\0');
@@ -1230,10 +1235,17 @@ const GenKernel* gen_kernel(const GProg& P, int tw, int th, uint32_t stream, std
   std::lock_guard<std::mutex> l(g_cache_mu);
   auto it = g_by_program->find(key);
   if (it != g_by_program->end()) return it->second;
+  auto no = g_rejected->find(key);
+  if (no != g_rejected->end()) {
+    *why = no->second;
+    return nullptr;
+  }
   GenSource src;
   if (!gen_source(P, tw, th, stream, &src, why)) return nullptr;
-  GenKernel* k = gen_compile(src, why);
+  bool rejected = false;
+  GenKernel* k = gen_compile(src, why, &rejected);
   if (k) (*g_by_program)[key] = k;
+  else if (rejected) (*g_rejected)[key] = *why;
   return k;
 }
 
