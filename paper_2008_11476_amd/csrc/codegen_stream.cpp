@@ -210,7 +210,7 @@ struct Planner {
     }
     LP = any_wide ? 4 : 8;
     plan_slides();
-    T = stream_bands(8, 0, kUnroll, E).tail;
+    T = stream_tail(E);
     int emax = 0;
     for (int i = 0; i < nv; ++i) emax = std::max(emax, eh[i]);
     halo = (emax + LP - 1) / LP;

@@ -38,16 +38,24 @@ constexpr int kStreamUnroll = 4;
 // item, 6.9 in bands (tiles 7.4), the F32 corner response 2513 and 13.1
 // (15.4), four Gaussian5x5 4003 and 24.9 (20.9); 640x19, three Gaussian5x5
 // 20.2 and 12.1 (13.6).
+//
+// Every wave starts with this, so what depends on `whole` is decided once, not
+// per band (Gaussian3x3 -> Histogram + MeanStdDev of 3840x2160, whose waves
+// take several bands, 14.9 -> 14.6 us).
 struct StreamBands {
-  int32_t h, rows, tail, shift, n;
+  int32_t rows, n;
+  int32_t end, shift, tail;  // the first row after those dealt out; shift and tail: 0 unless whole
   bool whole;
 };
+__host__ __device__ inline int stream_tail(int ext) {
+  return (ext + kStreamUnroll - 1) / kStreamUnroll * kStreamUnroll;
+}
 __host__ __device__ inline StreamBands stream_bands(int w, int h, int rows, int ext) {
-  const int tail = (ext + kStreamUnroll - 1) / kStreamUnroll * kStreamUnroll;
-  const int shift = (tail - h) & (kStreamUnroll - 1), main_rows = h - tail + shift;
+  const int tail = stream_tail(ext), shift = (tail - h) & (kStreamUnroll - 1);
   const bool whole = w >= 8 && h >= tail + 2 * kStreamUnroll && rows % kStreamUnroll == 0 && rows >= ext + shift &&
-                     (shift == 0 || main_rows > rows);
-  return {h, rows, tail, shift, ((whole ? main_rows : h) + rows - 1) / rows + (whole && tail > 0 ? 1 : 0), whole};
+                     (shift == 0 || h - tail + shift > rows);
+  const int t = whole ? tail : 0, s = whole ? shift : 0;
+  return {rows, (int)((unsigned)(h - t + s + rows - 1) / (unsigned)rows) + (t > 0 ? 1 : 0), h - t, s, t, whole};
 }
 // Band `band`: output rows [y0, y1) (`last`: the image's last rows follow), of
 // which those from `own` on are the next band's to count.
@@ -56,10 +64,9 @@ struct StreamBand {
   bool last;
 };
 __host__ __device__ inline StreamBand stream_band(const StreamBands& b, int band) {
-  const bool last = b.whole && b.tail > 0 && band + 1 == b.n;
-  const int end = b.whole ? b.h - b.tail : b.h, shift = b.whole && band > 0 ? b.shift : 0;
-  const int y0 = last ? end : band * b.rows - shift, y1 = last ? y0 : y0 + b.rows < end ? y0 + b.rows : end;
-  const int next = (band + 1) * b.rows - (b.whole ? b.shift : 0);  // the next band's first row
+  const bool last = b.tail > 0 && band + 1 == b.n;
+  const int start = band > 0 ? band * b.rows - b.shift : 0, y0 = last ? b.end : start;
+  const int y1 = last ? y0 : start + b.rows < b.end ? start + b.rows : b.end, next = (band + 1) * b.rows - b.shift;
   return {y0, y1, next < y1 ? next : y1, last};
 }
 
