@@ -113,8 +113,10 @@ __device__ __forceinline__ uint32_t isqrt_u32(uint32_t s) {
 // root (test_gpu_roots.py compares every float of two binades in the middle
 // and at both ends of the range).  5 instructions and the root instead of
 // 16 and the root, most of which scale small numbers.  With the scalings that
-// emit_expr folds into sums, 32 3840x2160 Tomasi frames: 366 -> 334 us.
+// emit_expr folds into sums, 32 3840x2160 Tomasi frames: 366 -> 334 us.  A
+// literal's root is left to the compiler, which knows it.
 __device__ __forceinline__ float sqrt_bounded(float x) {
+  if (__builtin_constant_p(x)) return __builtin_sqrtf(x);
   const float y = __builtin_amdgcn_rsqf(fmaxf(x, 0x1p-96f)), s = x * y;
   return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
 }

@@ -33,3 +33,27 @@ def test_long_user_kernels_are_generated(ctx, terms):
         hvx.hvx_graph_verify(g)
         assert hvx.hvx_graph_query(g, hvx.HVX_QUERY_NUM_GENERATED) == 1, expr
         hvx.hvx_release_graph(g)
+
+
+def test_the_root_of_a_literal_is_a_constant(ctx, tmp_path, monkeypatch):
+    """Roots of bounded numbers are formed from the hardware's reciprocal root;
+    of a literal, by the compiler."""
+    import glob
+    import subprocess
+    from paper_2008_11476_amd import build
+    monkeypatch.setenv("HVX_GEN_DUMP", str(tmp_path))
+    g = hvx.hvx_graph_create(ctx)
+    a = hvx.hvx_image_from_ptr(ctx, 640, 480, hvx.HVX_DF_U8, FAKE, 640)
+    o = hvx.hvx_image_from_ptr(ctx, 640, 480, hvx.HVX_DF_F32, FAKE + (1 << 28), 2560)
+    hvx.hvx_custom_point_node(g, "a * sqrt(2) + sqrt(abs(-7) * 3)", [a], hvx.HVX_DF_F32, o)
+    hvx.hvx_graph_verify(g)
+    src, = glob.glob(str(tmp_path / "hvx_gen_*.hip"))
+    text = open(src).read()
+    assert text.count("sqrt_bounded(") == 2
+    (tmp_path / "k.hip").write_text(text.replace("namespace __hip_internal {}\nusing namespace __hip_internal;\n", ""))
+    csrc = os.path.join(os.path.dirname(build.__file__), "csrc")
+    r = subprocess.run([build._hipcc(), "-x", "hip", "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only",
+                        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-w", "-S", "-I", csrc,
+                        str(tmp_path / "k.hip"), "-o", "-"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    assert "v_rsq" not in r.stdout and "v_sqrt" not in r.stdout
