@@ -813,7 +813,6 @@ struct Planner {
     t("  }");
     const int strip_px = (64 - 2 * halo) * LP;
     emit_geometry(strip_px);
-    t("  if (item >= strips * bd.n) return;");
     t("  SxRed red;");
     emit_item();
     t("}");

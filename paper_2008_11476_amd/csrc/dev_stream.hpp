@@ -293,8 +293,10 @@ __device__ __forceinline__ Strip<LP> make_strip(int strip, int halo, int out_lan
   s.W = W;
   s.H = H;
   s.zl = strip == 0 ? halo : -1;
-  s.rl = (W - 1 - base) / LP;
-  s.rq = (W - 1) % LP;
+  // (unsigned: rq is then known to lie in 0 .. LP - 1, which saves an edge
+  // strip's row of F32 pixels 6 of 164 vector instructions)
+  s.rl = (int)((unsigned)(W - 1 - base) / LP);
+  s.rq = (int)((unsigned)(W - 1) % LP);
   s.left = s.x0 < 0;
   s.ml = s.x0 == -LP ? 0xFFFF0000u : 0u;
 #pragma unroll

@@ -41,7 +41,8 @@ constexpr int kStreamUnroll = 4;
 //
 // Every wave starts with this, so what depends on `whole` is decided once, not
 // per band (Gaussian3x3 -> Histogram + MeanStdDev of 3840x2160, whose waves
-// take several bands, 14.9 -> 14.6 us).
+// take several bands, 14.9 -> 14.6 us), and a band is found without their number
+// n, a division that only the host and the reducing kernels make.
 struct StreamBands {
   int32_t rows, n;
   int32_t end, shift, tail;  // the first row after those dealt out; shift and tail: 0 unless whole
@@ -64,8 +65,9 @@ struct StreamBand {
   bool last;
 };
 __host__ __device__ inline StreamBand stream_band(const StreamBands& b, int band) {
-  const bool last = b.tail > 0 && band + 1 == b.n;
-  const int start = band > 0 ? band * b.rows - b.shift : 0, y0 = last ? b.end : start;
+  const int start = band > 0 ? band * b.rows - b.shift : 0;
+  const bool last = b.tail > 0 && start >= b.end;
+  const int y0 = last ? b.end : start;
   const int y1 = last ? y0 : start + b.rows < b.end ? start + b.rows : b.end, next = (band + 1) * b.rows - b.shift;
   return {y0, y1, next < y1 ? next : y1, last};
 }
