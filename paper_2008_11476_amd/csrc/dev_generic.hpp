@@ -118,7 +118,9 @@ __device__ __forceinline__ uint32_t isqrt_u32(uint32_t s) {
 __device__ __forceinline__ float sqrt_bounded(float x) {
   if (__builtin_constant_p(x)) return __builtin_sqrtf(x);
   const float y = __builtin_amdgcn_rsqf(fmaxf(x, 0x1p-96f)), s = x * y;
-  return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+  const float r = __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+  __builtin_assume(r >= 0.f);  // as the compiler knows of its own root
+  return r;
 }
 
 __device__ __forceinline__ int sat_u8(int v) { return min(max(v, 0), 255); }

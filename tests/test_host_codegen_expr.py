@@ -35,9 +35,8 @@ def test_long_user_kernels_are_generated(ctx, terms):
         hvx.hvx_release_graph(g)
 
 
-def test_the_root_of_a_literal_is_a_constant(ctx, tmp_path, monkeypatch):
-    """Roots of bounded numbers are formed from the hardware's reciprocal root;
-    of a literal, by the compiler."""
+def _assembly(ctx, tmp_path, monkeypatch, expr):
+    """The source and the assembly of an F32 point kernel of one U8 image."""
     import glob
     import subprocess
     from paper_2008_11476_amd import build
@@ -45,15 +44,25 @@ def test_the_root_of_a_literal_is_a_constant(ctx, tmp_path, monkeypatch):
     g = hvx.hvx_graph_create(ctx)
     a = hvx.hvx_image_from_ptr(ctx, 640, 480, hvx.HVX_DF_U8, FAKE, 640)
     o = hvx.hvx_image_from_ptr(ctx, 640, 480, hvx.HVX_DF_F32, FAKE + (1 << 28), 2560)
-    hvx.hvx_custom_point_node(g, "a * sqrt(2) + sqrt(abs(-7) * 3)", [a], hvx.HVX_DF_F32, o)
+    hvx.hvx_custom_point_node(g, expr, [a], hvx.HVX_DF_F32, o)
     hvx.hvx_graph_verify(g)
     src, = glob.glob(str(tmp_path / "hvx_gen_*.hip"))
     text = open(src).read()
-    assert text.count("sqrt_bounded(") == 2
     (tmp_path / "k.hip").write_text(text.replace("namespace __hip_internal {}\nusing namespace __hip_internal;\n", ""))
     csrc = os.path.join(os.path.dirname(build.__file__), "csrc")
     r = subprocess.run([build._hipcc(), "-x", "hip", "-O3", "-std=c++17", "--offload-arch=gfx950", "--cuda-device-only",
                         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-w", "-S", "-I", csrc,
                         str(tmp_path / "k.hip"), "-o", "-"], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    assert "v_rsq" not in r.stdout and "v_sqrt" not in r.stdout
+    return text, r.stdout
+
+
+@pytest.mark.parametrize("expr,roots", [("a * sqrt(2) + sqrt(abs(-7) * 3)", 2), ("sel(gt(0, sqrt(a * 3)), a * 5, a - 1)", 1)],
+                         ids=["literal", "comparison"])
+def test_roots_that_the_compiler_can_spare(ctx, tmp_path, monkeypatch, expr, roots):
+    """Roots of bounded numbers are formed from the hardware's reciprocal root;
+    that of a literal is a constant all the same, and one that is only compared
+    with what it cannot be under is not formed."""
+    text, asm = _assembly(ctx, tmp_path, monkeypatch, expr)
+    assert text.count("sqrt_bounded(") == roots
+    assert "v_rsq" not in asm and "v_sqrt" not in asm
