@@ -398,10 +398,12 @@ hvx_status hvx_graph_query(hvx_graph g, int attr, int64_t* out);
  * else the call fails).  Candidates (Section 6.3): the fused plan, each plan
  * that cuts fusion at one value inside a fused group, the plan that cuts at
  * all of them, then the tile of each generated kernel; for a plan of one
- * hand-fused kernel, its rows per work item and XCD mapping.  The plan choice
- * is recorded under the graph's operator signature, so any graph built the
- * same way (same operators, borders, formats and sizes, same options) is
- * verified with it; the launch shape under the graph's kernel signature.
+ * hand-fused kernel, its rows per work item and XCD mapping (of a launch of
+ * the graph alone: batches and server steps of several choose their own rows).
+ * The plan choice is recorded under the graph's operator signature, so any
+ * graph built the same way (same operators, borders, formats and sizes, same
+ * options) is verified with it; the launch shape under the graph's kernel
+ * signature.
  * The graph is re-planned: batches built on it must be created again. */
 hvx_status hvx_graph_autotune(hvx_graph g, void* hip_stream, int iters);
 /* Tune cache as JSON text keyed by device, graph signature and size. */
@@ -455,7 +457,10 @@ hvx_status hvx_batch_autotune(hvx_batch b, void* hip_stream, int iters);
 #define HVX_SERVER_PLAIN 1      /* one request at a time: copy in, process, copy out, wait */
 
 /* A request loop over device memory of at most hbm_budget_bytes, holding at
- * most max_slots requests on the device, using n_streams streams (>= 1). */
+ * most max_slots requests on the device, using n_streams streams (>= 1).  Its
+ * worker thread keeps one CPU core busy while a step runs on the device, for
+ * up to 500 us after the last event of the loop; otherwise it sleeps between
+ * looks, 50 us at a time. */
 hvx_status hvx_server_create(hvx_context ctx, int mode, size_t hbm_budget_bytes, uint32_t max_slots,
                              uint32_t n_streams, hvx_server* out);
 /* Queue a request: run verified `templ` (one non-virtual input image, one

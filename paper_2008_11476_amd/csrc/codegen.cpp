@@ -1307,10 +1307,11 @@ static int band_rows(const GenKernel* k, long long strip_rows, int unit, int lea
   // an item's start), shared by the SIMDs, plus about one item's latency at
   // the end, a step of a wave alone taking some 2.5 times its issue: the sum
   // is least at r^2 = 0.4 strip_rows (ext + 3) / SIMDs.  Measured: 1080p and
-  // smaller frames are fastest at 4 to 8 rows (640x480 Tomasi 5.8 us against
-  // 11.7 at 16), one 4K frame at 4 to 12, batches at 20 to 48 (32 4K frames:
-  // Tomasi 327 us at 32 rows, 459 at 4, 335 at 96); over five graphs and six
-  // launches the rule is within 14% of the best rows, mostly within 5%.
+  // smaller frames are fastest at 4 to 8 rows (640x480 Tomasi 5.0 us against
+  // 10.9 at 16), one 4K frame at 4 to 20, batches at 8 to 48 (eight 4K frames:
+  // Tomasi 91.5 us at 20 rows, 117 at 4, 104 at 64); over five graphs and six
+  // launches each the rule takes 15% longer than the best rows at most, 4% in
+  // the median.
   const double simds = 4.0 * (num_cus > 0 ? num_cus : 256);
   if (k->red) {
     // the waves of a reducing kernel go on from item to item: whole rounds of

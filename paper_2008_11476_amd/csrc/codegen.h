@@ -27,7 +27,7 @@ constexpr int kStreamRedWaves = 8;
 // Launch shape of a generated kernel.
 enum GenForm : int32_t {
   GEN_POINTS = 1,  // point operators only: four pixels of one row per thread, no LDS
-  GEN_TILES = 2,   // LDS tiles with halos: what GEN_STREAM does not cover; work-groups loop over tiles when the group reduces
+  GEN_TILES = 2,   // LDS tiles with halos: what GEN_STREAM does not cover, one work-group per tile
   GEN_STREAM = 3,  // a wave streams a strip of columns down a band of rows, values in registers
 };
 

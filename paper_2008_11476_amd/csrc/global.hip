@@ -1,11 +1,12 @@
 // Global operators (Table 2): operators that read every pixel of an image
 // and produce a few values.  Each kernel streams the image once in 16-byte
-// chunks (the chunks of all rows dealt out over all threads, four loaded
-// together, so that every lane has four independent loads in flight),
-// reduces inside the wave with lane exchanges, and combines work-groups with
-// one global atomic per group (per bin for the histogram).  The caller's result buffer is
-// initialised by a small kernel in the same stream, so the sequence can be
-// captured into a HIP graph.
+// chunks (the chunks of all rows dealt out over all threads, several loaded
+// together per thread so that every lane has independent loads in flight: eight
+// in the histogram, four in the others) and reduces inside the wave with lane
+// exchanges.  Work-groups combine with one global atomic per group (per bin for
+// the histogram) into a result that a small kernel in the same stream has
+// initialised; the counts of the extremes go to a key per group, which a last
+// kernel merges.  Kernels only, so the sequence can be captured into a HIP graph.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <stdint.h>

@@ -11,11 +11,11 @@
 // CONTINUOUS mode: a worker thread admits queued requests in arrival order
 // while their device memory fits in the HBM budget and a slot is free, packs
 // every admitted request into one device step (host-to-device copies, one
-// batch launch over all their work items plus the plans of the other
-// templates, device-to-host copies) on a stream with no step in flight, and
-// retires steps as their completion events fire.  With n_streams >= 2,
-// requests that arrive while a step runs start in a new step that overlaps
-// it on the device.
+// launch over the work items of every sixteen requests that join it plus the
+// plans of the other templates, device-to-host copies) on a stream with no step
+// in flight, and retires steps as their completion events fire.  With
+// n_streams >= 2, requests that arrive while a step runs start in a new step
+// that overlaps it on the device.
 //
 // PLAIN mode: one request at a time, each with its own copies, its own
 // kernel launches and a wait, the way a program calling process per frame
